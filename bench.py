@@ -67,7 +67,7 @@ def log(msg):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("mpt_device.hpp", "mpt_solve.hip", "mpt_internal.hpp"):
+    for f in ("mpt_device.hpp", "mpt_path.hpp", "mpt_lm.hip", "mpt_solve.hip", "mpt_internal.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2301_06399_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -304,7 +304,7 @@ mpt_status mpt_solve_batch(mpt_ctx *ctx, const mpt_batch_desc *batch, const mpt_
  * harnesses that forbid hipMalloc).  Same arguments, kernels and results as
  * mpt_solve_batch with spill = 0.  Its counters and lists live in a static
  * device scratch array of the library, sized for at most
- * MPT_NOALLOC_MAX_SOLVES solves (37.8 MB, held by every GPU the library
+ * MPT_NOALLOC_MAX_SOLVES solves (12.6 MB, held by every GPU the library
  * runs on until the process ends); the counters are cleared by a fill
  * kernel at the start of every call.  Every call on one GPU shares that
  * scratch, so calls that overlap on one GPU (other contexts or streams)

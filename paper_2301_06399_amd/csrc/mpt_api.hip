@@ -44,15 +44,15 @@ struct mpt_ctx {
     bool refr = false;       // some facet of the scene refracts
     bool param_ok = true;    // every quadric is a paraboloid of revolution
     uint64_t scene_hash = 0; // FNV-1a of the uploaded records and TX: the tuning key
-    // workspace: counters | perm | polish lists | fallback lists
+    // workspace: counters | perm | polish, fallback and straggler lists | state
+    // rows of the FP32 pass [n][32], or the parked FP64 stragglers' damping,
+    // plateau reference and stall count [3][n]
     int *ws = nullptr;
-    size_t ws_cap = 0;  // solves
+    size_t ws_cap = 0;  // ints
     int *blk = nullptr;
     size_t blk_cap = 0;
     double *x0l = nullptr;
     size_t x0l_cap = 0;
-    double *spf = nullptr;  // parked stragglers: damping, plateau reference, stall count [3][n]
-    size_t spf_cap = 0;
     int *scratch = nullptr;  // this device's copy of the allocation-free solve's scratch (device address)
     std::string scratch_err;
     hipEvent_t ev[7] = {};
@@ -83,13 +83,14 @@ static const int kSpillCounters = 32 + kKeyCounters;
 static const int kCounters = kSpillCounters + 16;
 
 // Scratch of the allocation-free solve (mpt_solve_batch_noalloc): the
-// counters, the perm / polish / fallback lists and the bin-ordered receiver
-// and primitive ids of at most MPT_NOALLOC_MAX_SOLVES solves (37.8 MB).  Every GPU the library runs on
+// counters and the perm / polish / fallback lists of at most
+// MPT_NOALLOC_MAX_SOLVES solves (12.6 MB; the FP32 pass keeps its state rows in
+// the caller's output rows).  Every GPU the library runs on
 // holds its own copy until the process ends, and every such call on that
 // GPU shares it.  In host code `scratch` names a host-side stand-in: its
 // device address comes from hipGetSymbolAddress, once per device, when a
 // context is created there (scratch_setup).
-static const size_t kScratchInts = (size_t)kCounters + 9 * (size_t)MPT_NOALLOC_MAX_SOLVES;
+static const size_t kScratchInts = (size_t)kCounters + 3 * (size_t)MPT_NOALLOC_MAX_SOLVES;
 static __device__ __align__(256) int scratch[kScratchInts];
 static const int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -208,7 +209,6 @@ mpt_status mpt_destroy(mpt_ctx *c)
     hipFree(c->ws);
     hipFree(c->blk);
     hipFree(c->x0l);
-    hipFree(c->spf);
     mlp_free(c->mlp);
     for (auto &e : c->ev) hipEventDestroy(e);
     for (int i = 0; i < MPT_MAX_ORDER; i++) {
@@ -444,14 +444,15 @@ static mpt_status batch_dev(mpt_ctx *c, const mpt_batch_desc *b, BatchDev &bd)
     return MPT_OK;
 }
 
-// Blocks of a persistent launch: as many as can be resident at once.
-static int resident_grid(mpt_ctx *c, const void *kern, int block, int64_t n, size_t lds = 0)
+// Blocks of a persistent launch: as many as can be resident at once, and no
+// more than n paths can use at `per_block` paths a block.
+static int resident_grid(mpt_ctx *c, const void *kern, int block, int64_t n, int per_block, size_t lds = 0)
 {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, lds) != hipSuccess || per_cu < 1)
         per_cu = 1;
     int64_t g = (int64_t)per_cu * c->cu;
-    const int64_t need = (n + block - 1) / block;
+    const int64_t need = (n + per_block - 1) / per_block;
     if (need < g) g = need;
     return (int)(g < 1 ? 1 : g);
 }
@@ -582,21 +583,28 @@ static mpt_status check_opts(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solv
     return MPT_OK;
 }
 
+// Where the state rows (whole 128-byte lines) or the parked FP64 state lie in
+// the workspace of n paths, in ints.
+static size_t state_offset(size_t n) { return (kCounters + 4 * n + 31) / 32 * 32; }
+
 // Work buffers of a solve of n paths (sized before any graph capture).
-static mpt_status size_buffers(mpt_ctx *c, int64_t n, bool learned)
+static mpt_status size_buffers(mpt_ctx *c, int64_t n, const mpt_solve_opts *o)
 {
     const size_t m = (size_t)(n > 0 ? n : 1);
+    const bool learned = o->init == MPT_INIT_LEARNED || o->init == MPT_INIT_LEARNED_ALL;
     mpt_status st;
-    if ((st = ensure(c, (void **)&c->ws, &c->ws_cap, kCounters + 10 * m, sizeof(int)))) return st;
-    if ((st = ensure(c, (void **)&c->spf, &c->spf_cap, 3 * m, sizeof(double)))) return st;
+    const size_t state = (o->precision == MPT_FP64_PLAIN ? 6 : 32) * m;
+    if ((st = ensure(c, (void **)&c->ws, &c->ws_cap, state_offset(m) + state, sizeof(int)))) return st;
     if (learned && (st = ensure(c, (void **)&c->x0l, &c->x0l_cap, MPT_ROW * m, sizeof(double)))) return st;
     return MPT_OK;
 }
 
-// Workspace of one solve: counters and lists (int32), parked straggler
-// state and network start points (FP64; null when unused).
+// Workspace of one solve: counters and lists (int32), state rows of the FP32
+// pass (FP32), parked straggler state and network start points (FP64); null
+// when unused.
 struct Work {
     int *ws;
+    float *rows;
     double *spf, *x0l;
 };
 
@@ -613,13 +621,16 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
     const int64_t n = b->n;
     const bool learned = opts->init == MPT_INIT_LEARNED || opts->init == MPT_INIT_LEARNED_ALL;
     if (c->refr) sched = MPT_SCHED_PERSISTENT, gdiv = 1;  // the only kernel with refracting rows
-    Work own{nullptr, nullptr, nullptr};
+    const bool fp64 = opts->precision == MPT_FP64_PLAIN;
+    Work own{nullptr, nullptr, nullptr, nullptr};
     if (!w) {
-        if ((st = size_buffers(c, n, learned))) return st;
-        own = Work{c->ws, c->spf, c->x0l};
+        if ((st = size_buffers(c, n, opts))) return st;
+        int *state = c->ws + state_offset((size_t)(n > 0 ? n : 1));
+        own = Work{c->ws, fp64 ? nullptr : (float *)state, fp64 ? (double *)state : nullptr, c->x0l};
         w = &own;
     }
-    if ((learned && !w->x0l) || (spill > 0 && !w->spf)) return fail(c, MPT_E_INVALID_ARG, "workspace too small");
+    if ((learned && !w->x0l) || (spill > 0 && (fp64 ? !w->spf : !w->rows)))
+        return fail(c, MPT_E_INVALID_ARG, "workspace too small");
     if (!timed) c->timed = c->kev_valid = false;  // no stale stage timings
     int *ctr = w->ws;
     KParams kp{};
@@ -655,13 +666,12 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
     kp.perm = ctr + kCounters;
     kp.pol_list = ctr + kCounters + n;
     kp.fb_list = ctr + kCounters + 2 * n;
-    kp.slot_rx = ctr + kCounters + 3 * n;
-    kp.slot_prim = ctr + kCounters + 4 * n;
+    kp.rows = w->rows;
     kp.spill_t = spill;
     kp.refill = opts->refill > 1 ? (opts->refill < 64 ? opts->refill : 64) : 1;
     kp.spill_cnt = ctr + kSpillCounters;
     kp.spill_head = ctr + kSpillCounters + 5;
-    kp.spill_list = w->spf ? ctr + kCounters + 9 * n : nullptr;
+    kp.spill_list = spill > 0 ? ctr + kCounters + 3 * n : nullptr;
     kp.spill_f = w->spf;
 
     // the network serves the paths with a curved object: none without
@@ -673,8 +683,9 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
     int *rows = (net && opts->init == MPT_INIT_LEARNED) ? (int *)kp.pol_list : nullptr, *rows_cnt = ctr + 30;
     if (timed) hipEventRecord(c->ev[0], s);
     launch_zero(ctr, kCounters, s);
-    launch_bin(bd, kp.out, c->s, ctr + 0, ctr + 32, (int *)kp.perm, (int *)kp.slot_rx, (int *)kp.slot_prim, rows,
-               ctr + 5, s);
+    launch_bin(bd, kp.out, c->s, ctr + 0, ctr + 32, (int *)kp.perm, kp.rows != nullptr, rows, ctr + 5, s);
+    const int mode = fp64 ? MODE_PLAIN64 : MODE_FP32;
+    launch_start(mode, form_used, kp, s);
     if (timed) hipEventRecord(c->ev[1], s);
     if (net) {
         if (opts->init == MPT_INIT_LEARNED) {
@@ -685,9 +696,9 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
             if (!st) launch_learned_choose(c->s, bd, nullptr, nullptr, true, w->x0l, opts->learned_gain, c->refr, s);
         }
         if (st) return fail(c, st, "network forward failed");
+        launch_learned_begin(mode, form_used, kp, rows, rows ? rows_cnt : nullptr, s);
     }
     if (timed) hipEventRecord(c->ev[2], s);
-    const int mode = (opts->precision == MPT_FP64_PLAIN) ? MODE_PLAIN64 : MODE_FP32;
     auto run_lm = [&](int md, int sch, int blk, bool first) {
         // stage the scene in LDS when it fits
         const size_t rec_bytes = (size_t)c->s.n_all * kRec * (md == MODE_FP32 ? sizeof(float) : sizeof(double));
@@ -700,7 +711,9 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
             if (!g) {
                 // all resident blocks, divided by gdiv for the concurrent
                 // per-order launches (fewer waves per SIMD in their tails)
-                g = resident_grid(c, k, blk, n, lds ? rec_bytes : 0);
+                // a small batch gets a wave per path: what it waits for is its
+                // longest descent, which lanes of other types only slow down
+                g = resident_grid(c, k, blk, n, blk / 64, lds ? rec_bytes : 0);
                 if (first && gdiv > 1) g = (g + gdiv - 1) / gdiv;
             }
             launch_lm(md, ord, lds, form, c->refr, rec_bytes, kp, g, blk, where);
@@ -743,8 +756,8 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
     }
     if (timed) hipEventRecord(c->ev[4], s);
     if (n > 0 && mode == MODE_FP32) {
-        launch_polish_list(kp, s);
-        launch_polish(kp, c->refr, resident_grid(c, polish_kernel(c->refr), 256, n), 256, s);
+        launch_finish(form_used, c->refr, kp, c->cu, s);
+        launch_polish(kp, c->refr, resident_grid(c, polish_kernel(c->refr), 256, n, 256), 256, s);
     }
     if (timed) hipEventRecord(c->ev[5], s);
     // the fallback handles a handful of paths: one mixed-order launch
@@ -793,8 +806,7 @@ mpt_status mpt_solve_batch(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_
         if (c->gexec) hipGraphExecDestroy(c->gexec), c->gexec = nullptr;
         if (!c->cap) HIPCHK(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
         // buffers are sized before capture: no allocation inside it
-        const bool learned = opts->init == MPT_INIT_LEARNED || opts->init == MPT_INIT_LEARNED_ALL;
-        if ((st = size_buffers(c, b->n, learned))) return st;
+        if ((st = size_buffers(c, b->n, opts))) return st;
         HIPCHK(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
         st = enqueue_solve(c, b, opts, out, c->cap, false, sched, block, gdiv, spill, form);
         hipGraph_t g = nullptr;
@@ -836,7 +848,7 @@ mpt_status mpt_solve_batch_noalloc(mpt_ctx *c, const mpt_batch_desc *b, const mp
     const int32_t chosen[5] = {sched, block, gdiv, spill, form};
     memcpy(c->last_launch, chosen, sizeof chosen);
     c->launched = true;
-    const Work w{c->scratch, nullptr, nullptr};
+    const Work w{c->scratch, nullptr, nullptr, nullptr};
     return enqueue_solve(c, b, opts, out, c->stream, c->timing, sched, block, gdiv, spill, form, &w);
 }
 

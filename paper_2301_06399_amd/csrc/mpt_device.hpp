@@ -95,214 +95,238 @@ template <typename T>
 __host__ __device__ __forceinline__ T dot3(const T *a, const T *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
 
 // -------------------------------------------------------------------------
-// Rows of one interaction (5 slots: 0..2 law rows, 3..4 object rows; unused
-// slots are exactly zero with zero derivatives).  Law rows are the unit-form
-// laws scaled by S = (|i| + |r|)/2 (metres):
-//   reflection  S (r^ - i^ + 2 <i^,n^> n^)                (Eqs. 1, 2, 8)
-//   diffraction S <i^ - r^, e^>                           (Eqs. 3, 4, 9)
-// object rows: f(X) for a surface; for a straight edge the two coordinates
-// across the line; for a circle the distance to its plane and
-// (|X-c|^2 - R^2)/(2R)                                     (Eq. 11)
-// Derivative blocks: Jp = d/dX_{k-1} (law rows), Jk = d/dX_k (all rows),
-// Jn = d/dX_{k+1} (law rows).
-// Returns false when a direction is undefined (degenerate).  REFR = false
-// compiles the refracting-facet rows out (scenes without such facets).
+// Rows of one interaction.  Law rows are the unit-form laws scaled by
+// S = (|i| + |r|)/2 (metres):
+//   reflection  S (r^ - i^ + 2 <i^,n^> n^)   three rows      (Eqs. 1, 2, 8)
+//   diffraction S <i^ - r^, e^>              one row         (Eqs. 3, 4, 9)
+// object rows: f(X) for a surface (one row); for a straight edge the two
+// coordinates across the line; for a circle the distance to its plane and
+// (|X-c|^2 - R^2)/(2R)                                        (Eq. 11)
+// Derivative blocks: Jp = d/dX_{k-1} (law rows), Jk = d/dX_k, Jn =
+// d/dX_{k+1} (law rows).  Surfaces and edges have functions of their own, so
+// that a caller accumulates exactly the rows a type has.
 // -------------------------------------------------------------------------
-template <typename T, bool WITH_J, bool REFR = true>
-__host__ __device__ __forceinline__ bool interaction_rows(int t, const T *__restrict__ r, const T *Xp, const T *Xk,
-                                                 const T *Xn, T u[5], T Jp[3][3], T Jk[5][3], T Jn[3][3])
+
+// The unit directions in and out of a point, their inverse lengths and the
+// row scale.  valid: both segments have a length (no early exit: an
+// undefined direction continues on a harmless substitute value).
+template <typename T>
+struct Dirs {
+    T ih[3], rh[3], ia, ib, S;
+    bool valid;
+};
+
+template <typename T>
+__host__ __device__ __forceinline__ Dirs<T> directions(const T *Xp, const T *Xk, const T *Xn)
 {
-    // No early exits: an undefined direction sets valid = false and the
-    // arithmetic continues on a harmless substitute value.
-    bool valid = true;
+    Dirs<T> D;
     T a[3], b[3];
 #pragma unroll
     for (int i = 0; i < 3; i++) { a[i] = Xk[i] - Xp[i]; b[i] = Xn[i] - Xk[i]; }
     T la2 = dot3(a, a), lb2 = dot3(b, b);
-    valid = valid && (la2 > T(0)) && (lb2 > T(0));
+    D.valid = (la2 > T(0)) && (lb2 > T(0));
     la2 = (la2 > T(0)) ? la2 : T(1);
     lb2 = (lb2 > T(0)) ? lb2 : T(1);
     const T ia = drsqrt(la2), ib = drsqrt(lb2);
     const T la = la2 * ia, lb = lb2 * ib;
-    T ih[3], rh[3];
 #pragma unroll
-    for (int i = 0; i < 3; i++) { ih[i] = a[i] * ia; rh[i] = b[i] * ib; }
-    const T S = T(0.5) * (la + lb);
-    if (t == TP || t == TQ) {
-        // plane: g = n, f = n.X - d.  quadric: w = X - p, g = 2 A w + b,
-        // f = w^T A w + b^T w + c, with A = [[a0 a1 a2][a1 a3 a4][a2 a4 a5]]
-        T g[3], f;
+    for (int i = 0; i < 3; i++) { D.ih[i] = a[i] * ia; D.rh[i] = b[i] * ib; }
+    D.ia = ia;
+    D.ib = ib;
+    D.S = T(0.5) * (la + lb);
+    return D;
+}
+
+// A plane or quadric: u[0..2] law rows, u[3] the object row; Jg = d u[3]/dX_k.
+// Returns false when the normal is undefined.  REFR = false compiles the
+// refracting-facet rows out (scenes without such facets).
+template <typename T, bool WITH_J, bool REFR = true>
+__host__ __device__ __forceinline__ bool surface_rows(int t, const T *__restrict__ r, const Dirs<T> &D, const T *Xk,
+                                                      T u[4], T Jp[3][3], T Jk[3][3], T Jn[3][3], T Jg[3])
+{
+    const T *ih = D.ih, *rh = D.rh;
+    const T ia = D.ia, ib = D.ib, S = D.S;
+    // plane: g = n, f = n.X - d.  quadric: w = X - p, g = 2 A w + b,
+    // f = w^T A w + b^T w + c, with A = [[a0 a1 a2][a1 a3 a4][a2 a4 a5]]
+    T g[3], f;
+    if (t == TQ) {
+        const T w0 = Xk[0] - r[0], w1 = Xk[1] - r[1], w2 = Xk[2] - r[2];
+        const T Aw0 = r[3] * w0 + r[4] * w1 + r[5] * w2;
+        const T Aw1 = r[4] * w0 + r[6] * w1 + r[7] * w2;
+        const T Aw2 = r[5] * w0 + r[7] * w1 + r[8] * w2;
+        f = w0 * Aw0 + w1 * Aw1 + w2 * Aw2 + r[9] * w0 + r[10] * w1 + r[11] * w2 + r[12];
+        g[0] = T(2) * Aw0 + r[9];
+        g[1] = T(2) * Aw1 + r[10];
+        g[2] = T(2) * Aw2 + r[11];
+    } else {
+        f = r[0] * Xk[0] + r[1] * Xk[1] + r[2] * Xk[2] - r[3];
+        g[0] = r[0];
+        g[1] = r[1];
+        g[2] = r[2];
+    }
+    T lg2 = dot3(g, g);
+    const bool valid = lg2 > T(0);
+    lg2 = (lg2 > T(0)) ? lg2 : T(1);
+    const T ig = drsqrt(lg2);
+    const T nh[3] = {g[0] * ig, g[1] * ig, g[2] * ig};
+    const T s = dot3(ih, nh);
+    // a refracting facet (record entries 16, 17: the indices of the side
+    // the normal points to and of the other side): Snell's law, the part
+    // of n r^ along the facet equals that of n i^ (Sec. VI), with n_i the
+    // index of the side the ray arrives from
+    const bool refr = REFR && (t == TP) && (r[16] > T(0));
+    const T n_i = refr ? ((s < T(0)) ? r[16] : r[17]) : T(0);
+    const T n_t = refr ? ((s < T(0)) ? r[17] : r[16]) : T(0);
+    const T sr = dot3(rh, nh);
+    T ul[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+        ul[i] = refr ? n_t * (rh[i] - sr * nh[i]) - n_i * (ih[i] - s * nh[i]) : rh[i] - ih[i] + T(2) * s * nh[i];
+#pragma unroll
+    for (int i = 0; i < 3; i++) u[i] = S * ul[i];
+    u[3] = f;
+    if (WITH_J) {
+        // (Q Pa)_ij = Pa_ij - nh_i m_j with m = 2 (nh - s ih)/|a|
+        T m[3];
+#pragma unroll
+        for (int j = 0; j < 3; j++) m[j] = T(2) * (nh[j] - s * ih[j]) * ia;
+        // curvature of a quadric: Nm = (I - nh nh^T) B, B = 2A/|g|;
+        // TN = 2 (nh ih^T + s I) Nm = 2 nh q^T + 2 s (B - nh v^T),
+        // v = B nh, q = B ih - s v.  A plane has no curvature.
+        T TN[3][3];
         if (t == TQ) {
-            const T w0 = Xk[0] - r[0], w1 = Xk[1] - r[1], w2 = Xk[2] - r[2];
-            const T Aw0 = r[3] * w0 + r[4] * w1 + r[5] * w2;
-            const T Aw1 = r[4] * w0 + r[6] * w1 + r[7] * w2;
-            const T Aw2 = r[5] * w0 + r[7] * w1 + r[8] * w2;
-            f = w0 * Aw0 + w1 * Aw1 + w2 * Aw2 + r[9] * w0 + r[10] * w1 + r[11] * w2 + r[12];
-            g[0] = T(2) * Aw0 + r[9];
-            g[1] = T(2) * Aw1 + r[10];
-            g[2] = T(2) * Aw2 + r[11];
+            const T c2 = T(2) * ig;
+            const T b0 = c2 * r[3], b1 = c2 * r[4], b2 = c2 * r[5], b3 = c2 * r[6], b4 = c2 * r[7], b5 = c2 * r[8];
+            const T v[3] = {b0 * nh[0] + b1 * nh[1] + b2 * nh[2], b1 * nh[0] + b3 * nh[1] + b4 * nh[2],
+                            b2 * nh[0] + b4 * nh[1] + b5 * nh[2]};
+            const T q[3] = {b0 * ih[0] + b1 * ih[1] + b2 * ih[2] - s * v[0],
+                            b1 * ih[0] + b3 * ih[1] + b4 * ih[2] - s * v[1],
+                            b2 * ih[0] + b4 * ih[1] + b5 * ih[2] - s * v[2]};
+            const T Bm[3][3] = {{b0, b1, b2}, {b1, b3, b4}, {b2, b4, b5}};
+            const T s2 = T(2) * s;
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) TN[i][j] = T(2) * nh[i] * q[j] + s2 * (Bm[i][j] - nh[i] * v[j]);
         } else {
-            f = r[0] * Xk[0] + r[1] * Xk[1] + r[2] * Xk[2] - r[3];
-            g[0] = r[0];
-            g[1] = r[1];
-            g[2] = r[2];
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) TN[i][j] = T(0);
         }
-        T lg2 = dot3(g, g);
-        valid = valid && (lg2 > T(0));
-        lg2 = (lg2 > T(0)) ? lg2 : T(1);
-        const T ig = drsqrt(lg2);
-        const T nh[3] = {g[0] * ig, g[1] * ig, g[2] * ig};
-        const T s = dot3(ih, nh);
-        // a refracting facet (record entries 16, 17: the indices of the side
-        // the normal points to and of the other side): Snell's law, the part
-        // of n r^ along the facet equals that of n i^ (Sec. VI), with n_i the
-        // index of the side the ray arrives from
-        const bool refr = REFR && (t == TP) && (r[16] > T(0));
-        const T n_i = refr ? ((s < T(0)) ? r[16] : r[17]) : T(0);
-        const T n_t = refr ? ((s < T(0)) ? r[17] : r[16]) : T(0);
-        const T sr = dot3(rh, nh);
-        T ul[3];
+        if (refr) {
+            // u = n_t Pn r^ - n_i Pn i^, Pn = I - n n^T constant on a plane:
+            // dU/dX_{k-1} = n_i Pn Pa, dU/dX_{k+1} = n_t Pn Pb, dU/dX_k = -(both)
+            T ma[3], mb[3];
 #pragma unroll
-        for (int i = 0; i < 3; i++)
-            ul[i] = refr ? n_t * (rh[i] - sr * nh[i]) - n_i * (ih[i] - s * nh[i]) : rh[i] - ih[i] + T(2) * s * nh[i];
-#pragma unroll
-        for (int i = 0; i < 3; i++) u[i] = S * ul[i];
-        u[3] = f;
-        u[4] = T(0);
-        if (WITH_J) {
-            // (Q Pa)_ij = Pa_ij - nh_i m_j with m = 2 (nh - s ih)/|a|
-            T m[3];
-#pragma unroll
-            for (int j = 0; j < 3; j++) m[j] = T(2) * (nh[j] - s * ih[j]) * ia;
-            // curvature of a quadric: Nm = (I - nh nh^T) B, B = 2A/|g|;
-            // TN = 2 (nh ih^T + s I) Nm = 2 nh q^T + 2 s (B - nh v^T),
-            // v = B nh, q = B ih - s v.  A plane has no curvature.
-            T TN[3][3];
-            if (t == TQ) {
-                const T c2 = T(2) * ig;
-                const T b0 = c2 * r[3], b1 = c2 * r[4], b2 = c2 * r[5], b3 = c2 * r[6], b4 = c2 * r[7],
-                        b5 = c2 * r[8];
-                const T v[3] = {b0 * nh[0] + b1 * nh[1] + b2 * nh[2], b1 * nh[0] + b3 * nh[1] + b4 * nh[2],
-                                b2 * nh[0] + b4 * nh[1] + b5 * nh[2]};
-                const T q[3] = {b0 * ih[0] + b1 * ih[1] + b2 * ih[2] - s * v[0],
-                                b1 * ih[0] + b3 * ih[1] + b4 * ih[2] - s * v[1],
-                                b2 * ih[0] + b4 * ih[1] + b5 * ih[2] - s * v[2]};
-                const T Bm[3][3] = {{b0, b1, b2}, {b1, b3, b4}, {b2, b4, b5}};
-                const T s2 = T(2) * s;
-#pragma unroll
-                for (int i = 0; i < 3; i++)
-#pragma unroll
-                    for (int j = 0; j < 3; j++) TN[i][j] = T(2) * nh[i] * q[j] + s2 * (Bm[i][j] - nh[i] * v[j]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 3; i++)
-#pragma unroll
-                    for (int j = 0; j < 3; j++) TN[i][j] = T(0);
+            for (int j = 0; j < 3; j++) {
+                ma[j] = (nh[j] - s * ih[j]) * ia;
+                mb[j] = (nh[j] - sr * rh[j]) * ib;
             }
-            if (refr) {
-                // u = n_t Pn r^ - n_i Pn i^, Pn = I - n n^T constant on a plane:
-                // dU/dX_{k-1} = n_i Pn Pa, dU/dX_{k+1} = n_t Pn Pb, dU/dX_k = -(both)
-                T ma[3], mb[3];
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
 #pragma unroll
                 for (int j = 0; j < 3; j++) {
-                    ma[j] = (nh[j] - s * ih[j]) * ia;
-                    mb[j] = (nh[j] - sr * rh[j]) * ib;
-                }
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-#pragma unroll
-                    for (int j = 0; j < 3; j++) {
-                        const T pa = ((i == j) ? ia : T(0)) - ih[i] * ih[j] * ia;
-                        const T pb = ((i == j) ? ib : T(0)) - rh[i] * rh[j] * ib;
-                        const T up = n_i * (pa - nh[i] * ma[j]);
-                        const T un = n_t * (pb - nh[i] * mb[j]);
-                        Jp[i][j] = S * up - T(0.5) * ul[i] * ih[j];
-                        Jn[i][j] = S * un + T(0.5) * ul[i] * rh[j];
-                        Jk[i][j] = -S * (up + un) + T(0.5) * ul[i] * (ih[j] - rh[j]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-#pragma unroll
-                    for (int j = 0; j < 3; j++) {
-                        const T pa = ((i == j) ? ia : T(0)) - ih[i] * ih[j] * ia;
-                        const T pb = ((i == j) ? ib : T(0)) - rh[i] * rh[j] * ib;
-                        const T qpa = pa - nh[i] * m[j];
-                        // product rule with dS: dS/dX_{k-1} = -ih/2, dS/dX_k = (ih - rh)/2, dS/dX_{k+1} = rh/2
-                        Jp[i][j] = S * qpa - T(0.5) * ul[i] * ih[j];
-                        Jn[i][j] = S * pb + T(0.5) * ul[i] * rh[j];
-                        Jk[i][j] = S * (TN[i][j] - pb - qpa) + T(0.5) * ul[i] * (ih[j] - rh[j]);
-                    }
+                    const T pa = ((i == j) ? ia : T(0)) - ih[i] * ih[j] * ia;
+                    const T pb = ((i == j) ? ib : T(0)) - rh[i] * rh[j] * ib;
+                    const T up = n_i * (pa - nh[i] * ma[j]);
+                    const T un = n_t * (pb - nh[i] * mb[j]);
+                    Jp[i][j] = S * up - T(0.5) * ul[i] * ih[j];
+                    Jn[i][j] = S * un + T(0.5) * ul[i] * rh[j];
+                    Jk[i][j] = -S * (up + un) + T(0.5) * ul[i] * (ih[j] - rh[j]);
                 }
             }
-#pragma unroll
-            for (int j = 0; j < 3; j++) { Jk[3][j] = g[j]; Jk[4][j] = T(0); }
-        }
-    } else {
-        const T d[3] = {Xk[0] - r[0], Xk[1] - r[1], Xk[2] - r[2]};
-        const T dv[3] = {ih[0] - rh[0], ih[1] - rh[1], ih[2] - rh[2]};
-        T e[3], go0[3], go1[3], o0, o1, iw = T(0);
-        if (t == TL) {
-            // straight edge: fixed e, rows across the line
-#pragma unroll
-            for (int j = 0; j < 3; j++) {
-                e[j] = r[3 + j];
-                go0[j] = r[8 + j];
-                go1[j] = r[11 + j];
-            }
-            o0 = dot3(d, go0);
-            o1 = dot3(d, go1);
         } else {
-            // circle: e = n x d / |n x d|, rows <d,n> and (|d|^2 - R^2)/(2R)
-            const T w[3] = {r[4] * d[2] - r[5] * d[1], r[5] * d[0] - r[3] * d[2], r[3] * d[1] - r[4] * d[0]};
-            T lw2 = dot3(w, w);
-            valid = valid && (lw2 > T(0));
-            lw2 = (lw2 > T(0)) ? lw2 : T(1);
-            iw = drsqrt(lw2);
-            const T R = r[6], iR = drcp(R);
 #pragma unroll
-            for (int j = 0; j < 3; j++) {
-                e[j] = w[j] * iw;
-                go0[j] = r[3 + j];
-                go1[j] = d[j] * iR;
+            for (int i = 0; i < 3; i++) {
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    const T pa = ((i == j) ? ia : T(0)) - ih[i] * ih[j] * ia;
+                    const T pb = ((i == j) ? ib : T(0)) - rh[i] * rh[j] * ib;
+                    const T qpa = pa - nh[i] * m[j];
+                    // product rule with dS: dS/dX_{k-1} = -ih/2, dS/dX_k = (ih - rh)/2, dS/dX_{k+1} = rh/2
+                    Jp[i][j] = S * qpa - T(0.5) * ul[i] * ih[j];
+                    Jn[i][j] = S * pb + T(0.5) * ul[i] * rh[j];
+                    Jk[i][j] = S * (TN[i][j] - pb - qpa) + T(0.5) * ul[i] * (ih[j] - rh[j]);
+                }
             }
-            o0 = dot3(d, go0);
-            o1 = (dot3(d, d) - R * R) * (T(0.5) * iR);
         }
-        const T u0 = dot3(dv, e);
-        u[0] = S * u0;
-        u[1] = T(0);
-        u[2] = T(0);
-        u[3] = o0;
-        u[4] = o1;
-        if (WITH_J) {
-            // circle: dv^T de/dX = (dv x n - <dv,e> (e x n)) / |w|; straight edge: 0
-            T dvE[3] = {T(0), T(0), T(0)};
-            if (t == TC) {
-                const T n0 = r[3], n1 = r[4], n2 = r[5];
-                const T dxn[3] = {dv[1] * n2 - dv[2] * n1, dv[2] * n0 - dv[0] * n2, dv[0] * n1 - dv[1] * n0};
-                const T exn[3] = {e[1] * n2 - e[2] * n1, e[2] * n0 - e[0] * n2, e[0] * n1 - e[1] * n0};
 #pragma unroll
-                for (int j = 0; j < 3; j++) dvE[j] = (dxn[j] - u0 * exn[j]) * iw;
-            }
-            const T ei = dot3(e, ih), er = dot3(e, rh);
+        for (int j = 0; j < 3; j++) Jg[j] = g[j];
+    }
+    return valid;
+}
+
+// A straight or circular edge: u[0] law row, u[1], u[2] object rows; Jp, Jk,
+// Jn the law row's derivatives, Jo those of the object rows.  Returns false
+// when a circle's tangent is undefined.
+template <typename T, bool WITH_J>
+__host__ __device__ __forceinline__ bool edge_rows(int t, const T *__restrict__ r, const Dirs<T> &D, const T *Xk,
+                                                   T u[3], T Jp[3], T Jk[3], T Jn[3], T Jo[2][3])
+{
+    const T *ih = D.ih, *rh = D.rh;
+    const T ia = D.ia, ib = D.ib, S = D.S;
+    bool valid = true;
+    const T d[3] = {Xk[0] - r[0], Xk[1] - r[1], Xk[2] - r[2]};
+    const T dv[3] = {ih[0] - rh[0], ih[1] - rh[1], ih[2] - rh[2]};
+    T e[3], go0[3], go1[3], o0, o1, iw = T(0);
+    if (t == TL) {
+        // straight edge: fixed e, rows across the line
 #pragma unroll
-            for (int j = 0; j < 3; j++) {
-                const T ePa = (e[j] - ei * ih[j]) * ia;
-                const T ePb = (e[j] - er * rh[j]) * ib;
-                Jp[0][j] = -S * ePa - T(0.5) * u0 * ih[j];
-                Jn[0][j] = -S * ePb + T(0.5) * u0 * rh[j];
-                Jk[0][j] = S * (ePa + ePb + dvE[j]) + T(0.5) * u0 * (ih[j] - rh[j]);
+        for (int j = 0; j < 3; j++) {
+            e[j] = r[3 + j];
+            go0[j] = r[8 + j];
+            go1[j] = r[11 + j];
+        }
+        o0 = dot3(d, go0);
+        o1 = dot3(d, go1);
+    } else {
+        // circle: e = n x d / |n x d|, rows <d,n> and (|d|^2 - R^2)/(2R)
+        const T w[3] = {r[4] * d[2] - r[5] * d[1], r[5] * d[0] - r[3] * d[2], r[3] * d[1] - r[4] * d[0]};
+        T lw2 = dot3(w, w);
+        valid = lw2 > T(0);
+        lw2 = (lw2 > T(0)) ? lw2 : T(1);
+        iw = drsqrt(lw2);
+        const T R = r[6], iR = drcp(R);
 #pragma unroll
-                for (int i = 1; i < 3; i++) { Jp[i][j] = T(0); Jn[i][j] = T(0); Jk[i][j] = T(0); }
-                Jk[3][j] = go0[j];
-                Jk[4][j] = go1[j];
-            }
+        for (int j = 0; j < 3; j++) {
+            e[j] = w[j] * iw;
+            go0[j] = r[3 + j];
+            go1[j] = d[j] * iR;
+        }
+        o0 = dot3(d, go0);
+        o1 = (dot3(d, d) - R * R) * (T(0.5) * iR);
+    }
+    const T u0 = dot3(dv, e);
+    u[0] = S * u0;
+    u[1] = o0;
+    u[2] = o1;
+    if (WITH_J) {
+        // circle: dv^T de/dX = (dv x n - <dv,e> (e x n)) / |w|; straight edge: 0
+        T dvE[3] = {T(0), T(0), T(0)};
+        if (t == TC) {
+            const T n0 = r[3], n1 = r[4], n2 = r[5];
+            const T dxn[3] = {dv[1] * n2 - dv[2] * n1, dv[2] * n0 - dv[0] * n2, dv[0] * n1 - dv[1] * n0};
+            const T exn[3] = {e[1] * n2 - e[2] * n1, e[2] * n0 - e[0] * n2, e[0] * n1 - e[1] * n0};
+#pragma unroll
+            for (int j = 0; j < 3; j++) dvE[j] = (dxn[j] - u0 * exn[j]) * iw;
+        }
+        const T ei = dot3(e, ih), er = dot3(e, rh);
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const T ePa = (e[j] - ei * ih[j]) * ia;
+            const T ePb = (e[j] - er * rh[j]) * ib;
+            Jp[j] = -S * ePa - T(0.5) * u0 * ih[j];
+            Jn[j] = -S * ePb + T(0.5) * u0 * rh[j];
+            Jk[j] = S * (ePa + ePb + dvE[j]) + T(0.5) * u0 * (ih[j] - rh[j]);
+            Jo[0][j] = go0[j];
+            Jo[1][j] = go1[j];
         }
     }
     return valid;
 }
+
+__host__ __device__ __forceinline__ bool is_surface(int t) { return t == TP || t == TQ; }
 
 // ------------------------------------------------------------------ band
 // Packed lower band of J^T J for N interactions of B unknowns each (B = 3:
@@ -347,20 +371,77 @@ __host__ __device__ __forceinline__ bool eval_cost(const SceneT<T> &sc, const Pa
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < N; k++) {
-        T Xp[3], Xk[3], Xn[3], u[5];
+        T Xp[3], Xk[3], Xn[3];
         point_at<T, N>(k - 1, X, dx, sc.tx, p.rx, Xp);
         point_at<T, N>(k, X, dx, sc.tx, p.rx, Xk);
         point_at<T, N>(k + 1, X, dx, sc.tx, p.rx, Xn);
-        const bool okk = interaction_rows<T, false, REFR>(p.ty[k], sc.rec + (size_t)p.id[k] * kRec, Xp, Xk, Xn, u,
-                                                    nullptr, nullptr, nullptr);
-        ok = ok && okk;
+        const Dirs<T> D = directions(Xp, Xk, Xn);
+        const T *r = sc.rec + (size_t)p.id[k] * kRec;
+        ok = ok && D.valid;
+        if (is_surface(p.ty[k])) {
+            T u[4];
+            ok = surface_rows<T, false, REFR>(p.ty[k], r, D, Xk, u, nullptr, nullptr, nullptr, nullptr) && ok;
 #pragma unroll
-        for (int i = 0; i < 5; i++) {
-            C += u[i] * u[i];
-            rinf = fmax(rinf, fabs(u[i]));
+            for (int i = 0; i < 4; i++) {
+                C += u[i] * u[i];
+                rinf = fmax(rinf, fabs(u[i]));
+            }
+        } else {
+            T u[3];
+            ok = edge_rows<T, false>(p.ty[k], r, D, Xk, u, nullptr, nullptr, nullptr, nullptr) && ok;
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
+                C += u[i] * u[i];
+                rinf = fmax(rinf, fabs(u[i]));
+            }
         }
     }
     return ok;
+}
+
+// A += J^T J and g += J^T u for the R law rows of interaction k (J = [Jp Jk
+// Jn] over blocks k-1, k, k+1) and the Q object rows (block k only).
+template <typename T, int N, int R, int Q>
+__host__ __device__ __forceinline__ void add_rows(int k, const T (*Jp)[3], const T (*Jk)[3], const T (*Jn)[3],
+                                                  const T (*Jo)[3], const T *u, T *A, T *g)
+{
+#pragma unroll
+    for (int row = 0; row < R; row++) {
+        T jr[9];
+#pragma unroll
+        for (int c = 0; c < 3; c++) { jr[c] = Jp[row][c]; jr[3 + c] = Jk[row][c]; jr[6 + c] = Jn[row][c]; }
+#pragma unroll
+        for (int bi = 0; bi < 3; bi++) {
+            const int Bi = k - 1 + bi;
+            if (Bi < 0 || Bi >= N) continue;
+#pragma unroll
+            for (int ci = 0; ci < 3; ci++) {
+                const int gi = 3 * Bi + ci;
+                g[gi] += jr[3 * bi + ci] * u[row];
+#pragma unroll
+                for (int bj = 0; bj < 3; bj++) {
+                    const int Bj = k - 1 + bj;
+                    if (Bj < 0 || Bj >= N) continue;
+#pragma unroll
+                    for (int cj = 0; cj < 3; cj++) {
+                        const int gj = 3 * Bj + cj;
+                        if (gj > gi) continue;
+                        A[Band<N>::at(gi, gj)] += jr[3 * bi + ci] * jr[3 * bj + cj];
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int row = 0; row < Q; row++) {
+#pragma unroll
+        for (int ci = 0; ci < 3; ci++) {
+            const int gi = 3 * k + ci;
+            g[gi] += Jo[row][ci] * u[R + row];
+#pragma unroll
+            for (int cj = 0; cj <= ci; cj++) A[Band<N>::at(gi, 3 * k + cj)] += Jo[row][ci] * Jo[row][cj];
+        }
+    }
 }
 
 // Residual, J^T J (in-band, packed lower) and g = J^T R at X.
@@ -381,55 +462,31 @@ __host__ __device__ __forceinline__ bool assemble(const SceneT<T> &sc, const Pat
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < N; k++) {
-        T Xp[3], Xk[3], Xn[3], u[5], Jp[3][3], Jk[5][3], Jn[3][3];
+        T Xp[3], Xk[3], Xn[3];
         point_at<T, N>(k - 1, X, nullptr, sc.tx, p.rx, Xp);
         point_at<T, N>(k, X, nullptr, sc.tx, p.rx, Xk);
         point_at<T, N>(k + 1, X, nullptr, sc.tx, p.rx, Xn);
-        const bool okk = interaction_rows<T, true, REFR>(p.ty[k], sc.rec + (size_t)p.id[k] * kRec, Xp, Xk, Xn, u, Jp, Jk, Jn);
-        ok = ok && okk;
+        const Dirs<T> D = directions(Xp, Xk, Xn);
+        const T *r = sc.rec + (size_t)p.id[k] * kRec;
+        ok = ok && D.valid;
+        if (is_surface(p.ty[k])) {
+            T u[4], Jp[3][3], Jk[3][3], Jn[3][3], Jg[1][3];
+            ok = surface_rows<T, true, REFR>(p.ty[k], r, D, Xk, u, Jp, Jk, Jn, Jg[0]) && ok;
 #pragma unroll
-        for (int i = 0; i < 5; i++) {
-            C += u[i] * u[i];
-            rinf = fmax(rinf, fabs(u[i]));
-        }
-        // law rows couple blocks k-1, k, k+1
-#pragma unroll
-        for (int row = 0; row < 3; row++) {
-            T jr[9];
-#pragma unroll
-            for (int c = 0; c < 3; c++) { jr[c] = Jp[row][c]; jr[3 + c] = Jk[row][c]; jr[6 + c] = Jn[row][c]; }
-#pragma unroll
-            for (int bi = 0; bi < 3; bi++) {
-                const int Bi = k - 1 + bi;
-                if (Bi < 0 || Bi >= N) continue;
-#pragma unroll
-                for (int ci = 0; ci < 3; ci++) {
-                    const int gi = 3 * Bi + ci;
-                    g[gi] += jr[3 * bi + ci] * u[row];
-#pragma unroll
-                    for (int bj = 0; bj < 3; bj++) {
-                        const int Bj = k - 1 + bj;
-                        if (Bj < 0 || Bj >= N) continue;
-#pragma unroll
-                        for (int cj = 0; cj < 3; cj++) {
-                            const int gj = 3 * Bj + cj;
-                            if (gj > gi) continue;
-                            A[Band<N>::at(gi, gj)] += jr[3 * bi + ci] * jr[3 * bj + cj];
-                        }
-                    }
-                }
+            for (int i = 0; i < 4; i++) {
+                C += u[i] * u[i];
+                rinf = fmax(rinf, fabs(u[i]));
             }
-        }
-        // object rows touch block k only
+            add_rows<T, N, 3, 1>(k, Jp, Jk, Jn, Jg, u, A, g);
+        } else {
+            T u[3], Jp[1][3], Jk[1][3], Jn[1][3], Jo[2][3];
+            ok = edge_rows<T, true>(p.ty[k], r, D, Xk, u, Jp[0], Jk[0], Jn[0], Jo) && ok;
 #pragma unroll
-        for (int row = 3; row < 5; row++) {
-#pragma unroll
-            for (int ci = 0; ci < 3; ci++) {
-                const int gi = 3 * k + ci;
-                g[gi] += Jk[row][ci] * u[row];
-#pragma unroll
-                for (int cj = 0; cj <= ci; cj++) A[Band<N>::at(gi, 3 * k + cj)] += Jk[row][ci] * Jk[row][cj];
+            for (int i = 0; i < 3; i++) {
+                C += u[i] * u[i];
+                rinf = fmax(rinf, fabs(u[i]));
             }
+            add_rows<T, N, 1, 2>(k, Jp, Jk, Jn, Jo, u, A, g);
         }
     }
     return ok;
@@ -589,19 +646,81 @@ __host__ __device__ __forceinline__ bool eval_cost_param(const SceneT<T> &sc, co
 #pragma unroll
     for (int k = 0; k < N; k++) {
         if (k + 1 < N) map(k + 1);
-        T u[5];
         const T *Xp = (k == 0) ? sc.tx : Xw[(k + 2) % 3];
         const T *Xn = (k + 1 < N) ? Xw[(k + 1) % 3] : p.rx;
-        const bool okk = interaction_rows<T, false, REFR>(p.ty[k], sc.rec + (size_t)p.id[k] * kRec, Xp, Xw[k % 3], Xn,
-                                                          u, nullptr, nullptr, nullptr);
-        ok = ok && okk;
+        const Dirs<T> D = directions(Xp, Xw[k % 3], Xn);
+        const T *r = sc.rec + (size_t)p.id[k] * kRec;
+        ok = ok && D.valid;
+        if (is_surface(p.ty[k])) {
+            T u[4];
+            ok = surface_rows<T, false, REFR>(p.ty[k], r, D, Xw[k % 3], u, nullptr, nullptr, nullptr, nullptr) && ok;
 #pragma unroll
-        for (int i = 0; i < 3; i++) {
-            C += u[i] * u[i];
-            rinf = fmax(rinf, fabs(u[i]));
+            for (int i = 0; i < 3; i++) {
+                C += u[i] * u[i];
+                rinf = fmax(rinf, fabs(u[i]));
+            }
+        } else {
+            T u[3];
+            ok = edge_rows<T, false>(p.ty[k], r, D, Xw[k % 3], u, nullptr, nullptr, nullptr, nullptr) && ok;
+            C += u[0] * u[0];
+            rinf = fmax(rinf, fabs(u[0]));
         }
     }
     return ok;
+}
+
+// The R law rows of interaction k of the parametric form: their derivatives
+// with respect to the parameters of interactions k-1, k, k+1 by the chain
+// rule (Tp, Tk, Tn: dX/dU of the three), added to the band and the gradient.
+// K: parameters of interaction k itself (1 for an edge, whose second slot is
+// a placeholder with a zero column).
+template <typename T, int N, int R, int K>
+__host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3], const T (*Jk)[3], const T (*Jn)[3],
+                                                        const T (*Tp)[2], const T (*Tk)[2], const T (*Tn)[2],
+                                                        const T *u, T *A, T *g, T &C, T &rinf)
+{
+#pragma unroll
+    for (int row = 0; row < R; row++) {
+        C += u[row] * u[row];
+        rinf = fmax(rinf, fabs(u[row]));
+        T jr[6];
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            T vp = T(0), vk = T(0), vn = T(0);
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                if (k > 0) vp += Jp[row][j] * Tp[j][c];
+                if (c < K) vk += Jk[row][j] * Tk[j][c];
+                if (k + 1 < N) vn += Jn[row][j] * Tn[j][c];
+            }
+            jr[c] = vp;
+            jr[2 + c] = vk;
+            jr[4 + c] = vn;
+        }
+#pragma unroll
+        for (int bi = 0; bi < 3; bi++) {
+            const int Bi = k - 1 + bi;
+            if (Bi < 0 || Bi >= N) continue;
+#pragma unroll
+            for (int ci = 0; ci < 2; ci++) {
+                if (bi == 1 && ci >= K) continue;
+                const int gi = 2 * Bi + ci;
+                g[gi] += jr[2 * bi + ci] * u[row];
+#pragma unroll
+                for (int bj = 0; bj < 3; bj++) {
+                    const int Bj = k - 1 + bj;
+                    if (Bj < 0 || Bj >= N) continue;
+#pragma unroll
+                    for (int cj = 0; cj < 2; cj++) {
+                        if (bj == 1 && cj >= K) continue;
+                        const int gj = 2 * Bj + cj;
+                        if (gj > gi) continue;
+                        A[Band<N, 2>::at(gi, gj)] += jr[2 * bi + ci] * jr[2 * bj + cj];
+                    }
+                }
+            }
+        }
+    }
 }
 
 // Normal equations of the parametric form: band of J^T J (2 x 2 blocks) and
@@ -633,53 +752,19 @@ __host__ __device__ __forceinline__ bool assemble_param(const SceneT<T> &sc, con
 #pragma unroll
     for (int k = 0; k < N; k++) {
         if (k + 1 < N) map(k + 1);
-        T u[5], Jp[3][3], Jk[5][3], Jn[3][3];
         const T *Xp = (k == 0) ? sc.tx : Xw[(k + 2) % 3];
         const T *Xn = (k + 1 < N) ? Xw[(k + 1) % 3] : p.rx;
-        const bool okk = interaction_rows<T, true, REFR>(p.ty[k], sc.rec + (size_t)p.id[k] * kRec, Xp, Xw[k % 3], Xn,
-                                                         u, Jp, Jk, Jn);
-        ok = ok && okk;
-#pragma unroll
-        for (int row = 0; row < 3; row++) {
-            C += u[row] * u[row];
-            rinf = fmax(rinf, fabs(u[row]));
-            // the row's derivatives with respect to the parameters of
-            // interactions k-1, k, k+1
-            T jr[6];
-#pragma unroll
-            for (int c = 0; c < 2; c++) {
-                T vp = T(0), vk = T(0), vn = T(0);
-#pragma unroll
-                for (int j = 0; j < 3; j++) {
-                    if (k > 0) vp += Jp[row][j] * Tw[(k + 2) % 3][j][c];
-                    vk += Jk[row][j] * Tw[k % 3][j][c];
-                    if (k + 1 < N) vn += Jn[row][j] * Tw[(k + 1) % 3][j][c];
-                }
-                jr[c] = vp;
-                jr[2 + c] = vk;
-                jr[4 + c] = vn;
-            }
-#pragma unroll
-            for (int bi = 0; bi < 3; bi++) {
-                const int Bi = k - 1 + bi;
-                if (Bi < 0 || Bi >= N) continue;
-#pragma unroll
-                for (int ci = 0; ci < 2; ci++) {
-                    const int gi = 2 * Bi + ci;
-                    g[gi] += jr[2 * bi + ci] * u[row];
-#pragma unroll
-                    for (int bj = 0; bj < 3; bj++) {
-                        const int Bj = k - 1 + bj;
-                        if (Bj < 0 || Bj >= N) continue;
-#pragma unroll
-                        for (int cj = 0; cj < 2; cj++) {
-                            const int gj = 2 * Bj + cj;
-                            if (gj > gi) continue;
-                            A[Band<N, 2>::at(gi, gj)] += jr[2 * bi + ci] * jr[2 * bj + cj];
-                        }
-                    }
-                }
-            }
+        const Dirs<T> D = directions(Xp, Xw[k % 3], Xn);
+        const T *r = sc.rec + (size_t)p.id[k] * kRec;
+        ok = ok && D.valid;
+        if (is_surface(p.ty[k])) {
+            T u[4], Jp[3][3], Jk[3][3], Jn[3][3], Jg[3];
+            ok = surface_rows<T, true, REFR>(p.ty[k], r, D, Xw[k % 3], u, Jp, Jk, Jn, Jg) && ok;
+            add_param_rows<T, N, 3, 2>(k, Jp, Jk, Jn, Tw[(k + 2) % 3], Tw[k % 3], Tw[(k + 1) % 3], u, A, g, C, rinf);
+        } else {
+            T u[3], Jp[1][3], Jk[1][3], Jn[1][3], Jo[2][3];
+            ok = edge_rows<T, true>(p.ty[k], r, D, Xw[k % 3], u, Jp[0], Jk[0], Jn[0], Jo) && ok;
+            add_param_rows<T, N, 1, 1>(k, Jp, Jk, Jn, Tw[(k + 2) % 3], Tw[k % 3], Tw[(k + 1) % 3], u, A, g, C, rinf);
         }
     }
     return ok;

@@ -65,9 +65,8 @@ struct KParams {
     OptsDev o;
     const double *x0_learned;  // [n][kRow] network start points (world)
     const int *bin_cnt;        // [5] solves per order
-    const int *perm;           // [n] solve ids grouped by order (bin order)
-    const int *slot_rx;        // [n] receiver of each bin slot
-    const int *slot_prim;      // [5][n] primitive ids of each bin slot
+    const int *perm;           // [n] with state rows: the bin slot of each solve (-1: invalid); else the solve of each slot
+    float *rows;               // [n][32] state rows of the FP32 pass in bin order, or null
     int *head;                 // [10] work counters: bins, fallback lists
     int *pol_cnt;              // [5]
     int *pol_list;             // [n] polish lists (bin-relative slots)
@@ -78,8 +77,8 @@ struct KParams {
     int resume;                // 1: this launch finishes the parked paths
     int *spill_cnt;            // [5] parked paths per order
     int *spill_head;           // [5] work counters of the straggler pass
-    int *spill_list;           // [n] parked paths (bin-relative slots)
-    double *spill_f;           // [2][n] damping and plateau reference of a parked path
+    int *spill_list;           // [n] bin slots of the parked paths (bin-relative places)
+    double *spill_f;           // [3][n] damping, plateau reference and stall count of a parked FP64 path
 };
 
 void launch_pack(const double *raw, const double *refr, const SceneDev &s, int n_pl, int n_ln, int n_q, int n_c,
@@ -89,8 +88,10 @@ int bin_key_count();
 // rows (or null): the list of the solves with a paraboloid or a circle,
 // grouped by order; curved: [5] per-order cursors, and curved[25] receives
 // the list's length
+// by_solve: perm receives each solve's bin slot (-1: invalid), else each
+// slot's solve
 void launch_bin(const BatchDev &b, const OutDev &out, const SceneDev &s, int *bin_cnt, int *keys, int *perm,
-                int *slot_rx, int *slot_prim, int *rows, int *curved, hipStream_t st);
+                bool by_solve, int *rows, int *curved, hipStream_t st);
 const void *lm_kernel(int mode, int order, bool lds, int form, bool refr);
 void launch_lm(int mode, int order, bool lds, int form, bool refr, size_t lds_bytes, const KParams &kp, int grid,
                int block, hipStream_t st);
@@ -98,7 +99,9 @@ const void *polish_kernel(bool refr);
 void launch_learned_choose(const SceneDev &s, const BatchDev &b, const int *rows, const int *count, bool all,
                            double *x0l, double gain, bool refr, hipStream_t st);
 void launch_polish(const KParams &kp, bool refr, int grid, int block, hipStream_t st);
-void launch_polish_list(const KParams &kp, hipStream_t st);
+void launch_start(int mode, int form, const KParams &kp, hipStream_t st);
+void launch_learned_begin(int mode, int form, const KParams &kp, const int *list, const int *count, hipStream_t st);
+void launch_finish(int form, bool refr, const KParams &kp, int cu, hipStream_t st);
 void launch_samples(const SceneDev &s, int k, double *samp, int *cnt, hipStream_t st);
 void launch_visibility(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt, uint32_t *V,
                        uint32_t *B, int W, size_t lds_max, int cu, hipStream_t st);

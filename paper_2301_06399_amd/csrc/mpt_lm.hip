@@ -1,0 +1,783 @@
+// The Levenberg-Marquardt kernels of the batched solve (gfx950, wave64):
+//  k_lm              persistent solver over every order's bin, one lane per
+//                    path, lanes refilled from a per-wave chunk of the bin once
+//                    enough of them are idle (FP64 plain, FP32 stage or FP64
+//                    fallback)
+//
+// What bounds them: VALU issue (an order-5 FP32 iteration is about 2400 vector
+// instructions, four cycles each) and, at one or two waves per SIMD, the
+// latency of the chain.  So the loop holds nothing but iterations: starts and
+// ends of paths are kernels of their own (k_start, k_finish), a lane reads and
+// writes one 128-byte state row, and finished lanes are saved together.  With
+// them in the loop an order-5 kernel was 78 KB of code at 256 registers, now
+// 33 KB at 185, and the stress workload's pass took 18.0 ms (with start and end
+// of the paths) against 10.7 ms (and 2.5 + 1.7 ms in k_start and k_finish); the
+// street canyon's (262,144 paths of orders 1-3) 466 us against 330.
+//  k_lm_low          the same over orders 1-3
+//  k_lm_one          one order's bin
+// The file is compiled once per (mode, form, scene in LDS or not), MPT_LM_MODE
+// / MPT_LM_FORM / MPT_LM_LDS, so that the instantiations build in parallel
+// (one translation unit took eight minutes).
+#include "mpt_path.hpp"
+
+namespace mpt {
+
+
+// ------------------------------------------------------------------ LM lane state
+template <typename T>
+struct LMOpts {
+    int max_iter, max_iter_planar, win, stat_win;
+    T frac, tol_step, tol_res, tau_root, lambda0, stat_tol;
+};
+
+// State of one lane's path: the unknowns (D = 3N points, or 2N parameters
+// in the parametric form) and the Levenberg-Marquardt scalars.
+template <typename T, int N, int D = 3 * N>
+struct Lane {
+    T X[D];
+    T lam, Cref, C, rinf;
+    int it, stat;
+    // The normal equations, gradient and cost of the current point, kept
+    // after a rejected step: the point has not moved, so the next iteration
+    // would rebuild the same values (only the damping changes).  FP32 and
+    // orders 1-3, whose copies fit in registers beside the order-5 code (the
+    // FP64 kernels already spill).
+    static constexpr bool kKeep = N <= 3 && sizeof(T) == 4;
+    static constexpr int kS = kKeep ? D * (D + 1) / 2 : 1;
+    static constexpr int kM = kKeep ? D : 1;
+    T A0[kS], g0[kM], C0, r0;
+    bool keep;
+};
+
+// One Levenberg-Marquardt iteration on the cost of Eq. (12) with the
+// rescaled rows; returns ST_RUNNING or the final status.  REFR: the scene
+// has refracting facets (their rows are compiled in).
+template <typename T, int N, bool REFR>
+__device__ __forceinline__ int lm_step(const SceneT<T> &sc, const PathIn<T, N> &p, Lane<T, N> &L,
+                                       const LMOpts<T> &o)
+{
+    constexpr int M = 3 * N;
+    using LT = Lane<T, N>;
+    L.it++;
+    T A[Band<N>::SIZE], g[M], C, rinf;
+    if (LT::kKeep && L.keep) {
+#pragma unroll
+        for (int i = 0; i < Band<N>::SIZE; i++) A[i] = L.A0[i % LT::kS];
+#pragma unroll
+        for (int i = 0; i < M; i++) g[i] = L.g0[i % LT::kM];
+        C = L.C0;
+        rinf = L.r0;
+    } else {
+        if (!assemble<T, N, REFR>(sc, p, L.X, A, g, C, rinf)) return ST_DEGEN;
+        if constexpr (LT::kKeep) {
+#pragma unroll
+            for (int i = 0; i < Band<N>::SIZE; i++) L.A0[i] = A[i];
+#pragma unroll
+            for (int i = 0; i < M; i++) L.g0[i] = g[i];
+            L.C0 = C;
+            L.r0 = rinf;
+        }
+    }
+    L.keep = false;
+    L.C = C;
+    L.rinf = rinf;
+    T dmax = T(0);
+#pragma unroll
+    for (int i = 0; i < M; i++) dmax = fmax(dmax, A[Band<N>::at(i, i)]);
+    if (L.it == 1) {
+        L.lam = o.lambda0 * dmax;
+        L.Cref = C;
+    }
+    if (rinf <= o.tol_res) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+    if (o.win > 0 && L.it > 1 && (L.it - 1) % o.win == 0) {
+        if (C > o.frac * L.Cref) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+        L.Cref = C;
+    }
+    const T floor_d = T(1e-12) * dmax;
+#pragma unroll
+    for (int i = 0; i < M; i++) A[Band<N>::at(i, i)] += L.lam * fmax(A[Band<N>::at(i, i)], floor_d);
+    if (!chol_band<T, N>(A)) {
+        L.lam *= T(10);
+        if (L.lam > T(1e12) * dmax) return ST_STALL;
+        L.keep = LT::kKeep;
+        return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
+    }
+#pragma unroll
+    for (int i = 0; i < M; i++) g[i] = -g[i];
+    const T pred = chol_solve_band<T, N>(A, g);  // g <- dx; pred = -g^T dx
+    if (o.stat_win > 0 && p.planar) {
+        // planes and straight edges: the descent has stalled when the damped
+        // model predicts too small a decrease several iterations in a row
+        L.stat = (pred < o.stat_tol * C) ? L.stat + 1 : 0;
+        if (L.stat >= o.stat_win) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+    }
+    T xinf = T(0), dinf = T(0);
+    bool guard = true;
+#pragma unroll
+    for (int k = 0; k < N; k++)
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            xinf = fmax(xinf, fabs(L.X[3 * k + i]));
+            dinf = fmax(dinf, fabs(g[3 * k + i]));
+            const T xt = L.X[3 * k + i] + g[3 * k + i];
+            guard = guard && (xt >= sc.glo[i]) && (xt <= sc.ghi[i]);
+        }
+    const bool small = dinf <= o.tol_step * (T(1) + xinf);
+    T Ct = T(0), rt = T(0);
+    bool okt = guard && eval_cost<T, N, REFR>(sc, p, L.X, g, Ct, rt);
+    if (okt && Ct < C) {
+#pragma unroll
+        for (int i = 0; i < M; i++) L.X[i] += g[i];
+        L.C = Ct;
+        L.rinf = rt;
+        L.lam = fmax(L.lam / T(10), T(1e-15) * dmax);
+        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+    } else {
+        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+        L.lam *= T(10);
+        if (L.lam > T(1e12) * dmax) return ST_STALL;
+        L.keep = LT::kKeep;
+    }
+    return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
+}
+
+// One Levenberg-Marquardt iteration of the parametric form (Eq. (15)), with
+// the same rules; the placeholder parameter of an edge is held fixed.
+template <typename T, int N, bool REFR>
+__device__ __forceinline__ int lm_step_param(const SceneT<T> &sc, const PathIn<T, N> &p, Lane<T, N, 2 * N> &L,
+                                             const LMOpts<T> &o)
+{
+    constexpr int M = 2 * N;
+    using LT = Lane<T, N, 2 * N>;
+    L.it++;
+    T A[Band<N, 2>::SIZE], g[M], C, rinf;
+    if (LT::kKeep && L.keep) {
+#pragma unroll
+        for (int i = 0; i < Band<N, 2>::SIZE; i++) A[i] = L.A0[i % LT::kS];
+#pragma unroll
+        for (int i = 0; i < M; i++) g[i] = L.g0[i % LT::kM];
+        C = L.C0;
+        rinf = L.r0;
+    } else {
+        if (!assemble_param<T, N, REFR>(sc, p, L.X, A, g, C, rinf)) return ST_DEGEN;
+        if constexpr (LT::kKeep) {
+#pragma unroll
+            for (int i = 0; i < Band<N, 2>::SIZE; i++) L.A0[i] = A[i];
+#pragma unroll
+            for (int i = 0; i < M; i++) L.g0[i] = g[i];
+            L.C0 = C;
+            L.r0 = rinf;
+        }
+    }
+    L.keep = false;
+    L.C = C;
+    L.rinf = rinf;
+    bool real[M];
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        real[2 * k] = true;
+        real[2 * k + 1] = p.ty[k] == TP || p.ty[k] == TQ;
+    }
+    T dmax = T(0);
+#pragma unroll
+    for (int i = 0; i < M; i++) dmax = real[i] ? fmax(dmax, A[Band<N, 2>::at(i, i)]) : dmax;
+    if (L.it == 1) {
+        L.lam = o.lambda0 * dmax;
+        L.Cref = C;
+    }
+    if (rinf <= o.tol_res) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+    if (o.win > 0 && L.it > 1 && (L.it - 1) % o.win == 0) {
+        if (C > o.frac * L.Cref) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+        L.Cref = C;
+    }
+    const T floor_d = T(1e-12) * dmax;
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        const T a = A[Band<N, 2>::at(i, i)];
+        A[Band<N, 2>::at(i, i)] = real[i] ? a + L.lam * fmax(a, floor_d) : T(1);
+    }
+    if (!chol_band<T, N, 2>(A)) {
+        L.lam *= T(10);
+        if (L.lam > T(1e12) * dmax) return ST_STALL;
+        L.keep = LT::kKeep;
+        return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
+    }
+#pragma unroll
+    for (int i = 0; i < M; i++) g[i] = -g[i];
+    const T pred = chol_solve_band<T, N, 2>(A, g);  // g <- dU (zero on the placeholders)
+    if (o.stat_win > 0 && p.planar) {
+        L.stat = (pred < o.stat_tol * C) ? L.stat + 1 : 0;
+        if (L.stat >= o.stat_win) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+    }
+    T xinf = T(0), dinf = T(0);
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        xinf = fmax(xinf, fabs(L.X[i]));
+        dinf = fmax(dinf, fabs(g[i]));
+    }
+    const bool small = dinf <= o.tol_step * (T(1) + xinf);
+    T Ct = T(0), rt = T(0);
+    bool guard = true;
+    bool okt = eval_cost_param<T, N, REFR>(sc, p, L.X, g, Ct, rt, guard) && guard;
+    if (okt && Ct < C) {
+#pragma unroll
+        for (int i = 0; i < M; i++) L.X[i] += g[i];
+        L.C = Ct;
+        L.rinf = rt;
+        L.lam = fmax(L.lam / T(10), T(1e-15) * dmax);
+        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+    } else {
+        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+        L.lam *= T(10);
+        if (L.lam > T(1e12) * dmax) return ST_STALL;
+        L.keep = LT::kKeep;
+    }
+    return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
+}
+
+// ------------------------------------------------------------------ persistent LM kernel
+// Lane-refill loop for the bin of order N.  Each wave takes a chunk of the bin
+// with one atomic, and hands the chunk's paths to its idle lanes once enough
+// lanes are idle, so lanes never wait for the slowest path of their wave.
+//
+// One iteration with the path's primitive types fixed at compile time (digit
+// k of CODE, base 4: 0 plane, 1 straight edge), so that no per-type branch
+// or select is left in the code.  Bins are type-homogeneous, so most waves
+// hold one planar sequence and run one of these variants only.  Used by the
+// parametric FP32 kernel: there it shortens an iteration (street canyon LM
+// stage 0.550 -> 0.484 ms, room 0.157 -> 0.119 ms); the implicit kernel's
+// larger variants made it slower (0.516 -> 0.556 ms).
+template <typename T, int N, int FORM, int CODE>
+__device__ __forceinline__ int lm_step_fixed(const SceneT<T> &sc, const PathIn<T, N> &p,
+                                             Lane<T, N, FORM ? 2 * N : 3 * N> &L, const LMOpts<T> &o)
+{
+    PathIn<T, N> q = p;
+#pragma unroll
+    for (int k = 0; k < N; k++) q.ty[k] = (CODE >> (2 * k)) & 3;
+    q.planar = true;  // planes and straight edges: no refracting facet
+    if constexpr (FORM) return lm_step_param<T, N, false>(sc, q, L, o);
+    else return lm_step<T, N, false>(sc, q, L, o);
+}
+
+// The fixed-type step for the planar sequence `code` of orders 1-3.
+template <typename T, int N, int FORM>
+__device__ __forceinline__ int lm_step_uniform(int code, const SceneT<T> &sc, const PathIn<T, N> &p,
+                                               Lane<T, N, FORM ? 2 * N : 3 * N> &L, const LMOpts<T> &o)
+{
+#define MPT_FIXED(c) \
+    case c: return lm_step_fixed<T, N, FORM, c>(sc, p, L, o);
+    if constexpr (N == 1) {
+        switch (code) { MPT_FIXED(0) MPT_FIXED(1) }
+    } else if constexpr (N == 2) {
+        switch (code) { MPT_FIXED(0) MPT_FIXED(1) MPT_FIXED(4) MPT_FIXED(5) }
+    } else if constexpr (N == 3) {
+        switch (code) {
+            MPT_FIXED(0) MPT_FIXED(1) MPT_FIXED(4) MPT_FIXED(5) MPT_FIXED(16) MPT_FIXED(17) MPT_FIXED(20) MPT_FIXED(21)
+        }
+    }
+#undef MPT_FIXED
+    return -1;
+}
+
+// How `size` waves share a bin of `count` paths.  Consecutive slots of a bin
+// hold one type sequence, and a wave pays for every type sequence among its
+// busy lanes, so a wave takes consecutive slots.  While an equal share is at
+// most kStaticChunk paths, that share is all a wave gets (few lanes per wave
+// on a small batch: idle lanes cost nothing, a second sequence in the wave
+// does); of a longer queue it first takes a quarter of an equal share and then
+// draws chunks of a quarter of what is left per wave from the bin's counter.
+// No wave's first chunk comes from the counter: 2048 waves drawing at once
+// waited 15-30 us for it (one counter is served one atomic at a time).
+constexpr int kStaticChunk = 128, kMinChunk = 64, kMaxChunk = 4096;
+
+__device__ __forceinline__ int launch_waves() { return (int)(gridDim.x * (blockDim.x >> 6)); }
+
+struct BinShare {
+    int rank, size;  // this wave among the waves that start with the bin; rank -1: none of them
+};
+
+__device__ __forceinline__ int first_chunk(int count, int size)
+{
+    return min(max(count / size / 4, kMinChunk), kMaxChunk);
+}
+
+// Stragglers.  Iteration counts are bimodal (a root converges in a handful of
+// iterations, a path without one creeps until the plateau test ends it), so
+// once the bin's queue is empty a wave would idle most of its lanes while its
+// slowest paths finish.  Instead, when no more than spill_t lanes are still
+// busy, the wave parks their state (points, iteration count, damping,
+// plateau reference) and leaves; a second launch of the same kernel
+// (kp.resume) packs the parked paths densely and finishes them.  The same
+// machine code runs every iteration of a path, from the exact state it was
+// parked in, so the results are identical bit for bit.
+
+template <int MODE, int N, int FORM = 0, bool TYPED = false, bool REFR = false>
+__device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<MODE>::T *__restrict__ srec,
+                                       const BinShare share)
+{
+    using T = typename ModeT<MODE>::T;
+    constexpr int D = FORM ? 2 * N : 3 * N;  // unknowns: points, or parameters
+    constexpr bool FB = MODE == MODE_FALLBACK64;
+    const int lane = __lane_id();
+    const bool resume = !FB && kp.resume != 0;
+    const int *cnt = resume ? kp.spill_cnt : FB ? kp.fb_cnt : kp.bin_cnt;
+    int *head = resume ? kp.spill_head + (N - 1) : kp.head + (FB ? 5 : 0) + (N - 1);
+    const int count = cnt[N - 1];
+    if (count == 0) return;
+    const int off = bin_offset(kp.bin_cnt, N);
+    // every path is in some wave's share, or the rest is drawn from `head`
+    const bool fixed = share.size > 0 && count <= (int64_t)share.size * kStaticChunk;
+    if (fixed && share.rank < 0) return;
+    const int c0 = share.size > 0 ? first_chunk(count, share.size) : 0, drawn0 = c0 * share.size;
+    const bool may_spill = !resume && !FB && kp.spill_t > 0;
+
+    SceneT<T> sc;
+    sc.rec = srec;
+    double sh[3];  // origin of the solver's frame
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        sh[i] = (MODE == MODE_FP32) ? kp.s.tx[i] : 0.0;
+        sc.tx[i] = (MODE == MODE_FP32) ? T(0) : (T)kp.s.tx[i];
+        sc.glo[i] = (T)(kp.s.glo[i] - sh[i]);
+        sc.ghi[i] = (T)(kp.s.ghi[i] - sh[i]);
+    }
+    LMOpts<T> o;
+    if (MODE == MODE_FP32) {
+        o.max_iter = kp.o.max_iter32;
+        o.max_iter_planar = kp.o.max_iter32_planar;
+        o.tol_step = (T)kp.o.tol_step32;
+        o.tol_res = (T)kp.o.tol_res32;
+        o.tau_root = (T)kp.o.tau_root32;  // an FP32 point this close is taken for a root
+    } else {
+        o.max_iter = FB ? kp.o.max_iter_fb : kp.o.max_iter;
+        o.max_iter_planar = o.max_iter;
+        o.tol_step = (T)kp.o.tol_step;
+        o.tol_res = (T)kp.o.tol_res;
+        o.tau_root = (T)kp.o.tau_root;
+    }
+    o.win = kp.o.plateau_win;
+    o.frac = (T)kp.o.plateau_frac;
+    o.lambda0 = (T)kp.o.lambda0;
+    o.stat_win = FB ? 0 : kp.o.stat_win;
+    o.stat_tol = (T)kp.o.stat_tol;
+
+    Lane<T, N, D> L;
+    PathIn<T, N> p;
+    int slot = 0, code = 0;
+    int ridx = 0;       // the path's state row (FP32) or solve id
+    int it0 = 0;        // iteration count at the start of a resumed path
+    int fin = 0;        // final status of a finished path that is not saved yet
+    bool active = false, done = false;
+    // wave-uniform chunk [cbase, cend) of the bin
+    int cbase = 0, cend = 0;
+    if (share.rank >= 0) {
+        cbase = fixed ? (int)((int64_t)count * share.rank / share.size) : c0 * share.rank;
+        cend = fixed ? (int)((int64_t)count * (share.rank + 1) / share.size) : cbase + c0;
+    }
+    // lanes the wave keeps busy: all, or its share of a small batch
+    const int width = (fixed && cend - cbase < 64) ? cend - cbase : 64;
+    bool drained = fixed && cbase >= cend;
+
+    while (true) {
+        const int busy = (int)__popcll(__ballot(active));
+        if (busy == 0 || (!drained && busy + min(kp.refill, width) <= width)) {
+            // ---- save the finished paths, together: a store of one or two
+            // lanes' results in every iteration costs as much as all lanes'
+            if (done) {
+                done = false;
+                if constexpr (MODE == MODE_FP32) {
+                    // the state row: k_finish turns it into the path's results
+                    f32a *rf = state_row(kp, ridx, ridx);
+#pragma unroll
+                    for (int j = 0; j < D; j += 4) {
+                        f32x4 v;
+#pragma unroll
+                        for (int q = 0; q < 4; q++) v[q] = L.X[j + q < D ? j + q : D - 1];
+                        *(f32x4 *)(rf + j) = v;
+                    }
+                    *(f32x4 *)(rf + RW_C) = f32x4{L.C, L.rinf, __int_as_float(L.it), __int_as_float(fin)};
+                    if (kp.spill_t > 0) rf[RW_ID] = __int_as_float(resume ? it0 : L.it);
+                } else {
+                    int ty[N];
+#pragma unroll
+                    for (int k = 0; k < N; k++) ty[k] = (code >> (2 * k)) & 3;
+                    double Xw[3 * N];
+                    world_points<N, FORM, T>(sc.rec, N, p.id, ty, L.X, sh, Xw);
+                    write_row<N>(kp.out.x + (size_t)ridx * kRow, Xw);
+                    kp.out.cost[ridx] = (double)L.C;
+                    kp.out.iters[ridx] = FB ? L.it + kp.out.iters[ridx] : L.it;
+                    if (kp.out.stage) {
+                        kp.out.stage[(FB ? (size_t)2 * kp.b.n : 0) + ridx] = L.it;
+                        if (resume) kp.out.stage[(size_t)3 * kp.b.n + ridx] = L.it - it0;
+                    }
+                    kp.out.status[ridx] = (uint8_t)(FB ? fin | 0x80 : fin);
+                }
+            }
+            // ---- refill the idle lanes from the wave's chunk (once enough
+            // are idle: each refill stalls the wave on the dependent loads of
+            // the new paths' inputs)
+            if (!drained && cbase >= cend) {
+                int b0 = count, ch = 0;
+                if (lane == 0) {
+                    // an estimate of what is left (other waves draw meanwhile)
+                    // sizes the chunk; the add alone hands it out
+                    const int left = count - drawn0 -
+                                     __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (left > 0) {
+                        ch = min(max(left / (4 * launch_waves()), kMinChunk), kMaxChunk);
+                        b0 = drawn0 + atomicAdd(head, ch);
+                    }
+                }
+                cbase = __builtin_amdgcn_readfirstlane(b0);
+                cend = min(cbase + __builtin_amdgcn_readfirstlane(ch), count);
+                if (cbase >= count) drained = true;
+            }
+            if (!drained) {
+                const uint64_t need = __ballot(!active);
+                const int rank = (int)__popcll(need & ((1ull << lane) - 1ull));
+                const int take = min((int)__popcll(need), cend - cbase);
+                if (!active && rank < take) {
+                    slot = off + cbase + rank;
+                    if constexpr (!FB)
+                        if (resume) slot = kp.spill_list[slot];
+                    L.it = 0;
+                    L.stat = 0;
+                    L.lam = T(0);
+                    L.keep = false;
+                    L.C = T(__builtin_huge_val());
+                    L.rinf = T(__builtin_huge_val());
+                    L.Cref = L.C;
+                    p.planar = true;
+                    if constexpr (MODE == MODE_FP32) {
+                        active = true;
+                        if (kp.rows) {
+                            ridx = slot;
+                        } else {
+                            ridx = kp.perm[slot];
+                            active = kp.out.status[ridx] == ST_RUNNING;
+                        }
+                        const f32a *rf = state_row(kp, ridx, ridx);
+                        const f32x4 rv = *(const f32x4 *)(rf + RW_RX), iv = *(const f32x4 *)(rf + RW_ID);
+#pragma unroll
+                        for (int j = 0; j < D; j += 4) {
+                            const f32x4 v = *(const f32x4 *)(rf + j);
+#pragma unroll
+                            for (int q = 0; q < 4; q++)
+                                if (j + q < D) L.X[j + q < D ? j + q : 0] = v[q];
+                        }
+#pragma unroll
+                        for (int k = 0; k < N && k < 4; k++) p.id[k] = __float_as_int(iv[k]);
+                        if constexpr (N > 4) p.id[N - 1] = ((const i32a *)rf)[RW_ID + 4];
+#pragma unroll
+                        for (int i = 0; i < 3; i++) p.rx[i] = rv[i];
+                        code = __float_as_int(rv[3]);
+                        active = active && code >= 0;  // else ended by the start kernel
+                        if (resume) {
+                            // a parked path: its state exactly as it was left
+                            L.it = ((const i32a *)rf)[RW_IT];
+                            L.lam = rf[RW_LAM];
+                            L.Cref = rf[RW_CREF];
+                            L.stat = ((const i32a *)rf)[RW_STAT];
+                        }
+                    } else {
+                        // by solve id; the fallback's lists are in no order
+                        ridx = FB ? kp.fb_list[slot] : kp.perm[slot];
+                        active = FB || kp.out.status[ridx] == ST_RUNNING;
+                        code = 0;
+#pragma unroll
+                        for (int k = 0; k < N; k++) p.id[k] = kp.b.prim[(size_t)k * kp.b.n + ridx];
+                        const int ri = kp.b.rx_index[ridx];
+#pragma unroll
+                        for (int k = 0; k < N; k++)
+                            code |= prim_type(p.id[k], kp.s.n_pl, kp.s.n_pl_ln, kp.s.n_pl_ln_q) << (2 * k);
+                        double rx[3];
+#pragma unroll
+                        for (int i = 0; i < 3; i++) {
+                            rx[i] = kp.b.rx[3 * (size_t)ri + i];
+                            p.rx[i] = (T)rx[i];
+                        }
+                        if constexpr (FB) {
+                            int ty[kMaxN], ids[kMaxN];
+#pragma unroll
+                            for (int k = 0; k < kMaxN; k++) {
+                                ids[k] = p.id[k < N ? k : 0];
+                                ty[k] = (code >> (2 * (k < N ? k : 0))) & 3;
+                            }
+                            // from the FP32 end point (already root-like)
+                            const double *row = kp.out.x + (size_t)ridx * kRow;
+                            T L0[3 * kMaxN];
+                            const int st0 = start_path<MODE, FORM>(kp, ridx, N, ids, ty, rx, sh, row, L0);
+#pragma unroll
+                            for (int j = 0; j < D; j++) L.X[j] = L0[j];
+                            if (st0 != ST_RUNNING) {
+                                // finished before the first iteration: the start
+                                // points as the solver holds them (zeros for bad
+                                // input)
+                                double Xs[3 * N];
+                                world_points<N, FORM, T>(sc.rec, st0 == ST_BAD ? 0 : N, ids, ty, L.X, sh, Xs);
+                                write_row<N>(kp.out.x + (size_t)ridx * kRow, Xs);
+                                kp.out.cost[ridx] = __builtin_huge_val();
+                                kp.out.status[ridx] = (uint8_t)(st0 | 0x80);
+                                active = false;
+                            }
+                        } else {
+                            const double *row = kp.out.x + (size_t)ridx * kRow;
+#pragma unroll
+                            for (int j = 0; j < D; j++) L.X[j] = row[j];
+                            if (resume) {
+                                L.it = kp.out.iters[ridx];
+                                L.lam = kp.spill_f[ridx];
+                                L.Cref = kp.spill_f[(size_t)kp.b.n + ridx];
+                                L.stat = (int)kp.spill_f[(size_t)2 * kp.b.n + ridx];
+                            }
+                        }
+                    }
+                    it0 = L.it;
+                    if constexpr (REFR) {
+                        if (active) {
+#pragma unroll
+                            for (int k = 0; k < N; k++) {
+                                const int t = (code >> (2 * k)) & 3;
+                                p.planar = p.planar &&
+                                           (t == TL || (t == TP && sc.rec[(size_t)p.id[k] * kRec + 16] <= T(0)));
+                            }
+                        }
+                    }
+                }
+                cbase += take;
+                if (fixed && cbase >= cend) drained = true;
+            }
+            if (!__any(active)) {
+                if (drained) break;
+                continue;
+            }
+        }
+        // the bin is drained and few lanes are busy: park them (wave-uniform)
+        if (may_spill && drained && (int)__popcll(__ballot(active)) <= kp.spill_t) {
+            if (active) {
+                // ---- a parked path: its exact state, for the straggler launch
+                if constexpr (MODE == MODE_FP32) {
+                    f32a *rf = state_row(kp, ridx, ridx);
+#pragma unroll
+                    for (int j = 0; j < D; j++) rf[j] = L.X[j];
+                    rf[RW_IT] = __int_as_float(L.it);
+                    rf[RW_LAM] = L.lam;
+                    rf[RW_CREF] = L.Cref;
+                    rf[RW_STAT] = __int_as_float(L.stat);
+                } else {
+                    double *row = kp.out.x + (size_t)ridx * kRow;
+#pragma unroll
+                    for (int j = 0; j < D; j++) row[j] = L.X[j];
+                    kp.out.iters[ridx] = L.it;
+                    kp.spill_f[ridx] = (double)L.lam;
+                    kp.spill_f[(size_t)kp.b.n + ridx] = (double)L.Cref;
+                    kp.spill_f[(size_t)2 * kp.b.n + ridx] = (double)L.stat;
+                }
+                kp.spill_list[off + atomicAdd(&kp.spill_cnt[N - 1], 1)] = slot;
+                active = false;
+            }
+            continue;
+        }
+        // ---- one iteration on every busy lane
+        // (the bins are sorted by type sequence, so the lanes of a wave mostly
+        // share theirs, and the branches on a type skip the others' rows)
+        int st = ST_RUNNING;
+        bool generic = active;
+        if constexpr (TYPED && MODE == MODE_FP32 && FORM == 1 && N <= 3) {
+            // every planar path takes its fixed-type step, whatever the other
+            // lanes of its wave hold, so that its result does not depend on
+            // the schedule: one sequence after the other
+            generic = active && !(REFR ? p.planar : (code & 0x2AA) == 0);
+            uint64_t todo = __ballot(active && !generic);
+            while (todo) {
+                const int c0 = __builtin_amdgcn_readlane(code, (int)__builtin_ctzll(todo));
+                const bool mine = active && !generic && code == c0;
+                todo &= ~__ballot(mine);
+                if (mine) st = lm_step_uniform<T, N, FORM>(c0, sc, p, L, o);
+            }
+        }
+        if (generic) {
+#pragma unroll
+            for (int k = 0; k < N; k++) p.ty[k] = (code >> (2 * k)) & 3;
+            if constexpr (!REFR) p.planar = (code & 0x2AA) == 0;
+            if constexpr (FORM) st = lm_step_param<T, N, REFR>(sc, p, L, o);
+            else st = lm_step<T, N, REFR>(sc, p, L, o);
+        }
+        if (active && st != ST_RUNNING) {
+            active = false;
+            done = true;
+            fin = st;
+        }
+    }
+}
+
+// Waves per SIMD each kernel is compiled for: as many as its registers allow
+// without spills (VGPRs per lane of orders 1-5: FP32 parametric 93 / 141 / 198
+// / 160 / 191, implicit 118 / 159 / 218 / 189 / 225; FP64 parametric 122 / 182 /
+// 223 / 261 / 301, implicit 142 / 220 / 280 / 344 / 400).
+template <int MODE, int N, int FORM = 0> struct Occ { static constexpr int W = 1; };
+template <> struct Occ<MODE_FP32, 1, 0> { static constexpr int W = 4; };
+template <> struct Occ<MODE_FP32, 2, 0> { static constexpr int W = 3; };
+template <> struct Occ<MODE_FP32, 3, 0> { static constexpr int W = 2; };
+template <> struct Occ<MODE_FP32, 4, 0> { static constexpr int W = 2; };
+template <> struct Occ<MODE_FP32, 5, 0> { static constexpr int W = 2; };
+template <> struct Occ<MODE_PLAIN64, 1, 0> { static constexpr int W = 3; };
+template <> struct Occ<MODE_PLAIN64, 2, 0> { static constexpr int W = 2; };
+template <> struct Occ<MODE_FP32, 1, 1> { static constexpr int W = 4; };
+template <> struct Occ<MODE_FP32, 2, 1> { static constexpr int W = 3; };
+template <> struct Occ<MODE_FP32, 3, 1> { static constexpr int W = 2; };
+template <> struct Occ<MODE_FP32, 4, 1> { static constexpr int W = 3; };
+template <> struct Occ<MODE_FP32, 5, 1> { static constexpr int W = 2; };
+template <> struct Occ<MODE_PLAIN64, 1, 1> { static constexpr int W = 4; };
+template <> struct Occ<MODE_PLAIN64, 2, 1> { static constexpr int W = 2; };
+template <> struct Occ<MODE_PLAIN64, 3, 1> { static constexpr int W = 2; };
+
+// The mixed-order kernels (and the one of orders 1-3).
+template <int MODE, int FORM> struct OccAll { static constexpr int W = (MODE == MODE_FP32) ? 2 : 1; };
+
+// Scene records staged in LDS by every block of a persistent launch (the
+// whole scene: 651 primitives x 18 floats = 47 KB for the street canyon).
+template <int MODE, bool LDS>
+__device__ __forceinline__ const typename ModeT<MODE>::T *stage_scene(const KParams &kp)
+{
+    using T = typename ModeT<MODE>::T;
+    const T *g = (MODE == MODE_FP32) ? (const T *)kp.s.rec32 : (const T *)kp.s.rec64;
+    if (!LDS) return g;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T *l = reinterpret_cast<T *>(smem_raw);
+    const int total = kp.s.n_all * kRec;
+    for (int i = threadIdx.x; i < total; i += blockDim.x) l[i] = g[i];
+    __syncthreads();
+    return l;
+}
+
+// The waves of a mixed-order launch are dealt to the nonempty orders in
+// proportion to their work (paths x order, and a sixteenth of the whole to
+// each so that none waits for a wave), long paths first.  lo[k], lo[k - 1]:
+// the waves that start with order k.
+struct OrderShare {
+    int wave, lo[kMaxN + 1];
+    __device__ __forceinline__ BinShare of(int k) const
+    {
+        const int size = lo[k - 1] - lo[k], r = wave - lo[k];
+        return {r >= 0 && r < size ? r : -1, size};
+    }
+};
+
+__device__ __forceinline__ OrderShare order_share(const int *cnt, int max_order)
+{
+    OrderShare s;
+    const int all = launch_waves();
+    s.wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    float w[kMaxN + 1], tot = 0.0f, sum = 0.0f;
+#pragma unroll
+    for (int k = 1; k <= kMaxN; k++) {
+        w[k] = (k <= max_order) ? (float)cnt[k - 1] * (float)k : 0.0f;
+        tot += w[k];
+    }
+#pragma unroll
+    for (int k = 1; k <= kMaxN; k++) {
+        w[k] = (w[k] > 0.0f) ? w[k] + tot * (1.0f / 16.0f) : 0.0f;
+        sum += w[k];
+    }
+    float upto = 0.0f;
+    s.lo[kMaxN] = 0;
+#pragma unroll
+    for (int k = kMaxN; k >= 1; k--) {
+        upto += w[k];
+        s.lo[k - 1] = min(all, (int)((float)all * (upto / sum) + 0.5f));
+    }
+    return s;
+}
+
+// A bin's turn: its own waves in the first pass, every wave in the second,
+// with what its own waves have not taken.
+__device__ __forceinline__ bool turn(const BinShare s, int pass) { return pass || s.rank >= 0; }
+__device__ __forceinline__ BinShare part(const BinShare s, int pass) { return {pass ? -1 : s.rank, s.size}; }
+
+// One persistent launch over every order (register budget of order 5).
+// FORM 0: the implicit form (points as unknowns); 1: the parametric form.
+// REFR: the scene has refracting facets; their rows are compiled into this
+// kernel only (a branch left in the other kernels slowed the stress
+// workload's LM launches by 16% in the parametric and 7% in the implicit
+// form, though no lane took it), so such scenes run this schedule.
+template <int MODE, bool LDS, int FORM, bool REFR>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OccAll<MODE, FORM>::W, OccAll<MODE, FORM>::W)))
+k_lm(KParams kp)
+{
+    const int *cnt = kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt;
+    if (cnt[0] + cnt[1] + cnt[2] + cnt[3] + cnt[4] == 0) return;  // nothing to solve: skip the staging
+    const typename ModeT<MODE>::T *rec = stage_scene<MODE, LDS>(kp);
+    // each wave starts with one order (all orders' longest descents begin at
+    // once), then helps the others, long paths first so that the short ones
+    // fill the tail
+    const OrderShare sh = order_share(cnt, 5);
+#pragma nounroll
+    for (int pass = 0; pass < 2; pass++) {
+        if (turn(sh.of(5), pass)) lm_bin<MODE, 5, FORM, true, REFR>(kp, rec, part(sh.of(5), pass));
+        if (turn(sh.of(4), pass)) lm_bin<MODE, 4, FORM, true, REFR>(kp, rec, part(sh.of(4), pass));
+        if (turn(sh.of(3), pass)) lm_bin<MODE, 3, FORM, true, REFR>(kp, rec, part(sh.of(3), pass));
+        if (turn(sh.of(2), pass)) lm_bin<MODE, 2, FORM, true, REFR>(kp, rec, part(sh.of(2), pass));
+        if (turn(sh.of(1), pass)) lm_bin<MODE, 1, FORM, true, REFR>(kp, rec, part(sh.of(1), pass));
+    }
+}
+
+// One persistent launch over orders 3, 2, 1 with the register budget of
+// order 3 (twice the waves per SIMD of the all-order kernel in FP32); the
+// split schedule runs orders 4 and 5 beside it with their own launches.
+template <int MODE, bool LDS, int FORM>
+__global__ void __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(Occ<MODE, 3, FORM>::W, Occ<MODE, 3, FORM>::W))) k_lm_low(KParams kp)
+{
+    const int *cnt = kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt;
+    if (cnt[0] + cnt[1] + cnt[2] == 0) return;
+    const typename ModeT<MODE>::T *rec = stage_scene<MODE, LDS>(kp);
+    const OrderShare sh = order_share(cnt, 3);
+#pragma nounroll
+    for (int pass = 0; pass < 2; pass++) {
+        if (turn(sh.of(3), pass)) lm_bin<MODE, 3, FORM>(kp, rec, part(sh.of(3), pass));
+        if (turn(sh.of(2), pass)) lm_bin<MODE, 2, FORM>(kp, rec, part(sh.of(2), pass));
+        if (turn(sh.of(1), pass)) lm_bin<MODE, 1, FORM>(kp, rec, part(sh.of(1), pass));
+    }
+}
+
+// One persistent launch per order, each with its own register budget.
+template <int MODE, int N, bool LDS, int FORM>
+__global__ void __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(Occ<MODE, N, FORM>::W, Occ<MODE, N, FORM>::W))) k_lm_one(KParams kp)
+{
+    if ((kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt)[N - 1] == 0) return;
+    const typename ModeT<MODE>::T *rec = stage_scene<MODE, LDS>(kp);
+    // fixed-type steps for the planar paths of orders 1-3 here as in the
+    // mixed-order kernel (stress LM stage 22.0 -> 21.7 ms, bit-identical)
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    lm_bin<MODE, N, FORM, (N <= 3)>(kp, rec, BinShare{wave, launch_waves()});
+}
+
+// ------------------------------------------------------------------ kernel table
+// order 0: the mixed-order kernel; 1..5: the per-order kernels; 6: the
+// kernel of orders 1-3.  refr: the mixed-order kernel with the rows of
+// refracting facets (order ignored).  The fallback runs one mixed-order
+// launch in the solve's form (from the FP32 end point).
+template <int MODE, int FORM, bool LDS>
+const void *lm_kernel_of(int order, bool refr)
+{
+    if (refr) return (const void *)k_lm<MODE, LDS, FORM, true>;
+    if constexpr (MODE == MODE_FALLBACK64) {
+        return (const void *)k_lm<MODE, LDS, FORM, false>;
+    } else {
+        switch (order) {
+        case 0: return (const void *)k_lm<MODE, LDS, FORM, false>;
+        case 1: return (const void *)k_lm_one<MODE, 1, LDS, FORM>;
+        case 2: return (const void *)k_lm_one<MODE, 2, LDS, FORM>;
+        case 3: return (const void *)k_lm_one<MODE, 3, LDS, FORM>;
+        case 4: return (const void *)k_lm_one<MODE, 4, LDS, FORM>;
+        case 5: return (const void *)k_lm_one<MODE, 5, LDS, FORM>;
+        default: return (const void *)k_lm_low<MODE, LDS, FORM>;
+        }
+    }
+}
+
+template const void *lm_kernel_of<MPT_LM_MODE, MPT_LM_FORM, MPT_LM_LDS != 0>(int order, bool refr);
+
+}  // namespace mpt

@@ -28,7 +28,8 @@ struct mpt_ctx {
     size_t lds_max = 65536;  // dynamic LDS a block may use
     // scene
     double *raw = nullptr, *rec64 = nullptr, *wd = nullptr, *sd = nullptr, *rfd = nullptr;
-    float *rec32 = nullptr;
+    float *rec32 = nullptr, *occ = nullptr;
+    size_t occ_cap = 0;
     size_t scene_cap = 0, raw_cap = 0, wd_cap = 0, sd_cap = 0, rfd_cap = 0;
     // candidate generation: sample points, their counts, path counts / offsets
     double *samp = nullptr;
@@ -198,6 +199,7 @@ mpt_status mpt_destroy(mpt_ctx *c)
     hipFree(c->raw);
     hipFree(c->rec64);
     hipFree(c->rec32);
+    hipFree(c->occ);
     hipFree(c->wd);
     hipFree(c->sd);
     hipFree(c->rfd);
@@ -309,6 +311,7 @@ mpt_status mpt_scene_upload(mpt_ctx *c, const mpt_scene_desc *d)
     if ((st = ensure(c, (void **)&c->rec64, &cap64, n_all * kRec, sizeof(double)))) return st;
     if ((st = ensure(c, (void **)&c->rec32, &cap32, n_all * kRec, sizeof(float)))) return st;
     c->scene_cap = cap64 < cap32 ? cap64 : cap32;
+    if ((st = ensure(c, (void **)&c->occ, &c->occ_cap, ((size_t)np + nq) * 8, sizeof(float)))) return st;
     std::vector<double> host(raw_n ? raw_n : 1);
     size_t o = 0;
     memcpy(host.data() + o, d->planes, (size_t)np * 13 * 8), o += (size_t)np * 13;
@@ -332,6 +335,7 @@ mpt_status mpt_scene_upload(mpt_ctx *c, const mpt_scene_desc *d)
     s.side = sides ? c->sd : nullptr;
     s.rec64 = c->rec64;
     s.rec32 = c->rec32;
+    s.occ = c->occ;
     s.n_pl = np;
     s.n_pl_ln = np + nl;
     s.n_pl_ln_q = np + nl + nq;
@@ -352,6 +356,7 @@ mpt_status mpt_scene_upload(mpt_ctx *c, const mpt_scene_desc *d)
                                  c->stream));
     }
     launch_pack(c->raw, refr ? c->rfd : nullptr, s, np, nl, nq, nc, c->stream);
+    launch_occluders(s, c->stream);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->s = s;
@@ -1284,13 +1289,16 @@ mpt_status mpt_mlp_load(mpt_ctx *c, const void *blob, size_t bytes)
     return st ? fail(c, st, "network load failed (bad blob)") : MPT_OK;
 }
 
-static mpt_status cand_samples(mpt_ctx *c, int k)
+// Sample points, counts and boxes of the objects; clears the n0 + n1 words of
+// two bit arrays.
+static mpt_status cand_samples(mpt_ctx *c, int k, uint32_t *z0, int64_t n0, uint32_t *z1, int64_t n1, float **box)
 {
     mpt_status st;
-    const size_t n = (size_t)c->s.n_all;
-    if ((st = ensure(c, (void **)&c->samp, &c->samp_cap, n * (size_t)(k * k + 2 * k) * 3, sizeof(double)))) return st;
+    const size_t n = (size_t)c->s.n_all, pts = n * (size_t)(k * k + 2 * k) * 3;
+    if ((st = ensure(c, (void **)&c->samp, &c->samp_cap, pts + 4 * n, sizeof(double)))) return st;
     if ((st = ensure(c, (void **)&c->scnt, &c->scnt_cap, n, sizeof(int)))) return st;
-    launch_samples(c->s, k, c->samp, c->scnt, c->stream);
+    *box = (float *)(c->samp + pts);
+    launch_samples(c->s, k, c->samp, c->scnt, *box, z0, n0, z1, n1, c->stream);
     return MPT_OK;
 }
 
@@ -1310,9 +1318,10 @@ mpt_status mpt_visibility(mpt_ctx *c, int32_t k, double min_seg, uint32_t *vis, 
     if (st) return st;
     if (!vis || !bs) return fail(c, MPT_E_INVALID_ARG, "null visibility output");
     hipSetDevice(c->device);
-    if ((st = cand_samples(c, k))) return st;
     const int W = (c->s.n_all + 31) / 32;
-    launch_visibility(c->s, k, min_seg, c->samp, c->scnt, vis, bs, W, c->lds_max, c->cu, c->stream);
+    float *box;
+    if ((st = cand_samples(c, k, vis, (int64_t)c->s.n_all * W, bs, W, &box))) return st;
+    launch_visibility(c->s, k, min_seg, c->samp, c->scnt, box, vis, bs, W, c->lds_max, c->cu, c->stream);
     HIPCHK(c, hipGetLastError());
     return MPT_OK;
 }
@@ -1325,8 +1334,9 @@ mpt_status mpt_visibility_rx(mpt_ctx *c, const double *rx, int32_t n_rx, int32_t
     if (n_rx < 0) return fail(c, MPT_E_INVALID_ARG, "negative receiver count");
     if (n_rx > 0 && (!rx || !ue)) return fail(c, MPT_E_INVALID_ARG, "null receiver argument");
     hipSetDevice(c->device);
-    if ((st = cand_samples(c, k))) return st;
     const int W = (c->s.n_all + 31) / 32;
+    float *box;
+    if ((st = cand_samples(c, k, ue, (int64_t)n_rx * W, nullptr, 0, &box))) return st;
     launch_visibility_rx(c->s, k, min_seg, c->samp, c->scnt, rx, n_rx, ue, los, W, c->lds_max, c->cu, c->stream);
     HIPCHK(c, hipGetLastError());
     return MPT_OK;
@@ -1349,9 +1359,12 @@ mpt_status mpt_candidates(mpt_ctx *c, const uint32_t *vis, const uint32_t *bs, c
     hipSetDevice(c->device);
     const int W = (c->s.n_all + 31) / 32;
     const int64_t nb = (n + 1023) / 1024;
-    if ((st = ensure(c, (void **)&c->ccnt, &c->ccnt_cap, (size_t)n, sizeof(int64_t)))) return st;
+    const size_t heads = (size_t)n_rx * c->s.n_all;
+    if ((st = ensure(c, (void **)&c->ccnt, &c->ccnt_cap, (size_t)n + (heads + 1) / 2, sizeof(int64_t)))) return st;
+    int *last = (int *)(c->ccnt + n);
     if ((st = ensure(c, (void **)&c->csum, &c->csum_cap, (size_t)nb + 1, sizeof(int64_t)))) return st;
-    launch_cand_count(c->s, vis, bs, ue, W, n_rx, max_order, edge_last ? 1 : 0, c->ccnt, c->csum, c->cu, c->stream);
+    launch_cand_count(c->s, vis, bs, ue, W, n_rx, max_order, edge_last ? 1 : 0, c->ccnt, c->csum, last, c->cu,
+                      c->stream);
     HIPCHK(c, hipGetLastError());
     int64_t total = 0;
     HIPCHK(c, hipMemcpyAsync(&total, c->csum + nb, sizeof total, hipMemcpyDeviceToHost, c->stream));
@@ -1360,8 +1373,8 @@ mpt_status mpt_candidates(mpt_ctx *c, const uint32_t *vis, const uint32_t *bs, c
     if (cap == 0 || total == 0) return MPT_OK;
     if (cap < total) return fail(c, MPT_E_CAPACITY, "%lld candidates do not fit in %lld", (long long)total,
                                  (long long)cap);
-    launch_cand_fill(c->s, vis, bs, ue, W, n_rx, max_order, edge_last ? 1 : 0, c->ccnt, cap, rx_index, order, prim,
-                     c->cu, c->stream);
+    launch_cand_fill(c->s, vis, bs, ue, W, n_rx, max_order, edge_last ? 1 : 0, c->ccnt, last, cap, rx_index, order,
+                     prim, c->cu, c->stream);
     HIPCHK(c, hipGetLastError());
     return MPT_OK;
 }

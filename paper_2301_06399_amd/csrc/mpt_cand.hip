@@ -3,13 +3,15 @@
 // Figs. 3-4), and the enumeration of every simple path BS -> objects -> UE
 // of at most max_order objects as interaction lists.
 //
+//  k_occluders      bounding boxes of the facets and patches (scene upload)
 //  k_samples        sample points of every object (mpt_geom.hpp)
-//  k_vis_pairs      one wave per object pair i < j: lanes test sample pairs
-//                   (sides / wedges, then every facet and patch staged in LDS)
-//  k_vis_bs         one wave per object: its samples against BS
-//  k_vis_rx         one wave per (receiver, object): its samples against RX
-//  k_cand_count     one block per (receiver, first object): path counts per
-//                   order from popcounts of the bit rows
+//  k_vis_pairs      one wave per object and group of objects: lanes test sample
+//                   pairs (sides / wedges, then the facets and patches whose
+//                   boxes meet the shaft between the objects); the BS row
+//  k_vis_rx         one wave per receiver and 64 samples
+//  k_cand_last      the ends of the paths through each object
+//  k_cand_count     one wave per (receiver, first object): path counts per
+//                   order
 //  k_scan_*         exclusive scan of the counts (receiver, order, first object)
 //  k_cand_fill      one block per (receiver, first object): writes the paths in
 //                   increasing object ids at the scanned offsets
@@ -18,17 +20,38 @@
 
 namespace mpt {
 
-__global__ void __launch_bounds__(256) k_fill_u32(uint32_t *__restrict__ p, int64_t n)
+// Boxes of the facets and patches (scene upload).
+__global__ void __launch_bounds__(64) k_occluders(SceneDev s, float *__restrict__ occ)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
+    const int o = blockIdx.x * blockDim.x + threadIdx.x;
+    const int nq = s.n_pl_ln_q - s.n_pl_ln;
+    if (o >= s.n_pl + nq) return;
+    const int g = o < s.n_pl ? o : s.n_pl_ln + (o - s.n_pl);
+    occluder_box(o < s.n_pl ? TP : TQ, s.rec64 + (size_t)g * kRec, occ + (size_t)o * 8);
 }
 
-__global__ void __launch_bounds__(256) k_samples(SceneDev s, int k, double *__restrict__ samp, int *__restrict__ cnt)
+__global__ void __launch_bounds__(64) k_samples(SceneDev s, int k, double *__restrict__ samp, int *__restrict__ cnt,
+                                                float *__restrict__ box, uint32_t *__restrict__ z0, int64_t n0,
+                                                uint32_t *__restrict__ z1, int64_t n1)
 {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = g; i < n0 + n1; i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < n0) z0[i] = 0u;
+        else z1[i - n0] = 0u;
+    }
     if (g >= s.n_all) return;
-    cnt[g] = obj_samples(s, g, k, samp + (size_t)g * sample_cap(k) * 3);
+    double *pts = samp + (size_t)g * sample_cap(k) * 3;
+    const int m = obj_samples(s, g, k, pts);
+    cnt[g] = m;
+    for (int c = 0; c < 3; c++) {
+        double lo = pts[c], hi = pts[c];
+        for (int j = 1; j < m; j++) {
+            lo = fmin(lo, pts[3 * j + c]);
+            hi = fmax(hi, pts[3 * j + c]);
+        }
+        box[(size_t)g * 8 + c] = (float)lo;
+        box[(size_t)g * 8 + 4 + c] = (float)hi;
+    }
 }
 
 // Plane and quadric records staged in LDS (or read from HBM without).
@@ -49,112 +72,261 @@ __device__ __forceinline__ Occluders stage_occluders(const SceneDev &s, double *
     return {s.rec64, s.rec64 + (size_t)s.n_pl_ln * kRec};
 }
 
-// Pair index p of the strict upper triangle (row-major) -> (i, j), i < j.
-__device__ __forceinline__ void pair_of(int64_t p, int n, int &i, int &j)
+// Sample points per object by type (a bound: the lanes a type gets).
+__device__ __forceinline__ int type_samples(int t, int k) { return t == TL ? k : t == TC ? 2 * k : k * k; }
+
+// The objects of type t: [lo, hi).
+__device__ __forceinline__ void type_range(const SceneDev &s, int t, int &lo, int &hi)
 {
-    // rows before i hold i n - i (i + 1) / 2 pairs; start from the real root
-    // and correct by whole rows
-    const double nn = (double)n - 0.5;
-    int r = (int)(nn - sqrt(nn * nn - 2.0 * (double)p));
-    if (r < 0) r = 0;
-    if (r > n - 2) r = n - 2;
-    auto before = [n](int64_t q) { return q * n - q * (q + 1) / 2; };
-    while (r > 0 && before(r) > p) r--;
-    while (r < n - 2 && before(r + 1) <= p) r++;
-    i = r;
-    j = (int)(p - before(r)) + r + 1;
+    lo = t == TP ? 0 : t == TL ? s.n_pl : t == TQ ? s.n_pl_ln : s.n_pl_ln_q;
+    hi = t == TP ? s.n_pl : t == TL ? s.n_pl_ln : t == TQ ? s.n_pl_ln_q : s.n_all;
 }
 
+// Occluders whose box meets the shaft, kTile at a time: the wave's lanes test
+// one box each and list the survivors in LDS; then every lane tests its own
+// segment against the listed ones.  The street canyon's shafts keep 20 to 40 of
+// 251 facets; the order of the tests does not change a decision.
+constexpr int kTile = 512;
+
+struct CullList {
+    uint16_t *list;  // [kTile] of this wave
+    int tile, n;     // tile the list holds (-1: none) and its length
+};
+
+__device__ __forceinline__ void cull_tile(const SceneDev &s, const Shaft &sh, int tile, CullList &c)
+{
+    const int nocc = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln), lane = threadIdx.x & 63;
+    c.tile = tile;
+    c.n = 0;
+    const int hi = min(kTile, nocc - tile * kTile);
+    for (int q = 0; q < hi; q += 64) {
+        const int o = q + lane;
+        bool keep = false;
+        if (o < hi) {
+            const float4 a = *reinterpret_cast<const float4 *>(s.occ + (size_t)(tile * kTile + o) * 8),
+                         b = *reinterpret_cast<const float4 *>(s.occ + (size_t)(tile * kTile + o) * 8 + 4);
+            const float box[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            keep = !outside_shaft(sh, box);
+        }
+        const uint64_t m = __ballot(keep);
+        if (keep) c.list[c.n + (int)__popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)o;
+        c.n += (int)__popcll(m);
+    }
+    // the list is written and read by one wave: its LDS accesses are in order
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The lanes (of `alive`) whose segment no occluder blocks.
+__device__ __forceinline__ bool unblocked(const SceneDev &s, const Occluders &oc, const Shaft &sh, CullList &c,
+                                          bool alive, const Seg &g, int gi, int gj)
+{
+    const int nocc = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln);
+    for (int tile = 0; tile * kTile < nocc; tile++) {
+        if (c.tile != tile) cull_tile(s, sh, tile, c);
+        for (int q = 0; q < c.n; q++) {
+            if (!__any(alive)) return false;
+            const int o = tile * kTile + __builtin_amdgcn_readfirstlane((int)c.list[q]);
+            if (alive && blocks(s, oc.prec, oc.qrec, o, g, gi, gj)) alive = false;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    return alive;
+}
+
+__device__ __forceinline__ float wave_min(float v)
+{
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v = fminf(v, __shfl_xor(v, d));
+    return v;
+}
+
+// The samples of every object against one point X (BS or a receiver), 64 of
+// the flattened samples (type-major, type_samples per object) per call: bit j
+// of `row` is set when a sample of object j sees X.  from_x: the segments run
+// from X to the sample (BS), else from the sample to X.  With `los`, the sample
+// after the last is BS itself, seen or not in *los.
+__device__ __forceinline__ void see_point(const SceneDev &s, const Occluders &oc, CullList c, int k, double min_seg,
+                                          const double *__restrict__ samp, const int *__restrict__ cnt, int chunk,
+                                          const double *X, bool from_x, uint32_t *row, uint8_t *los)
+{
+    const int lane = threadIdx.x & 63, sc = sample_cap(k);
+    int idx = chunk * 64 + lane, j = -1, sj = 0;
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+        int lo, hi;
+        type_range(s, t, lo, hi);
+        const int m = type_samples(t, k), len = (hi - lo) * m;
+        if (j < 0 && idx >= 0 && idx < len) {
+            j = lo + idx / m;
+            sj = idx % m;
+        }
+        idx -= len;
+    }
+    const bool is_los = los && idx == 0;  // one past the last sample
+    double S[3] = {s.tx[0], s.tx[1], s.tx[2]};
+    bool alive = is_los;
+    if (j >= 0 && sj < cnt[j]) {
+        double d[3];
+        for (int i = 0; i < 3; i++) {
+            S[i] = samp[((size_t)j * sc + sj) * 3 + i];
+            d[i] = X[i] - S[i];
+        }
+        alive = leaves_obj(s, j, S, d);
+    }
+    const Seg g = (from_x || is_los) ? segment(is_los ? S : X, is_los ? X : S, min_seg) : segment(S, X, min_seg);
+    alive = alive && g.ok;
+    if (!__any(alive)) {
+        if (is_los) *los = 0;
+        return;
+    }
+    float lo[3], hi[3], x[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const float v = (float)S[i];
+        lo[i] = wave_min(alive ? v : __builtin_huge_valf());
+        hi[i] = -wave_min(alive ? -v : __builtin_huge_valf());
+        x[i] = (float)X[i];
+    }
+    const Shaft sh = shaft_between(lo, hi, x, x);
+    c.tile = -1;
+    alive = unblocked(s, oc, sh, c, alive, g, is_los ? -1 : from_x ? -1 : j, is_los ? -1 : from_x ? j : -1);
+    if (is_los) *los = alive ? 1 : 0;
+    // the first seeing sample of each object sets its bit
+    const uint64_t m = __ballot(alive && j >= 0);
+    const int first = max(0, lane - sj);
+    const uint64_t before = ((1ull << lane) - 1ull) & ~((1ull << first) - 1ull);
+    if (alive && j >= 0 && (m & before) == 0) atomicOr(row + (j >> 5), 1u << (j & 31));
+}
+
+__device__ __forceinline__ int flat_samples(const SceneDev &s, int k)
+{
+    int n = 0;
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+        int lo, hi;
+        type_range(s, t, lo, hi);
+        n += (hi - lo) * type_samples(t, k);
+    }
+    return n;
+}
+
+// The object pairs i < j, then the BS row.  A wave takes object i and as many
+// consecutive objects j of one type as their sample pairs fit its lanes (one
+// with several rounds where they do not), culls the occluders once for all of
+// them, and sets the bits of the pairs some sample pair of which is free.
+// Bound: FP64 vector issue.  One wave per pair with every facet tested by every
+// lane took 2.34 ms (and the BS row 0.10 ms) on the street canyon (651 objects,
+// 4 samples per side); this takes 0.60 ms for both.
 __global__ void __launch_bounds__(256) k_vis_pairs(SceneDev s, int k, double min_seg, const double *__restrict__ samp,
-                                                   const int *__restrict__ cnt, uint32_t *__restrict__ V, int W,
-                                                   int lds)
+                                                   const int *__restrict__ cnt, const float *__restrict__ obox,
+                                                   uint32_t *__restrict__ V, uint32_t *__restrict__ B, int W, int lds)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ uint16_t lists[4][kTile];
     const Occluders oc = stage_occluders(s, reinterpret_cast<double *>(smem_raw), lds);
     const int n = s.n_all, sc = sample_cap(k), lane = threadIdx.x & 63;
-    const int64_t npairs = (int64_t)n * (n - 1) / 2;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t p = wave; p < npairs; p += nwave) {
-        int i, j;
-        pair_of(p, n, i, j);
-        const int mi = cnt[i], mj = cnt[j], tot = mi * mj;
-        const double *Si = samp + (size_t)i * sc * 3, *Sj = samp + (size_t)j * sc * 3;
-        bool found = false;
-        for (int t0 = 0; t0 < tot && !found; t0 += 64) {
-            const int t = t0 + lane;
-            bool vis = false;
-            if (t < tot) {
-                const double *P = Si + 3 * (t / mj), *Q = Sj + 3 * (t % mj);
-                const double d[3] = {Q[0] - P[0], Q[1] - P[1], Q[2] - P[2]};
-                const double e[3] = {P[0] - Q[0], P[1] - Q[1], P[2] - Q[2]};
-                vis = leaves_obj(s, i, P, d) && leaves_obj(s, j, Q, e) &&
-                      !seg_blocked(s, oc.prec, oc.qrec, P, Q, i, j, min_seg);
-            }
-            found = __any(vis);
+    const bool one_tile = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln) <= kTile;
+    CullList cull{lists[threadIdx.x >> 6], -1, 0};
+    const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    const int nwave = (int)((gridDim.x * blockDim.x) >> 6);
+    const int64_t pairs = (int64_t)n * n;
+    const int nbs = (flat_samples(s, k) + 63) / 64;
+    for (int64_t p = wave; p < pairs + nbs; p += nwave) {
+        if (p >= pairs) {
+            see_point(s, oc, cull, k, min_seg, samp, cnt, (int)(p - pairs), s.tx, true, B, nullptr);
+            continue;
         }
-        if (found && lane == 0) {
+        const int i = (int)(p / n);
+        int slot = (int)(p - (int64_t)i * n);
+        const int ti = prim_type(i, s.n_pl, s.n_pl_ln, s.n_pl_ln_q), mi = type_samples(ti, k);
+        // slots of one object i: the groups of each type in turn
+        int j0 = -1, j1 = 0, mj = 1, grp = 1;
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            int lo, hi;
+            type_range(s, t, lo, hi);
+            const int m = type_samples(t, k), gs = max(1, 64 / (mi * m)), ng = (hi - lo + gs - 1) / gs;
+            if (j0 < 0 && slot >= 0 && slot < ng) {
+                j0 = lo + slot * gs;
+                j1 = min(j0 + gs, hi);
+                mj = m;
+                grp = gs;
+            }
+            slot -= ng;
+        }
+        if (j0 < 0 || j1 - 1 <= i) continue;
+        const int tot = mi * mj, ci = cnt[i];
+        const float itot = 1.0f / (float)tot, imj = 1.0f / (float)mj;
+        Shaft sh;
+        bool have = false;
+        uint64_t seen = 0;  // lanes with a free sample pair
+        cull.tile = -1;
+        for (int t0 = 0; t0 < max(tot, 64); t0 += 64) {
+            const int idx = t0 + lane;
+            const int jj = grp > 1 ? (int)(((float)idx + 0.5f) * itot) : 0, rem = idx - jj * tot;
+            const int si = (int)(((float)rem + 0.5f) * imj), sj = rem - si * mj;
+            const int j = j0 + jj;
+            bool alive = rem < tot && j < j1 && j > i && si < ci && sj < cnt[j < j1 ? j : i];
+            Seg g;
+            g.ok = false;
+            if (alive) {
+                const double *P = samp + ((size_t)i * sc + si) * 3, *Q = samp + ((size_t)j * sc + sj) * 3;
+                g = segment(P, Q, min_seg);
+                const double e[3] = {P[0] - Q[0], P[1] - Q[1], P[2] - Q[2]};
+                alive = g.ok && leaves_obj(s, i, P, g.d) && leaves_obj(s, j, Q, e);
+            }
+            if (!__any(alive)) continue;
+            if (!have) {
+                float lo[3], hi[3];
+                const float *bi = obox + (size_t)i * 8;
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    lo[c] = __builtin_huge_valf();
+                    hi[c] = -__builtin_huge_valf();
+                }
+                for (int q = max(j0, i + 1); q < j1; q++)
+#pragma unroll
+                    for (int c = 0; c < 3; c++) {
+                        lo[c] = fminf(lo[c], obox[(size_t)q * 8 + c]);
+                        hi[c] = fmaxf(hi[c], obox[(size_t)q * 8 + 4 + c]);
+                    }
+                sh = shaft_between(bi, bi + 4, lo, hi);
+                have = true;
+            }
+            if (!one_tile) cull.tile = -1;
+            seen |= __ballot(unblocked(s, oc, sh, cull, alive, g, i, j));
+            if (grp == 1 && seen) break;
+        }
+        // lane q: group member q
+        const uint64_t mask = tot >= 64 ? ~0ull : ((1ull << tot) - 1ull) << (lane < grp ? lane * tot : 0);
+        if (lane < grp && (seen & mask)) {
+            const int j = j0 + lane;
             atomicOr(V + (size_t)i * W + (j >> 5), 1u << (j & 31));
             atomicOr(V + (size_t)j * W + (i >> 5), 1u << (i & 31));
         }
     }
 }
 
-__global__ void __launch_bounds__(256) k_vis_bs(SceneDev s, int k, double min_seg, const double *__restrict__ samp,
-                                                const int *__restrict__ cnt, uint32_t *__restrict__ B, int lds)
-{
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    const Occluders oc = stage_occluders(s, reinterpret_cast<double *>(smem_raw), lds);
-    const int sc = sample_cap(k), lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t g = wave; g < s.n_all; g += nwave) {
-        const int j = (int)g, m = cnt[j];
-        const double *S = samp + (size_t)j * sc * 3;
-        bool found = false;
-        for (int t0 = 0; t0 < m && !found; t0 += 64) {
-            const int t = t0 + lane;
-            bool vis = false;
-            if (t < m) {
-                const double *Q = S + 3 * t;
-                const double e[3] = {s.tx[0] - Q[0], s.tx[1] - Q[1], s.tx[2] - Q[2]};
-                vis = leaves_obj(s, j, Q, e) && !seg_blocked(s, oc.prec, oc.qrec, s.tx, Q, -1, j, min_seg);
-            }
-            found = __any(vis);
-        }
-        if (found && lane == 0) atomicOr(B + (j >> 5), 1u << (j & 31));
-    }
-}
-
+// The UE columns: a wave takes 64 samples of consecutive objects against one
+// receiver.  With a wave per object (four of its lanes busy for an edge's four
+// samples) and no culling 64 receivers of the street canyon took 0.50 ms, now
+// 0.14 ms.
 __global__ void __launch_bounds__(256) k_vis_rx(SceneDev s, int k, double min_seg, const double *__restrict__ samp,
                                                 const int *__restrict__ cnt, const double *__restrict__ rx, int n_rx,
                                                 uint32_t *__restrict__ U, uint8_t *__restrict__ los, int W, int lds)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ uint16_t lists[4][kTile];
     const Occluders oc = stage_occluders(s, reinterpret_cast<double *>(smem_raw), lds);
-    const int n = s.n_all, sc = sample_cap(k), lane = threadIdx.x & 63;
-    // line of sight, one thread per receiver
-    if (los)
-        for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_rx; r += (int64_t)gridDim.x * blockDim.x)
-            los[r] = seg_blocked(s, oc.prec, oc.qrec, s.tx, rx + 3 * r, -1, -1, min_seg) ? 0 : 1;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t items = (int64_t)n_rx * n;
-    for (int64_t it = wave; it < items; it += nwave) {
-        const int r = (int)(it / n), j = (int)(it % n), m = cnt[j];
-        const double *S = samp + (size_t)j * sc * 3, *R = rx + 3 * (size_t)r;
-        bool found = false;
-        for (int t0 = 0; t0 < m && !found; t0 += 64) {
-            const int t = t0 + lane;
-            bool vis = false;
-            if (t < m) {
-                const double *Q = S + 3 * t;
-                const double d[3] = {R[0] - Q[0], R[1] - Q[1], R[2] - Q[2]};
-                vis = leaves_obj(s, j, Q, d) && !seg_blocked(s, oc.prec, oc.qrec, Q, R, j, -1, min_seg);
-            }
-            found = __any(vis);
-        }
-        if (found && lane == 0) atomicOr(U + (size_t)r * W + (j >> 5), 1u << (j & 31));
+    const CullList cull{lists[threadIdx.x >> 6], -1, 0};
+    const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    const int nwave = (int)((gridDim.x * blockDim.x) >> 6);
+    const int per = (flat_samples(s, k) + 1 + 63) / 64;
+    for (int64_t it = wave; it < (int64_t)n_rx * per; it += nwave) {
+        const int r = (int)(it / per);
+        const double X[3] = {rx[3 * (size_t)r], rx[3 * (size_t)r + 1], rx[3 * (size_t)r + 2]};
+        see_point(s, oc, cull, k, min_seg, samp, cnt, (int)(it - (int64_t)r * per), X, false, U + (size_t)r * W,
+                  los ? los + r : nullptr);
     }
 }
 
@@ -179,13 +351,33 @@ __device__ __forceinline__ const uint32_t *succ(const CandGraph &G, int u)
     return (G.edge_last && is_edge(G, u)) ? nullptr : G.V + (size_t)u * G.W;
 }
 
+// Last objects of the paths that extend path[0..d-1] by one: the successors of
+// its end that see the receiver (last[end] of them), without those already on
+// the path.
+__device__ __forceinline__ int count_last(const CandGraph &G, const uint32_t *Ur, const int *last, const int *path,
+                                          int d)
+{
+    const int u = path[d - 1];
+    int c = last[u];
+    if (c == 0) return 0;  // none, or an edge object with no successor
+    const uint32_t *row = G.V + (size_t)u * G.W;
+    for (int q = 0; q < d; q++) {
+        bool twice = false;
+        for (int p = 0; p < q; p++) twice = twice || path[p] == path[q];
+        if (!twice && bit(row, path[q]) && bit(Ur, path[q])) c--;
+    }
+    return c;
+}
+
 // Depth-first walk, in increasing object ids and without recursion, of the
 // simple paths that extend path[0..d0-1] to o objects, the last one seeing
-// the receiver (row Ur).  Counts them, or writes them from position pos on.
+// the receiver (row Ur).  Counts them (the last objects of a path by `last`,
+// without walking them), or writes them from position pos on.
 template <bool WRITE>
-__device__ int64_t walk_tail(const CandGraph &G, const uint32_t *Ur, int *path, int d0, int o, int r, int64_t pos,
-                             int64_t cap, int32_t *rx_index, int32_t *order, int32_t *prim)
+__device__ int64_t walk_tail(const CandGraph &G, const uint32_t *Ur, const int *last, int *path, int d0, int o, int r,
+                             int64_t pos, int64_t cap, int32_t *rx_index, int32_t *order, int32_t *prim)
 {
+    if (!WRITE && d0 == o - 1) return count_last(G, Ur, last, path, d0);
     const uint32_t *row[kMaxN];
     uint32_t m[kMaxN];
     int w[kMaxN];
@@ -210,15 +402,15 @@ __device__ int64_t walk_tail(const CandGraph &G, const uint32_t *Ur, int *path, 
         for (int q = 0; q < d; q++) seen = seen || path[q] == v;
         if (seen) continue;
         path[d] = v;
-        if (d == o - 1) {
-            if (WRITE) {
-                rx_index[pos] = r;
-                order[pos] = o;
-                for (int q = 0; q < kMaxN; q++) prim[(size_t)q * cap + pos] = q < o ? path[q] : -1;
-                pos++;
-            } else {
-                c++;
-            }
+        if (WRITE && d == o - 1) {
+            rx_index[pos] = r;
+            order[pos] = o;
+            for (int q = 0; q < kMaxN; q++) prim[(size_t)q * cap + pos] = q < o ? path[q] : -1;
+            pos++;
+            continue;
+        }
+        if (!WRITE && d == o - 2) {
+            c += count_last(G, Ur, last, path, d + 1);
             continue;
         }
         const uint32_t *nr = succ(G, v);
@@ -231,40 +423,25 @@ __device__ int64_t walk_tail(const CandGraph &G, const uint32_t *Ur, int *path, 
     return WRITE ? pos : c;
 }
 
-// Successors v2 of v1 in increasing order into an LDS list.
-__device__ __forceinline__ int list_succ(const CandGraph &G, int v1, int *list)
+// Successors v2 of v1 in increasing order into an LDS list: the first wave
+// tests 64 objects at a time.
+__device__ __forceinline__ int list_succ(const CandGraph &G, int v1, uint16_t *list)
 {
     __shared__ int nlist;
-    if (threadIdx.x == 0) nlist = 0;
-    __syncthreads();
     const uint32_t *row = succ(G, v1);
-    if (row && threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
         int c = 0;
-        for (int w = 0; w < G.W; w++) {
-            uint32_t m = row[w];
-            while (m) {
-                const int b = __ffs(m) - 1;
-                m &= m - 1;
-                list[c++] = (w << 5) + b;
-            }
+        for (int v0 = 0; row && v0 < G.n; v0 += 64) {
+            const int v = v0 + (int)threadIdx.x;
+            const bool in = v < G.n && bit(row, v);
+            const uint64_t m = __ballot(in);
+            if (in) list[c + (int)__popcll(m & ((1ull << threadIdx.x) - 1ull))] = (uint16_t)v;
+            c += (int)__popcll(m);
         }
-        nlist = c;
+        if (threadIdx.x == 0) nlist = c;
     }
     __syncthreads();
     return nlist;
-}
-
-__device__ __forceinline__ int64_t block_sum_i64(int64_t v, int64_t *red)
-{
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const int64_t t = red[0];
-    __syncthreads();
-    return t;
 }
 
 // Inclusive scan over the block (Hillis-Steele in LDS).
@@ -286,77 +463,115 @@ __device__ __forceinline__ int64_t block_scan_i64(int64_t v, int64_t *red)
 constexpr int kCandBlock = 256;
 constexpr int kMaxObjCand = 4096;
 
-__global__ void __launch_bounds__(kCandBlock) k_cand_count(CandGraph G, int n_rx, int64_t *__restrict__ cnt)
+// last[r][v]: the successors of v that see receiver r.
+__global__ void __launch_bounds__(256) k_cand_last(CandGraph G, int n_rx, int *__restrict__ last)
 {
-    __shared__ int list[kMaxObjCand];
-    __shared__ int64_t red[kCandBlock];
     const int64_t items = (int64_t)n_rx * G.n;
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+    for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < items; it += (int64_t)gridDim.x * blockDim.x) {
+        const int r = (int)(it / G.n), v = (int)(it % G.n);
+        const uint32_t *Ur = G.U + (size_t)r * G.W, *row = succ(G, v);
+        int c = 0;
+        for (int w = 0; row && w < G.W; w++) c += __popc(row[w] & Ur[w]);
+        last[it] = c;
+    }
+}
+
+// One wave per (receiver, first object); the lanes take its successors.  One
+// block each, with the successors listed by one thread and the last objects
+// walked one by one, took 0.41 ms for 16 receivers of the street canyon (651
+// objects, orders 1-3), now 0.02 ms.
+__global__ void __launch_bounds__(256) k_cand_count(CandGraph G, int n_rx, const int *__restrict__ last,
+                                                    int64_t *__restrict__ cnt)
+{
+    const int64_t items = (int64_t)n_rx * G.n;
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t it = wave; it < items; it += nwave) {
         const int r = (int)(it / G.n), v1 = (int)(it % G.n);
         const uint32_t *Ur = G.U + (size_t)r * G.W;
         int64_t *out = cnt + (size_t)r * G.maxo * G.n + v1;
-        if (!bit(G.B, v1)) {
-            if (threadIdx.x == 0)
-                for (int o = 1; o <= G.maxo; o++) out[(size_t)(o - 1) * G.n] = 0;
-            continue;
-        }
-        const int nl = list_succ(G, v1, list);
+        const int *lr = last + (size_t)r * G.n;
+        const bool bs = bit(G.B, v1);
+        const uint32_t *row = bs ? succ(G, v1) : nullptr;
         for (int o = 1; o <= G.maxo; o++) {
             int64_t c = 0;
-            if (o == 1) {
-                c = threadIdx.x == 0 ? (int64_t)bit(Ur, v1) : 0;
-            } else {
-                for (int e = threadIdx.x; e < nl; e += blockDim.x) {
-                    const int v2 = list[e];
-                    if (o == 2) {
-                        c += bit(Ur, v2);
-                    } else {
-                        int path[kMaxN] = {v1, v2};
-                        c += walk_tail<false>(G, Ur, path, 2, o, r, 0, 0, nullptr, nullptr, nullptr);
-                    }
+            if (o <= 2) {
+                c = bs && lane == 0 ? (o == 1 ? (int64_t)bit(Ur, v1) : (int64_t)lr[v1]) : 0;
+            } else if (row) {
+                for (int v2 = lane; v2 < G.n; v2 += 64) {
+                    if (!bit(row, v2)) continue;
+                    int path[kMaxN] = {v1, v2};
+                    c += walk_tail<false>(G, Ur, lr, path, 2, o, r, 0, 0, nullptr, nullptr, nullptr);
                 }
+#pragma unroll
+                for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d);
             }
-            c = block_sum_i64(c, red);
-            if (threadIdx.x == 0) out[(size_t)(o - 1) * G.n] = c;
+            if (lane == 0) out[(size_t)(o - 1) * G.n] = c;
         }
     }
 }
 
-__global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx, const int64_t *__restrict__ off,
-                                                          int64_t cap, int32_t *__restrict__ rx_index,
-                                                          int32_t *__restrict__ order, int32_t *__restrict__ prim)
+// Writes the paths.  blockIdx.y splits the successors of a first object into
+// kFillParts consecutive parts for orders up to 3 (few first objects see BS, and
+// one block per first object left most of the device idle); the deeper orders
+// are walked by the first part's block.
+constexpr int kFillParts = 8;
+
+__global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx, const int *__restrict__ last,
+                                                          const int64_t *__restrict__ off, int64_t cap,
+                                                          int32_t *__restrict__ rx_index, int32_t *__restrict__ order,
+                                                          int32_t *__restrict__ prim)
 {
-    __shared__ int list[kMaxObjCand];
+    __shared__ uint16_t list[kMaxObjCand];
     __shared__ int64_t red[kCandBlock];
     const int64_t items = (int64_t)n_rx * G.n;
+    const int part = blockIdx.y;
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
         const int r = (int)(it / G.n), v1 = (int)(it % G.n);
         if (!bit(G.B, v1)) continue;
         const uint32_t *Ur = G.U + (size_t)r * G.W;
+        const int *lr = last + (size_t)r * G.n;
+        __syncthreads();  // the previous item's readers of list and red
         const int nl = list_succ(G, v1, list);
         for (int o = 1; o <= G.maxo; o++) {
             int64_t base = off[((size_t)r * G.maxo + (o - 1)) * G.n + v1];
             if (o == 1) {
-                if (threadIdx.x == 0 && bit(Ur, v1)) {
+                if (part == 0 && threadIdx.x == 0 && bit(Ur, v1)) {
                     rx_index[base] = r;
                     order[base] = 1;
                     for (int q = 0; q < kMaxN; q++) prim[(size_t)q * cap + base] = q < 1 ? v1 : -1;
                 }
                 continue;
             }
+            if (part && o != 3) continue;
+            // this block's part of the list, and what the parts before it write
+            int e_lo = 0, e_hi = nl;
+            if (o == 3) {
+                e_lo = (int)((int64_t)nl * part / kFillParts);
+                e_hi = (int)((int64_t)nl * (part + 1) / kFillParts);
+                int64_t before = 0;
+                for (int e = threadIdx.x; e < e_lo; e += blockDim.x) {
+                    const int path[2] = {v1, list[e]};
+                    before += count_last(G, Ur, lr, path, 2);
+                }
+                block_scan_i64(before, red);
+                base += red[blockDim.x - 1];
+                __syncthreads();
+            }
             // successors in increasing id, a chunk of blockDim at a time: each
             // thread's subtree count, scanned in list order, gives its offset
-            for (int e0 = 0; e0 < nl; e0 += blockDim.x) {
+            for (int e0 = e_lo; e0 < e_hi; e0 += blockDim.x) {
                 const int e = e0 + threadIdx.x;
                 int64_t c = 0;
                 int v2 = -1;
-                if (e < nl) {
+                if (e < e_hi) {
                     v2 = list[e];
                     if (o == 2) {
                         c = bit(Ur, v2);
                     } else {
                         int path[kMaxN] = {v1, v2};
-                        c = walk_tail<false>(G, Ur, path, 2, o, r, 0, 0, nullptr, nullptr, nullptr);
+                        c = walk_tail<false>(G, Ur, lr, path, 2, o, r, 0, 0, nullptr, nullptr, nullptr);
                     }
                 }
                 const int64_t incl = block_scan_i64(c, red);
@@ -365,7 +580,7 @@ __global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx,
                     // consecutive threads write consecutive paths: path q of
                     // the chunk belongs to the first successor whose inclusive
                     // count exceeds q, and is the rank-th object after it
-                    const int ne = min((int)blockDim.x, nl - e0);
+                    const int ne = min((int)blockDim.x, e_hi - e0);
                     for (int64_t q = threadIdx.x; q < chunk; q += blockDim.x) {
                         int lo = 0, hi = ne - 1;
                         while (lo < hi) {
@@ -374,15 +589,16 @@ __global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx,
                             else lo = mid + 1;
                         }
                         const int w2 = list[e0 + lo];
-                        int64_t rank = q - (lo ? red[lo - 1] : 0);
+                        int rank = (int)(q - (lo ? red[lo - 1] : 0));
                         const uint32_t *row2 = G.V + (size_t)w2 * G.W;
                         int v3 = -1;
                         for (int w = 0; w < G.W && v3 < 0; w++) {
                             uint32_t m = row2[w] & Ur[w];
                             if ((v1 >> 5) == w) m &= ~(1u << (v1 & 31));
+                            if ((w2 >> 5) == w) m &= ~(1u << (w2 & 31));
                             const int pc = __popc(m);
                             if (rank < pc) {
-                                for (int z = 0; z < (int)rank; z++) m &= m - 1u;
+                                for (int z = 0; z < rank; z++) m &= m - 1u;
                                 v3 = (w << 5) + (__ffs(m) - 1);
                             }
                             rank -= pc;
@@ -404,7 +620,7 @@ __global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx,
                         order[pos] = 2;
                         for (int q = 0; q < kMaxN; q++) prim[(size_t)q * cap + pos] = q < 2 ? path[q] : -1;
                     } else {
-                        walk_tail<true>(G, Ur, path, 2, o, r, pos, cap, rx_index, order, prim);
+                        walk_tail<true>(G, Ur, lr, path, 2, o, r, pos, cap, rx_index, order, prim);
                     }
                 }
                 __syncthreads();  // red is read above; the next chunk rewrites it
@@ -477,46 +693,51 @@ static int lds_choice(const void *kern, const SceneDev &s, size_t lds_max, size_
     return lds;
 }
 
-void launch_samples(const SceneDev &s, int k, double *samp, int *cnt, hipStream_t st)
+void launch_occluders(const SceneDev &s, hipStream_t st)
 {
-    if (s.n_all == 0) return;
-    hipLaunchKernelGGL(k_samples, dim3((s.n_all + 255) / 256), dim3(256), 0, st, s, k, samp, cnt);
+    const int n = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln);
+    if (n == 0) return;
+    hipLaunchKernelGGL(k_occluders, dim3((n + 63) / 64), dim3(64), 0, st, s, (float *)s.occ);
 }
 
-void launch_visibility(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt, uint32_t *V,
-                       uint32_t *B, int W, size_t lds_max, int cu, hipStream_t st)
+void launch_samples(const SceneDev &s, int k, double *samp, int *cnt, float *box, uint32_t *z0, int64_t n0,
+                    uint32_t *z1, int64_t n1, hipStream_t st)
 {
-    const int64_t nv = (int64_t)s.n_all * W;
-    hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>((nv + 255) / 256 + 1, 4096)), dim3(256), 0, st, V,
-                       nv);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, B, (int64_t)W);
+    const int64_t n = std::max<int64_t>(s.n_all, std::min<int64_t>((n0 + n1 + 3) / 4, 64 * 1024));
+    if (n == 0) return;
+    hipLaunchKernelGGL(k_samples, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, s, k, samp, cnt, box, z0, n0, z1,
+                       n1);
+}
+
+// Blocks of a kernel that stages the occluders: as many as the records let
+// reside at once (each stages them once and then walks its items).
+static unsigned resident_blocks(int64_t waves, size_t lds_bytes, size_t lds_max, int cu)
+{
+    const size_t per = lds_bytes + 4 * kTile * sizeof(uint16_t);
+    const int64_t fit = std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(lds_max / per)));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, (int64_t)cu * fit));
+}
+
+void launch_visibility(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt, const float *box,
+                       uint32_t *V, uint32_t *B, int W, size_t lds_max, int cu, hipStream_t st)
+{
     if (s.n_all == 0) return;
     size_t bytes;
-    const int64_t npairs = (int64_t)s.n_all * (s.n_all - 1) / 2;
-    if (npairs > 0) {
-        const int lds = lds_choice((const void *)k_vis_pairs, s, lds_max, bytes);
-        const unsigned g = (unsigned)std::min<int64_t>((npairs + 3) / 4, (int64_t)cu * 64);
-        hipLaunchKernelGGL(k_vis_pairs, dim3(g), dim3(256), bytes, st, s, k, min_seg, samp, cnt, V, W, lds);
-    }
-    const int lds = lds_choice((const void *)k_vis_bs, s, lds_max, bytes);
-    hipLaunchKernelGGL(k_vis_bs, dim3((s.n_all + 3) / 4), dim3(256), bytes, st, s, k, min_seg, samp, cnt, B, lds);
+    const int lds = lds_choice((const void *)k_vis_pairs, s, lds_max, bytes);
+    hipLaunchKernelGGL(k_vis_pairs, dim3(resident_blocks((int64_t)s.n_all * s.n_all, bytes, lds_max, cu)), dim3(256),
+                       bytes, st, s, k, min_seg, samp, cnt, box, V, B, W, lds);
 }
 
 void launch_visibility_rx(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt,
                           const double *rx, int n_rx, uint32_t *U, uint8_t *los, int W, size_t lds_max, int cu,
                           hipStream_t st)
 {
-    const int64_t nu = (int64_t)n_rx * W;
-    if (nu > 0)
-        hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>((nu + 255) / 256, 4096)), dim3(256), 0, st, U,
-                           nu);
     if (n_rx == 0) return;
     size_t bytes;
     const int lds = lds_choice((const void *)k_vis_rx, s, lds_max, bytes);
-    const int64_t items = (int64_t)n_rx * s.n_all;
-    const unsigned g = (unsigned)std::max<int64_t>(std::min<int64_t>((items + 3) / 4, (int64_t)cu * 64),
-                                                   (n_rx + 255) / 256);
-    hipLaunchKernelGGL(k_vis_rx, dim3(g), dim3(256), bytes, st, s, k, min_seg, samp, cnt, rx, n_rx, U, los, W, lds);
+    const int64_t waves = (int64_t)n_rx * ((int64_t)s.n_all * std::max(k * k, 2 * k) / 64 + 1);
+    hipLaunchKernelGGL(k_vis_rx, dim3(resident_blocks(waves, bytes, lds_max, cu)), dim3(256), bytes, st, s, k, min_seg,
+                       samp, cnt, rx, n_rx, U, los, W, lds);
 }
 
 static CandGraph graph_of(const SceneDev &s, const uint32_t *V, const uint32_t *B, const uint32_t *U, int W,
@@ -537,12 +758,14 @@ static CandGraph graph_of(const SceneDev &s, const uint32_t *V, const uint32_t *
 }
 
 void launch_cand_count(const SceneDev &s, const uint32_t *V, const uint32_t *B, const uint32_t *U, int W, int n_rx,
-                       int maxo, int edge_last, int64_t *cnt, int64_t *sums, int cu, hipStream_t st)
+                       int maxo, int edge_last, int64_t *cnt, int64_t *sums, int *last, int cu, hipStream_t st)
 {
     const CandGraph G = graph_of(s, V, B, U, W, maxo, edge_last);
     const int64_t items = (int64_t)n_rx * s.n_all;
-    hipLaunchKernelGGL(k_cand_count, dim3((unsigned)std::min<int64_t>(items, (int64_t)cu * 32)), dim3(kCandBlock), 0,
-                       st, G, n_rx, cnt);
+    hipLaunchKernelGGL(k_cand_last, dim3((unsigned)std::min<int64_t>((items + 255) / 256, (int64_t)cu * 8)), dim3(256),
+                       0, st, G, n_rx, last);
+    hipLaunchKernelGGL(k_cand_count, dim3((unsigned)std::min<int64_t>((items + 3) / 4, (int64_t)cu * 8)), dim3(256), 0,
+                       st, G, n_rx, last, cnt);
     // exclusive scan over (receiver, order, first object)
     const int64_t n = items * maxo;
     const int64_t nb = (n + 256 * kScanPer - 1) / (256 * kScanPer);
@@ -552,13 +775,13 @@ void launch_cand_count(const SceneDev &s, const uint32_t *V, const uint32_t *B, 
 }
 
 void launch_cand_fill(const SceneDev &s, const uint32_t *V, const uint32_t *B, const uint32_t *U, int W, int n_rx,
-                      int maxo, int edge_last, const int64_t *off, int64_t cap, int32_t *rx_index, int32_t *order,
-                      int32_t *prim, int cu, hipStream_t st)
+                      int maxo, int edge_last, const int64_t *off, const int *last, int64_t cap, int32_t *rx_index,
+                      int32_t *order, int32_t *prim, int cu, hipStream_t st)
 {
     const CandGraph G = graph_of(s, V, B, U, W, maxo, edge_last);
     const int64_t items = (int64_t)n_rx * s.n_all;
-    hipLaunchKernelGGL(k_cand_fill, dim3((unsigned)std::min<int64_t>(items, (int64_t)cu * 32)), dim3(kCandBlock), 0,
-                       st, G, n_rx, off, cap, rx_index, order, prim);
+    hipLaunchKernelGGL(k_cand_fill, dim3((unsigned)std::min<int64_t>(items, (int64_t)cu * 32), maxo >= 3 ? kFillParts : 1),
+                       dim3(kCandBlock), 0, st, G, n_rx, last, off, cap, rx_index, order, prim);
 }
 
 }  // namespace mpt

@@ -21,9 +21,11 @@ __device__ __forceinline__ double vdot(const double *a, const double *b)
 __device__ __forceinline__ bool vis_plane(const double *r, const double P[3], const double d[3], double tmin, double tmax)
 {
 #pragma clang fp contract(off)
-    const double den = vdot(r, d);
-    if (den == 0.0) return false;
-    const double t = (r[3] - vdot(r, P)) / den;
+    const double den = vdot(r, d), num = r[3] - vdot(r, P);
+    // t = num / den lies in (tmin, tmax), inside (0, 1), only if both have one
+    // sign and |num| < |den|: the division is left to the few that do
+    if (den == 0.0 || num == 0.0 || (num > 0.0) != (den > 0.0) || !(fabs(num) < fabs(den))) return false;
+    const double t = num / den;
     if (!(t > tmin && t < tmax)) return false;
     double w[3];
     for (int i = 0; i < 3; i++) w[i] = (P[i] + t * d[i]) - r[4 + i];
@@ -213,25 +215,148 @@ __device__ __forceinline__ bool leaves_obj(const SceneDev &s, int g, const doubl
     return true;
 }
 
-// The segment P -> Q crosses a facet or paraboloid patch other than gi, gj
-// strictly inside (more than min_seg from its ends).  prec / qrec: the
-// plane and quadric records (possibly staged in LDS).
-__device__ __forceinline__ bool seg_blocked(const SceneDev &s, const double *prec, const double *qrec,
-                                            const double P[3], const double Q[3], int gi, int gj, double min_seg)
+// ------------------------------------------------------------------ culling
+// Bounding box (lo, hi; FP32, expanded past every rounding error of the tests
+// above) of the points at which a segment can be blocked by a facet or patch:
+// the rectangle, or the ball about a paraboloid of revolution's vertex that
+// holds its patch.  A record whose region is not that (sides that are not
+// perpendicular or have no length, another quadric) gets the whole space.
+__device__ inline void occluder_box(int t, const double *r, float *box)
+{
+    double lo[3], hi[3], big = 0.0;
+    bool ok;
+    double m;
+    if (t == TP) {
+        const double *n = r, *o = r + 4, *u = r + 7, *v = r + 10;
+        const double lu = sqrt(vdot(u, u)), lv = sqrt(vdot(v, v)), shift = r[3] - vdot(n, o);
+        ok = lu > 1e-9 && lv > 1e-9 && fabs(vdot(u, v)) <= 1e-9 * lu * lv && fabs(vdot(n, u)) <= 1e-9 * lu &&
+             fabs(vdot(n, v)) <= 1e-9 * lv;
+        for (int i = 0; i < 3; i++) {
+            const double c = o[i] + shift * n[i];
+            lo[i] = c + fmin(u[i], 0.0) + fmin(v[i], 0.0);
+            hi[i] = c + fmax(u[i], 0.0) + fmax(v[i], 0.0);
+            big = fmax(big, fmax(fabs(lo[i]), fabs(hi[i])));
+        }
+        m = 1e-5 * (1.0 + big);
+    } else {
+        const double kap = revolution_kappa(r), h = kap * r[16] * r[16];
+        const double R = sqrt(r[16] * r[16] + h * h);
+        ok = kap > 0.0 && r[16] >= 0.0;
+        for (int i = 0; i < 3; i++) {
+            lo[i] = r[i] - R;
+            hi[i] = r[i] + R;
+            big = fmax(big, fmax(fabs(lo[i]), fabs(hi[i])));
+        }
+        m = 1e-3 * (1.0 + big);
+    }
+    ok = ok && big < 1e30;
+    for (int i = 0; i < 3; i++) {
+        box[i] = ok ? (float)(lo[i] - m) : -__builtin_huge_valf();
+        box[4 + i] = ok ? (float)(hi[i] + m) : __builtin_huge_valf();
+    }
+    box[3] = box[7] = 0.0f;
+}
+
+// The space the segments between two boxes (lo[3], hi[3]) can pass through:
+// the box around both, and their extent along two directions across the line
+// between their centres (one level, one in the vertical plane through it).
+struct Shaft {
+    float lo[3], hi[3], a[2][3], l[2], h[2];
+};
+
+__device__ __forceinline__ void box_extent(const float *lo, const float *hi, const float *a, float &l, float &h)
+{
+    float c = 0.0f, e = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        c += 0.5f * (lo[i] + hi[i]) * a[i];
+        e += 0.5f * (hi[i] - lo[i]) * fabsf(a[i]);
+    }
+    l = c - e;
+    h = c + e;
+}
+
+__device__ __forceinline__ Shaft shaft_between(const float *alo, const float *ahi, const float *blo, const float *bhi)
+{
+    Shaft s;
+    float d[3], big = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        s.lo[i] = fminf(alo[i], blo[i]);
+        s.hi[i] = fmaxf(ahi[i], bhi[i]);
+        d[i] = 0.5f * (blo[i] + bhi[i]) - 0.5f * (alo[i] + ahi[i]);
+        big = fmaxf(big, fmaxf(fabsf(s.lo[i]), fabsf(s.hi[i])));
+    }
+    // FP32 rounding of coordinates and projections, with room to spare
+    const float m = 1e-4f + 1e-5f * big, xy = d[0] * d[0] + d[1] * d[1];
+    const float dir[2][3] = {{-d[1], d[0], 0.0f}, {-d[0] * d[2], -d[1] * d[2], xy}};
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const float n2 = dir[q][0] * dir[q][0] + dir[q][1] * dir[q][1] + dir[q][2] * dir[q][2];
+        const float in = (n2 > 1e-12f && n2 < 1e30f) ? rsqrtf(n2) : 0.0f;  // no direction: no test
+#pragma unroll
+        for (int i = 0; i < 3; i++) s.a[q][i] = dir[q][i] * in;
+        float l0, h0, l1, h1;
+        box_extent(alo, ahi, s.a[q], l0, h0);
+        box_extent(blo, bhi, s.a[q], l1, h1);
+        s.l[q] = fminf(l0, l1) - m;
+        s.h[q] = fmaxf(h0, h1) + m;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        s.lo[i] -= m;
+        s.hi[i] += m;
+    }
+    return s;
+}
+
+// True when nothing in the box can block a segment of the shaft (any
+// comparison with a NaN or infinite bound keeps the box).
+__device__ __forceinline__ bool outside_shaft(const Shaft &s, const float *box)
+{
+    bool out = false;
+#pragma unroll
+    for (int i = 0; i < 3; i++) out = out || box[i] > s.hi[i] || box[4 + i] < s.lo[i];
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        float l, h;
+        box_extent(box, box + 4, s.a[q], l, h);
+        out = out || l > s.h[q] || h < s.l[q];
+    }
+    return out;
+}
+
+// A segment P -> Q and the open range of its parameter in which it can be
+// blocked; ok: it has a length.
+struct Seg {
+    double P[3], d[3], tmin, tmax;
+    bool ok;
+};
+
+__device__ __forceinline__ Seg segment(const double *P, const double *Q, double min_seg)
 {
 #pragma clang fp contract(off)
-    const double d[3] = {Q[0] - P[0], Q[1] - P[1], Q[2] - P[2]};
-    const double L = sqrt(vdot(d, d));
-    if (!(L > 0.0)) return true;
-    const double tmin = min_seg / L, tmax = 1.0 - tmin;
-    for (int j = 0; j < s.n_pl; j++)
-        if (j != gi && j != gj && vis_plane(prec + (size_t)j * kRec, P, d, tmin, tmax)) return true;
-    const int nq = s.n_pl_ln_q - s.n_pl_ln;
-    for (int j = 0; j < nq; j++) {
-        const int gid = s.n_pl_ln + j;
-        if (gid != gi && gid != gj && vis_quadric(qrec + (size_t)j * kRec, P, d, tmin, tmax)) return true;
+    Seg g;
+    for (int i = 0; i < 3; i++) {
+        g.P[i] = P[i];
+        g.d[i] = Q[i] - P[i];
     }
-    return false;
+    const double L = sqrt(vdot(g.d, g.d));
+    g.ok = L > 0.0;
+    g.tmin = min_seg / L;
+    g.tmax = 1.0 - g.tmin;
+    return g;
+}
+
+// Does occluder o (a facet, then the patches) block the segment?  gi, gj: the
+// objects it starts and ends on.  prec / qrec: the plane and quadric records
+// (possibly staged in LDS).
+__device__ __forceinline__ bool blocks(const SceneDev &s, const double *prec, const double *qrec, int o, const Seg &g,
+                                       int gi, int gj)
+{
+    if (o < s.n_pl) return o != gi && o != gj && vis_plane(prec + (size_t)o * kRec, g.P, g.d, g.tmin, g.tmax);
+    const int q = o - s.n_pl, gid = s.n_pl_ln + q;
+    return gid != gi && gid != gj && vis_quadric(qrec + (size_t)q * kRec, g.P, g.d, g.tmin, g.tmax);
 }
 
 }  // namespace mpt

@@ -21,6 +21,7 @@ struct SceneDev {
     double lo[3], hi[3];    // scene box (random starts)
     const double *wedge;    // [n_pl_ln - n_pl][7] wedges of the straight edges, or null
     const double *side;     // [n_pl] free side of each facet (+1, -1, 0), or null
+    const float *occ;       // [n_pl + quadrics][8] bounding boxes of the facets and patches (lo, hi)
 };
 
 struct BatchDev {
@@ -83,6 +84,7 @@ struct KParams {
 
 void launch_pack(const double *raw, const double *refr, const SceneDev &s, int n_pl, int n_ln, int n_q, int n_c,
                  hipStream_t st);
+void launch_occluders(const SceneDev &s, hipStream_t st);
 void launch_zero(int *p, int n, hipStream_t st);
 int bin_key_count();
 // rows (or null): the list of the solves with a paraboloid or a circle,
@@ -102,17 +104,21 @@ void launch_polish(const KParams &kp, bool refr, int grid, int block, hipStream_
 void launch_start(int mode, int form, const KParams &kp, hipStream_t st);
 void launch_learned_begin(int mode, int form, const KParams &kp, const int *list, const int *count, hipStream_t st);
 void launch_finish(int form, bool refr, const KParams &kp, int cu, hipStream_t st);
-void launch_samples(const SceneDev &s, int k, double *samp, int *cnt, hipStream_t st);
-void launch_visibility(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt, uint32_t *V,
-                       uint32_t *B, int W, size_t lds_max, int cu, hipStream_t st);
+// Sample points of every object ([n_all][k k + 2 k][3]), their counts and
+// boxes ([n_all][8], as occ); clears the two bit arrays.
+void launch_samples(const SceneDev &s, int k, double *samp, int *cnt, float *box, uint32_t *z0, int64_t n0,
+                    uint32_t *z1, int64_t n1, hipStream_t st);
+void launch_visibility(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt, const float *box,
+                       uint32_t *V, uint32_t *B, int W, size_t lds_max, int cu, hipStream_t st);
 void launch_visibility_rx(const SceneDev &s, int k, double min_seg, const double *samp, const int *cnt,
                           const double *rx, int n_rx, uint32_t *U, uint8_t *los, int W, size_t lds_max, int cu,
                           hipStream_t st);
+// last: [n_rx][n_all] last objects a path through each object can end with
 void launch_cand_count(const SceneDev &s, const uint32_t *V, const uint32_t *B, const uint32_t *U, int W, int n_rx,
-                       int maxo, int edge_last, int64_t *cnt, int64_t *sums, int cu, hipStream_t st);
+                       int maxo, int edge_last, int64_t *cnt, int64_t *sums, int *last, int cu, hipStream_t st);
 void launch_cand_fill(const SceneDev &s, const uint32_t *V, const uint32_t *B, const uint32_t *U, int W, int n_rx,
-                      int maxo, int edge_last, const int64_t *off, int64_t cap, int32_t *rx_index, int32_t *order,
-                      int32_t *prim, int cu, hipStream_t st);
+                      int maxo, int edge_last, const int64_t *off, const int *last, int64_t cap, int32_t *rx_index,
+                      int32_t *order, int32_t *prim, int cu, hipStream_t st);
 void launch_visible(const SceneDev &s, const BatchDev &b, const OutDevC &in, const uint8_t *acc, double min_seg,
                     uint8_t *vis, int *count, int *list, size_t lds_max, int cu, hipStream_t st);
 void launch_accept(const SceneDev &s, const BatchDev &b, const OutDevC &in, double tau_res, double min_seg,

@@ -472,9 +472,9 @@ mpt_status mpt_gemm_bf16_check(mpt_ctx *ctx, int32_t M, int32_t N, int32_t K, co
                                int32_t splits);
 /* Predicted points [n][MPT_ROW] FP64 world frame (device, caller-owned). */
 mpt_status mpt_mlp_predict(mpt_ctx *ctx, const mpt_batch_desc *batch, double *x_out);
-/* The same prediction through the layer-by-layer GEMM kernels training
- * uses (activations in device memory) instead of the fused kernel; for
- * checking the fused kernel. */
+/* The same prediction through layer-by-layer GEMM kernels (activations in
+ * device memory) instead of the fused kernel; for checking the fused
+ * kernel. */
 mpt_status mpt_mlp_predict_unfused(mpt_ctx *ctx, const mpt_batch_desc *batch, double *x_out);
 /* Serialise / restore the network (FP32 master weights and Adam state).
  * mpt_mlp_save with blob = NULL stores the needed size in *bytes. */

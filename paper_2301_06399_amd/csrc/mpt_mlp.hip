@@ -6,9 +6,12 @@
 //   hidden layers; BF16 weights and activations, FP32 accumulation on the
 //   matrix cores (v_mfma_f32_32x32x16_bf16), FP32 master weights + Adam.
 //
-// Kernels: k_features (per path), k_gemm (LDS-tiled MFMA GEMM with bias /
-// GELU / GELU' epilogues and split-K partials), k_reduce_splits, k_colsum
-// (bias gradients), k_loss (masked MSE and its gradient), k_adam, k_decode.
+// Kernels: k_mlp_fused (inference), k_train_forward (features to loss, one
+// block per 32 rows), k_train_backward (loss gradient down to the first layer),
+// k_train_weights (every weight and bias gradient, split over the rows),
+// k_reduce_splits, k_adam; k_features, k_gemm, k_decode (the layer-by-layer
+// forward that checks k_mlp_fused, and the GEMM check); k_gemm_f32 and
+// k_colsum_f32, k_loss_* (the FP32 gradient check).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -56,6 +59,36 @@ __host__ __device__ constexpr long long frag_of(size_t i)
     const size_t u = off / K, k = off % K, S = K / 16;
     const size_t blk = u / 64, half = (u % 64) / 32, lane = u % 32 + 32 * ((k % 16) / 8);
     return (long long)(base + (((blk * S + k / 16) * 2 + half) * 64 + lane) * 8 + k % 8);
+}
+
+// The backward pass reads the transposed matrices W2^T, W3^T (rows = inputs,
+// K = HID outputs) and W4^T (K = 16) in the same order, after the copy above.
+constexpr size_t NFRAGT = 2 * (size_t)HID * HID + (size_t)F_OUTP * HID;
+__host__ __device__ constexpr long long frag_t_of(size_t i)
+{
+    constexpr size_t w2 = (size_t)HID * F_IN + HID, w3 = w2 + (size_t)HID * HID + HID,
+                     w4 = w3 + (size_t)HID * HID + HID;
+    size_t off, S, base;
+    if (i >= w2 && i < w2 + (size_t)HID * HID) {
+        off = i - w2, S = HID / 16, base = 0;
+    } else if (i >= w3 && i < w3 + (size_t)HID * HID) {
+        off = i - w3, S = HID / 16, base = (size_t)HID * HID;
+    } else if (i >= w4 && i < w4 + (size_t)F_OUTP * HID) {
+        off = i - w4, S = 1, base = 2 * (size_t)HID * HID;
+    } else {
+        return -1;
+    }
+    const size_t k = off / HID, u = off % HID;  // output, input
+    const size_t blk = u / 64, half = (u % 64) / 32, lane = u % 32 + 32 * ((k % 16) / 8);
+    return (long long)(NFRAG + base + (((blk * S + k / 16) * 2 + half) * 64 + lane) * 8 + k % 8);
+}
+
+// Both fragment copies of one weight.
+__device__ __forceinline__ void put_frags(bf16 *wf, size_t i, bf16 h)
+{
+    const long long j = frag_of(i), t = frag_t_of(i);
+    if (j >= 0) wf[j] = h;
+    if (t >= 0) wf[t] = h;
 }
 
 // GELU in its erf form, with erf from Abramowitz & Stegun 7.1.26 (Hastings'
@@ -198,10 +231,8 @@ enum : int { EPI_BIAS_GELU = 0, EPI_BIAS = 1, EPI_DGELU = 2, EPI_F32 = 3 };
 
 struct Epi {
     const float *bias;   // [N]
-    float *zout;         // [M][ldc] pre-activation (EPI_BIAS_GELU, optional)
-    bf16 *hout;          // [M][ldc] bf16 output (EPI_BIAS_GELU, EPI_DGELU)
+    bf16 *hout;          // [M][ldc] bf16 output (EPI_BIAS_GELU)
     float *fout;         // [splits][M][ldc] fp32 output (EPI_BIAS, EPI_F32)
-    const float *zin;    // [M][ldc] pre-activation to differentiate (EPI_DGELU)
     int ldc;
 };
 
@@ -265,13 +296,9 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const bf16 *_
         const float x = acc[v];
         const size_t o = (size_t)row * e.ldc + col;
         if (EPI == EPI_BIAS_GELU) {
-            const float z = x + e.bias[col];
-            if (e.zout) e.zout[o] = z;
-            e.hout[o] = f2bf(gelu(z));
+            e.hout[o] = f2bf(gelu(x + e.bias[col]));
         } else if (EPI == EPI_BIAS) {
             e.fout[o] = x + e.bias[col];
-        } else if (EPI == EPI_DGELU) {
-            e.hout[o] = f2bf(x * gelu_d(e.zin[o]));
         } else {
             e.fout[(size_t)blockIdx.z * M * e.ldc + o] = x;
         }
@@ -286,22 +313,6 @@ __global__ void k_reduce_splits(const float *__restrict__ part, int splits, size
     float s = 0.0f;
     for (int q = 0; q < splits; q++) s += part[(size_t)q * n + i];
     out[i] = s;
-}
-
-// column sums of a [M][N] bf16 matrix (bias gradients), one block per column
-__global__ void k_colsum(const bf16 *__restrict__ X, int M, int N, int ld, float *__restrict__ out)
-{
-    __shared__ float red[256];
-    const int col = blockIdx.x;
-    float s = 0.0f;
-    for (int r = threadIdx.x; r < M; r += blockDim.x) s += bf2f(X[(size_t)r * ld + col]);
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[col] = red[0];
 }
 
 // ------------------------------------------------------------------ FP32 check mode
@@ -436,10 +447,10 @@ __global__ void k_loss_partial(SceneDev s, BatchDev b, const int *__restrict__ r
     }
 }
 
-// total loss and dY = 2 diff / count (bf16)
+// total loss and dY = 2 diff / count
 __global__ void k_loss_final(const float *__restrict__ part, const int *__restrict__ cnt_part, int nblk,
-                             const float *__restrict__ diff, int nrows, bf16 *__restrict__ dY, float *__restrict__ loss,
-                             float *__restrict__ dYf = nullptr)
+                             const float *__restrict__ diff, int nrows, float *__restrict__ loss,
+                             float *__restrict__ dYf)
 {
     __shared__ float tot_s;
     __shared__ int tot_c;
@@ -455,8 +466,7 @@ __global__ void k_loss_final(const float *__restrict__ part, const int *__restri
     // every block sums the few partials itself and scales its own slice
     const float sc = tot_c ? 2.0f / tot_c : 0.0f;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nrows * F_OUTP; i += gridDim.x * blockDim.x) {
-        if (dY) dY[i] = f2bf(sc * diff[i]);
-        if (dYf) dYf[i] = sc * diff[i];
+        dYf[i] = sc * diff[i];
     }
 }
 
@@ -477,8 +487,7 @@ __global__ void k_adam(float *__restrict__ w, float *__restrict__ m, float *__re
     if (wb) {
         const bf16 h = f2bf(wi);
         wb[i] = h;
-        const long long j = frag_of((size_t)i);
-        if (j >= 0) wf[j] = h;
+        put_frags(wf, (size_t)i, h);
     }
 }
 
@@ -488,8 +497,7 @@ __global__ void k_to_bf16(const float *__restrict__ w, bf16 *__restrict__ wb, bf
     if (i >= n) return;
     const bf16 h = f2bf(w[i]);
     wb[i] = h;
-    const long long j = frag_of((size_t)i);
-    if (j >= 0) wf[j] = h;
+    put_frags(wf, (size_t)i, h);
 }
 
 // ------------------------------------------------------------------ decode
@@ -727,9 +735,11 @@ struct MlpState {
     bf16 *wf = nullptr;  // the hidden layers' bf16 weights in fragment order
     int64_t step = 0;
     uint64_t seed = 0;
-    // activation workspace for up to cap rows
+    // activation workspace for up to cap rows (parts of one allocation)
     size_t cap = 0;
-    bf16 *X = nullptr, *H1 = nullptr, *H2 = nullptr, *H3 = nullptr, *dY = nullptr, *dA = nullptr, *dB = nullptr;
+    unsigned char *ws = nullptr;
+    bf16 *X = nullptr, *H1 = nullptr, *H2 = nullptr, *H3 = nullptr, *dY = nullptr, *dZ1 = nullptr, *dZ2 = nullptr,
+         *dZ3 = nullptr;
     float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr, *Y = nullptr, *diff = nullptr, *part = nullptr,
           *lpart = nullptr;
     int *lcnt = nullptr;
@@ -740,15 +750,346 @@ struct MlpState {
           *dBf = nullptr;
 };
 
+// ------------------------------------------------------------------ training
+// The minibatch in tiles of TR rows, one block of four waves each.  A layer is
+// computed transposed as in k_mlp_fused (weights = A operand, read from L2 in
+// fragment order, activations = B operand in LDS); wave w holds units 64 w ..
+// +64 of the tile's 32 rows.  Forward and backward keep their activations in
+// LDS from layer to layer and store what the weight gradients read, so a
+// gradient takes four launches: with a launch per layer, GEMM, column sum and
+// reduction (22, each 5 to 23 us for 4096 rows, their operands loaded two bytes
+// at a time) it took 333 us, now 122 (kernels 27 + 19 + 15 + 7).
+constexpr int TR = 32;
+
+// acc[mt][v]: unit 64 wave + 32 mt + 8 (v / 4) + 4 (lane / 32) + v % 4 of row
+// lane % 32, over K inputs of the tile in LDS (row stride ILD).
+template <int K>
+__device__ __forceinline__ void train_layer(const bf16 *in, const bf16 *__restrict__ Wf, int wave, int lane,
+                                            float16_t acc[2])
+{
+    constexpr int S = K / 16, D = PF < S ? PF : S;
+    const int blk = __builtin_amdgcn_readfirstlane(wave & 3);
+    const bf16x8_t *wf = reinterpret_cast<const bf16x8_t *>(Wf) + (size_t)blk * S * 2 * 64 + lane;
+    const bf16 *ip = in + (lane & 31) * ILD + 8 * (lane >> 5);
+#pragma unroll
+    for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[mt][v] = 0.0f;
+    bf16x8_t a0[D], a1[D];
+#pragma unroll
+    for (int t = 0; t < D; t++) {
+        a0[t] = wf[t * 128];
+        a1[t] = wf[t * 128 + 64];
+    }
+#pragma unroll
+    for (int t = 0; t < S; t++) {
+        const bf16x8_t x0 = a0[t % D], x1 = a1[t % D];
+        if (t + D < S) {
+            a0[t % D] = wf[(t + D) * 128];
+            a1[t % D] = wf[(t + D) * 128 + 64];
+        }
+        const bf16x8_t b = *reinterpret_cast<const bf16x8_t *>(ip + 16 * t);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, b, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, b, acc[1], 0, 0, 0);
+    }
+}
+
+__device__ __forceinline__ uint2 pack4(float a, float b, float c, float d)
+{
+    return make_uint2((uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16), (uint32_t)f2bf(c) | ((uint32_t)f2bf(d) << 16));
+}
+
+// Activations of a hidden layer: h = GELU(acc + bias) to LDS and global memory,
+// the derivative to gd.
+__device__ __forceinline__ void train_activate(const float16_t acc[2], const float *__restrict__ bias, bf16 *out,
+                                               bf16 *__restrict__ H, float *__restrict__ gd, int row0, int nrows,
+                                               int wave, int lane)
+{
+    const int li = lane & 31, r = row0 + li;
+#pragma unroll
+    for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+            const int u = 64 * wave + 32 * mt + 8 * g + 4 * (lane >> 5);
+            const float4 bc = *reinterpret_cast<const float4 *>(bias + u);
+            float h[4], d[4];
+            gelu_both(acc[mt][4 * g + 0] + bc.x, h[0], d[0]);
+            gelu_both(acc[mt][4 * g + 1] + bc.y, h[1], d[1]);
+            gelu_both(acc[mt][4 * g + 2] + bc.z, h[2], d[2]);
+            gelu_both(acc[mt][4 * g + 3] + bc.w, h[3], d[3]);
+            const uint2 pk = pack4(h[0], h[1], h[2], h[3]);
+            *reinterpret_cast<uint2 *>(out + li * ILD + u) = pk;
+            if (r < nrows) {
+                *reinterpret_cast<uint2 *>(H + (size_t)r * HID + u) = pk;
+                *reinterpret_cast<float4 *>(gd + (size_t)r * HID + u) = make_float4(d[0], d[1], d[2], d[3]);
+            }
+        }
+}
+
+struct TrainBufs {
+    bf16 *X, *H1, *H2, *H3, *dY, *dZ1, *dZ2, *dZ3;  // [rows][F_IN], [rows][HID], dY [rows][F_OUTP]
+    float *G1, *G2, *G3, *diff, *part;              // GELU', [rows][F_OUTP] Y - target, loss per tile
+    int *cnt;                                       // coordinates per tile
+};
+
+__global__ void __launch_bounds__(256) k_train_forward(SceneDev s, BatchDev b, const int *__restrict__ rows, int nrows,
+                                                       const double *__restrict__ target,
+                                                       const uint8_t *__restrict__ use, const bf16 *__restrict__ wb,
+                                                       const bf16 *__restrict__ wf, const float *__restrict__ w,
+                                                       TrainBufs t)
+{
+    __shared__ __align__(16) bf16 bufA[TR * ILD], bufB[TR * ILD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row0 = blockIdx.x * TR;
+    {
+        // features, eight threads per row: thread q < 5 writes slot q, thread 5
+        // the receiver and the zero padding
+        const int pr = tid >> 3, q = tid & 7, r = row0 + pr;
+        const int i = r < nrows ? (rows ? rows[r] : r) : -1;
+        bf16 *dst = bufA + pr * ILD;
+        double rx[3] = {0.0, 0.0, 0.0};
+        const double L = i >= 0 ? row_frame(s, b, i, rx) : 1.0;
+        if (q < kMaxN) {
+            float g[SLOT];
+            slot_features(s, b, i < 0 ? 0 : i, q, i < 0 ? 0 : b.order[i], L, g);
+            for (int j = 0; j < SLOT; j++) dst[6 + SLOT * q + j] = f2bf(g[j]);
+        } else if (q == kMaxN) {
+            const double is = 1.0 / L;
+            for (int c = 0; c < 3; c++) {
+                dst[c] = f2bf(i >= 0 ? (float)((rx[c] - s.tx[c]) * is) : 0.0f);
+                dst[3 + c] = f2bf(0.0f);
+            }
+            for (int j = 6 + SLOT * kMaxN; j < F_IN; j++) dst[j] = f2bf(0.0f);
+        }
+    }
+    __syncthreads();
+    for (int q = tid; q < TR * F_IN / 8; q += 256) {
+        const int r = q / (F_IN / 8), c = q % (F_IN / 8) * 8;
+        if (row0 + r < nrows)
+            *reinterpret_cast<uint4 *>(t.X + (size_t)(row0 + r) * F_IN + c) =
+                *reinterpret_cast<const uint4 *>(bufA + r * ILD + c);
+    }
+    float16_t acc[2];
+    train_layer<F_IN>(bufA, wf, wave, lane, acc);
+    train_activate(acc, w + OB1, bufB, t.H1, t.G1, row0, nrows, wave, lane);
+    __syncthreads();
+    train_layer<HID>(bufB, wf + (size_t)HID * F_IN, wave, lane, acc);
+    train_activate(acc, w + OB2, bufA, t.H2, t.G2, row0, nrows, wave, lane);
+    __syncthreads();
+    train_layer<HID>(bufA, wf + (size_t)HID * F_IN + (size_t)HID * HID, wave, lane, acc);
+    train_activate(acc, w + OB3, bufB, t.H3, t.G3, row0, nrows, wave, lane);
+    __syncthreads();
+    if (wave) return;
+    // output layer (units 0..15) and the masked squared error of the tile
+    float16_t y;
+#pragma unroll
+    for (int v = 0; v < 16; v++) y[v] = 0.0f;
+    const int li = lane & 31, kq = 8 * (lane >> 5);
+    const bf16 *wp = wb + OW4 + (size_t)(li & 15) * HID + kq;
+    const bf16 *ip = bufB + li * ILD + kq;
+#pragma unroll 4
+    for (int k0 = 0; k0 < HID; k0 += 16) {
+        bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(wp + k0);
+        if (li >= F_OUTP) a = bf16x8_t{};
+        y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, *reinterpret_cast<const bf16x8_t *>(ip + k0), y, 0, 0, 0);
+    }
+    const int r = row0 + li;
+    float sum = 0.0f;
+    int cnt = 0;
+    if (r < nrows) {
+        const int i = rows ? rows[r] : r;
+        const int ord = b.order[i];
+        const bool u = (!use || use[i]) && ord >= 1 && ord <= kMaxN;
+        const int ri = b.rx_index[i];
+        double L = 1.0;
+        if (ri >= 0 && ri < b.n_rx) {
+            double d2 = 0.0;
+            for (int c = 0; c < 3; c++) {
+                const double d = b.rx[3 * (size_t)ri + c] - s.tx[c];
+                d2 += d * d;
+            }
+            if (d2 > 0.0 && isfinite(d2)) L = sqrt(d2);
+        }
+#pragma unroll
+        for (int v = 0; v < 8; v++) {
+            const int j = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            float dd = 0.0f;
+            if (u && j < 3 * ord) {
+                const double tg = (target[(size_t)i * kRow + j] - s.tx[j % 3]) / L;
+                dd = (y[v] + w[OB4 + j]) - (float)tg;
+                if (!isfinite(dd)) dd = 0.0f;
+                sum += dd * dd;
+                cnt++;
+            }
+            t.diff[(size_t)r * F_OUTP + j] = dd;
+        }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        sum += __shfl_xor(sum, d);
+        cnt += __shfl_xor(cnt, d);
+    }
+    if (lane == 0) {
+        t.part[blockIdx.x] = sum;
+        t.cnt[blockIdx.x] = cnt;
+    }
+}
+
+// dZ = (W^T dZ_next) GELU'(Z), BF16, to LDS and global memory.
+__device__ __forceinline__ void train_derive(const float16_t acc[2], const float *__restrict__ gd, bf16 *out,
+                                             bf16 *__restrict__ dZ, int row0, int nrows, int wave, int lane)
+{
+    const int li = lane & 31, r = row0 + li;
+#pragma unroll
+    for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+            const int u = 64 * wave + 32 * mt + 8 * g + 4 * (lane >> 5);
+            float4 d = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (r < nrows) d = *reinterpret_cast<const float4 *>(gd + (size_t)r * HID + u);
+            const uint2 pk = pack4(acc[mt][4 * g] * d.x, acc[mt][4 * g + 1] * d.y, acc[mt][4 * g + 2] * d.z,
+                                   acc[mt][4 * g + 3] * d.w);
+            *reinterpret_cast<uint2 *>(out + li * ILD + u) = pk;
+            if (r < nrows) *reinterpret_cast<uint2 *>(dZ + (size_t)r * HID + u) = pk;
+        }
+}
+
+__global__ void __launch_bounds__(256) k_train_backward(int nrows, int ntiles, const bf16 *__restrict__ wf, TrainBufs t,
+                                                        float *__restrict__ loss)
+{
+    __shared__ __align__(16) bf16 bufA[TR * ILD], bufB[TR * ILD];
+    __shared__ float rs[256];
+    __shared__ int rc[256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row0 = blockIdx.x * TR;
+    // the tiles' losses and counts, in a fixed order
+    float sum = 0.0f;
+    int cnt = 0;
+    for (int q = tid; q < ntiles; q += 256) sum += t.part[q], cnt += t.cnt[q];
+    rs[tid] = sum;
+    rc[tid] = cnt;
+    __syncthreads();
+    for (int d = 128; d > 0; d >>= 1) {
+        if (tid < d) rs[tid] += rs[tid + d], rc[tid] += rc[tid + d];
+        __syncthreads();
+    }
+    cnt = rc[0];
+    if (loss && blockIdx.x == 0 && tid == 0) *loss = cnt ? rs[0] / cnt : 0.0f;
+    const float sc = cnt ? 2.0f / cnt : 0.0f;
+    // dY = 2 diff / count
+    for (int q = tid; q < TR * F_OUTP; q += 256) {
+        const int r = row0 + q / F_OUTP;
+        bf16 h = 0;
+        if (r < nrows) {
+            h = f2bf(sc * t.diff[(size_t)r * F_OUTP + q % F_OUTP]);
+            t.dY[(size_t)r * F_OUTP + q % F_OUTP] = h;
+        }
+        bufA[q / F_OUTP * ILD + q % F_OUTP] = h;
+    }
+    __syncthreads();
+    const bf16 *wt = wf + NFRAG;
+    float16_t acc[2];
+    train_layer<F_OUTP>(bufA, wt + 2 * (size_t)HID * HID, wave, lane, acc);
+    train_derive(acc, t.G3, bufB, t.dZ3, row0, nrows, wave, lane);
+    __syncthreads();
+    train_layer<HID>(bufB, wt + (size_t)HID * HID, wave, lane, acc);
+    train_derive(acc, t.G2, bufA, t.dZ2, row0, nrows, wave, lane);
+    __syncthreads();
+    train_layer<HID>(bufA, wt, wave, lane, acc);
+    train_derive(acc, t.G1, bufB, t.dZ1, row0, nrows, wave, lane);
+}
+
+// Weight gradients dW[o][i] = sum over rows of dZ[r][o] X[r][i] and bias
+// gradients (column sums of dZ), 64 x 64 tiles of the four layers, the rows
+// split over blockIdx.y; partial sums in the parameters' layout.  The operands
+// are row-major and the matrix cores want consecutive rows of one column, so a
+// step's 64 rows are transposed on their way to LDS.  Bound: the latency of a
+// step (load, transpose, 8 matrix instructions per wave) with two or three
+// blocks per CU.
+constexpr int WT_TILES = 16 + 16 + 8 + 4;  // W3, W2, W1, W4
+constexpr int WK = 64;                     // rows per step
+
+__global__ void __launch_bounds__(256) k_train_weights(int nrows, int rows_per, TrainBufs t, float *__restrict__ part)
+{
+    __shared__ __align__(16) bf16 As[64][WK + 8], Bs[64][WK + 8];
+    __shared__ float cs[32][64 + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int tile = blockIdx.x;
+    const bf16 *A, *B;
+    int lda = HID, M = HID, ldb = HID, N = HID;
+    size_t ow, ob;
+    if (tile < 16) {
+        A = t.dZ3, B = t.H2, ow = OW3, ob = OB3;
+    } else if (tile < 32) {
+        tile -= 16, A = t.dZ2, B = t.H1, ow = OW2, ob = OB2;
+    } else if (tile < 40) {
+        tile -= 32, A = t.dZ1, B = t.X, ldb = N = F_IN, ow = OW1, ob = OB1;
+    } else {
+        tile -= 40, A = t.dY, lda = M = F_OUTP, B = t.H3, ow = OW4, ob = OB4;
+    }
+    const int nt = (N + 63) / 64, m0 = tile / nt * 64, n0 = tile % nt * 64;
+    const int r_lo = blockIdx.y * rows_per, r_hi = min(nrows, r_lo + rows_per);
+    // this thread's rows of a step (lr and lr + 1) and its eight columns
+    const int lr = (tid >> 3) * 2, lc = (tid & 7) * 8;
+    float16_t acc;
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[v] = 0.0f;
+    float col[8] = {};
+    union Pack { uint4 q; bf16 h[8]; };
+    Pack a[2], bb[2];
+    auto load = [&](int r0) {
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            const int r = r0 + lr + q;
+            a[q].q = bb[q].q = make_uint4(0u, 0u, 0u, 0u);
+            if (r < r_hi) {
+                if (m0 + lc < M) a[q].q = *reinterpret_cast<const uint4 *>(A + (size_t)r * lda + m0 + lc);
+                if (n0 + lc < N) bb[q].q = *reinterpret_cast<const uint4 *>(B + (size_t)r * ldb + n0 + lc);
+            }
+        }
+    };
+    load(r_lo);
+    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+    for (int r0 = r_lo; r0 < r_hi; r0 += WK) {
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            *reinterpret_cast<uint32_t *>(&As[lc + j][lr]) = (uint32_t)a[0].h[j] | ((uint32_t)a[1].h[j] << 16);
+            *reinterpret_cast<uint32_t *>(&Bs[lc + j][lr]) = (uint32_t)bb[0].h[j] | ((uint32_t)bb[1].h[j] << 16);
+            col[j] += bf2f(a[0].h[j]) + bf2f(a[1].h[j]);
+        }
+        __syncthreads();
+        load(r0 + WK);
+#pragma unroll
+        for (int ks = 0; ks < WK; ks += 16) {
+            const int kk = ks + 8 * (lane >> 5);
+            const bf16x8_t x = *reinterpret_cast<const bf16x8_t *>(&As[wm + (lane & 31)][kk]);
+            const bf16x8_t y = *reinterpret_cast<const bf16x8_t *>(&Bs[wn + (lane & 31)][kk]);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    float *out = part + (size_t)blockIdx.y * NPAR;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+        const int o = m0 + wm + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), i = n0 + wn + (lane & 31);
+        if (o < M && i < N) out[ow + (size_t)o * N + i] = acc[v];
+    }
+    if (n0) return;  // block-uniform
+#pragma unroll
+    for (int j = 0; j < 8; j++) cs[tid >> 3][lc + j] = col[j];
+    __syncthreads();
+    if (tid < 64 && m0 + tid < M) {
+        float v = 0.0f;
+        for (int q = 0; q < 32; q++) v += cs[q][tid];
+        out[ob + m0 + tid] = v;
+    }
+}
+
 bool mlp_ready(const MlpState *m) { return m != nullptr && m->w != nullptr; }
 
 static void free_ws(MlpState *m)
 {
-    for (void *p : {(void *)m->X, (void *)m->H1, (void *)m->H2, (void *)m->H3, (void *)m->dY, (void *)m->dA,
-                    (void *)m->dB, (void *)m->Z1, (void *)m->Z2, (void *)m->Z3, (void *)m->Y, (void *)m->diff,
-                    (void *)m->lpart, (void *)m->lcnt})
-        if (p) hipFree(p);
-    m->X = m->H1 = m->H2 = m->H3 = m->dY = m->dA = m->dB = nullptr;
+    hipFree(m->ws);
+    m->ws = nullptr;
+    m->X = m->H1 = m->H2 = m->H3 = m->dY = m->dZ1 = m->dZ2 = m->dZ3 = nullptr;
     m->Z1 = m->Z2 = m->Z3 = m->Y = m->diff = m->lpart = nullptr;
     m->lcnt = nullptr;
     m->cap = 0;
@@ -783,8 +1124,14 @@ static mpt_status ensure_ws(MlpState *m, size_t rows, bool train)
     if (rows <= m->cap && (!train || m->dY)) return MPT_OK;
     free_ws(m);
     size_t cap = rows < 1024 ? 1024 : rows;
-    bool ok = true;
-    auto A = [&](void **p, size_t bytes) { ok = ok && hipMalloc(p, bytes) == hipSuccess; };
+    void **part[16];
+    size_t at[16], total = 0;
+    int np = 0;
+    auto A = [&](void **p, size_t bytes) {
+        part[np] = p;
+        at[np++] = total;
+        total += (bytes + 255) / 256 * 256;
+    };
     A((void **)&m->X, cap * F_IN * sizeof(bf16));
     A((void **)&m->H1, cap * HID * sizeof(bf16));
     A((void **)&m->H2, cap * HID * sizeof(bf16));
@@ -795,16 +1142,18 @@ static mpt_status ensure_ws(MlpState *m, size_t rows, bool train)
         A((void **)&m->Z2, cap * HID * sizeof(float));
         A((void **)&m->Z3, cap * HID * sizeof(float));
         A((void **)&m->dY, cap * F_OUTP * sizeof(bf16));
-        A((void **)&m->dA, cap * HID * sizeof(bf16));
-        A((void **)&m->dB, cap * HID * sizeof(bf16));
+        A((void **)&m->dZ1, cap * HID * sizeof(bf16));
+        A((void **)&m->dZ2, cap * HID * sizeof(bf16));
+        A((void **)&m->dZ3, cap * HID * sizeof(bf16));
         A((void **)&m->diff, cap * F_OUTP * sizeof(float));
-        A((void **)&m->lpart, ((cap + 255) / 256) * sizeof(float));
-        A((void **)&m->lcnt, ((cap + 255) / 256) * sizeof(int));
+        A((void **)&m->lpart, ((cap + TR - 1) / TR) * sizeof(float));
+        A((void **)&m->lcnt, ((cap + TR - 1) / TR) * sizeof(int));
     }
-    if (!ok) {
+    if (hipMalloc((void **)&m->ws, total) != hipSuccess) {
         free_ws(m);
         return MPT_E_NOMEM;
     }
+    for (int i = 0; i < np; i++) *part[i] = m->ws + at[i];
     m->cap = cap;
     return MPT_OK;
 }
@@ -842,7 +1191,7 @@ static mpt_status alloc_params(MlpState *m)
 {
     bool ok = hipMalloc((void **)&m->w, NPAR * 4) == hipSuccess && hipMalloc((void **)&m->m, NPAR * 4) == hipSuccess &&
               hipMalloc((void **)&m->v, NPAR * 4) == hipSuccess && hipMalloc((void **)&m->g, NPAR * 4) == hipSuccess &&
-              hipMalloc((void **)&m->wb, NPAR * 2) == hipSuccess && hipMalloc((void **)&m->wf, NFRAG * 2) == hipSuccess;
+              hipMalloc((void **)&m->wb, NPAR * 2) == hipSuccess && hipMalloc((void **)&m->wf, (NFRAG + NFRAGT) * 2) == hipSuccess;
     return ok ? MPT_OK : MPT_E_NOMEM;
 }
 
@@ -876,21 +1225,18 @@ static void gemm(int M, int N, int K, const bf16 *A, int lda, const bf16 *B, int
     hipLaunchKernelGGL((k_gemm<AT, BT, EPI>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, e, kps);
 }
 
-// forward over `nrows` rows already featurised in m->X; with train, keep Z
-static void forward(MlpState *m, int nrows, bool train, hipStream_t st)
+// layer-by-layer forward over `nrows` rows already featurised in m->X
+static void forward(MlpState *m, int nrows, hipStream_t st)
 {
     Epi e{};
     e.ldc = HID;
     e.bias = m->w + OB1;
-    e.zout = train ? m->Z1 : nullptr;
     e.hout = m->H1;
     gemm<false, true, EPI_BIAS_GELU>(nrows, HID, F_IN, m->X, F_IN, m->wb + OW1, F_IN, e, 1, st);
     e.bias = m->w + OB2;
-    e.zout = train ? m->Z2 : nullptr;
     e.hout = m->H2;
     gemm<false, true, EPI_BIAS_GELU>(nrows, HID, HID, m->H1, HID, m->wb + OW2, HID, e, 1, st);
     e.bias = m->w + OB3;
-    e.zout = train ? m->Z3 : nullptr;
     e.hout = m->H3;
     gemm<false, true, EPI_BIAS_GELU>(nrows, HID, HID, m->H2, HID, m->wb + OW3, HID, e, 1, st);
     Epi e4{};
@@ -941,10 +1287,22 @@ mpt_status mlp_predict_unfused(MlpState *m, const SceneDev &s, const BatchDev &b
         v.order = b.order + c0;
         v.prim = b.prim + c0;
         hipLaunchKernelGGL(k_features, dim3((nr + 127) / 128), dim3(128), 0, st, s, v, nullptr, nr, nullptr, m->X);
-        forward(m, nr, false, st);
+        forward(m, nr, st);
         hipLaunchKernelGGL(k_decode, dim3((nr + 255) / 256), dim3(256), 0, st, s, v, nr, m->Y, x_out + c0 * kRow);
     }
     return hipGetLastError() == hipSuccess ? MPT_OK : MPT_E_DEVICE;
+}
+
+// partial sums of the weight gradients
+static mpt_status ensure_part(MlpState *m, size_t need)
+{
+    if (m->part_cap >= need) return MPT_OK;
+    if (m->part) hipFree(m->part);
+    m->part = nullptr;
+    m->part_cap = 0;
+    if (hipMalloc((void **)&m->part, need * 4) != hipSuccess) return MPT_E_NOMEM;
+    m->part_cap = need;
+    return MPT_OK;
 }
 
 // loss, gradient into m->g (no update); rows = minibatch ids (may be null)
@@ -952,57 +1310,21 @@ static mpt_status grad_dev(MlpState *m, const SceneDev &s, const BatchDev &b, co
                            const double *target, const uint8_t *use, float *d_loss, hipStream_t st)
 {
     if (ensure_ws(m, (size_t)nrows, true)) return MPT_E_NOMEM;
-    hipLaunchKernelGGL(k_features, dim3((nrows + 127) / 128), dim3(128), 0, st, s, b, rows, nrows, nullptr, m->X);
-    forward(m, nrows, true, st);
-    const int nblk = (nrows + 255) / 256;
-    hipLaunchKernelGGL(k_loss_partial, dim3(nblk), dim3(256), 0, st, s, b, rows, nrows, m->Y, target, use, m->diff,
-                       m->lpart, m->lcnt);
-    hipLaunchKernelGGL(k_loss_final, dim3(std::min(256, (nrows * F_OUTP + 255) / 256)), dim3(256), 0, st, m->lpart, m->lcnt, nblk, m->diff, nrows, m->dY,
-                       d_loss);
-    // split-K partial buffer for the weight gradients
-    const int splits = nrows >= 4096 ? 16 : (nrows >= 1024 ? 4 : 1);
-    const size_t need = (size_t)splits * HID * HID;
-    if (m->part_cap < need) {
-        if (m->part) hipFree(m->part);
-        m->part = nullptr;
-        if (hipMalloc((void **)&m->part, need * 4) != hipSuccess) return MPT_E_NOMEM;
-        m->part_cap = need;
-    }
-    auto wgrad = [&](int Mo, int Ni, const bf16 *dZ, int ldz, const bf16 *Xin, int ldx, float *gout) {
-        // dW[o][i] = sum_r dZ[r][o] X[r][i]: A = dZ^T (AT), B = X (row-major)
-        Epi e{};
-        e.ldc = Ni;
-        e.fout = m->part;
-        int kps = (nrows + splits - 1) / splits;
-        kps = ((kps + GK - 1) / GK) * GK;
-        const int sp = (nrows + kps - 1) / kps;
-        gemm<true, false, EPI_F32>(Mo, Ni, nrows, dZ, ldz, Xin, ldx, e, splits, st);
-        const size_t n = (size_t)Mo * Ni;
-        hipLaunchKernelGGL(k_reduce_splits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, m->part, sp, n, gout);
-    };
-    // layer 4: dW4, db4, dH3 = dY W4
-    wgrad(F_OUTP, HID, m->dY, F_OUTP, m->H3, HID, m->g + OW4);
-    hipLaunchKernelGGL(k_colsum, dim3(F_OUTP), dim3(256), 0, st, m->dY, nrows, F_OUTP, F_OUTP, m->g + OB4);
-    Epi e{};
-    e.ldc = HID;
-    e.zin = m->Z3;
-    e.hout = m->dA;  // dZ3
-    gemm<false, false, EPI_DGELU>(nrows, HID, F_OUTP, m->dY, F_OUTP, m->wb + OW4, HID, e, 1, st);
-    // layer 3
-    wgrad(HID, HID, m->dA, HID, m->H2, HID, m->g + OW3);
-    hipLaunchKernelGGL(k_colsum, dim3(HID), dim3(256), 0, st, m->dA, nrows, HID, HID, m->g + OB3);
-    e.zin = m->Z2;
-    e.hout = m->dB;  // dZ2
-    gemm<false, false, EPI_DGELU>(nrows, HID, HID, m->dA, HID, m->wb + OW3, HID, e, 1, st);
-    // layer 2
-    wgrad(HID, HID, m->dB, HID, m->H1, HID, m->g + OW2);
-    hipLaunchKernelGGL(k_colsum, dim3(HID), dim3(256), 0, st, m->dB, nrows, HID, HID, m->g + OB2);
-    e.zin = m->Z1;
-    e.hout = m->dA;  // dZ1
-    gemm<false, false, EPI_DGELU>(nrows, HID, HID, m->dB, HID, m->wb + OW2, HID, e, 1, st);
-    // layer 1
-    wgrad(HID, F_IN, m->dA, HID, m->X, F_IN, m->g + OW1);
-    hipLaunchKernelGGL(k_colsum, dim3(HID), dim3(256), 0, st, m->dA, nrows, HID, HID, m->g + OB1);
+    // the weight gradients' row splits: about 256 rows each (4096 rows: 704
+    // blocks, 14.7 us; 512 rows each: 26 us), at most 32 partial sums to add
+    const int splits = std::max(1, std::min(32, (nrows + 255) / 256));
+    const int rows_per = ((nrows + splits - 1) / splits + WK - 1) / WK * WK;
+    const int sp = (nrows + rows_per - 1) / rows_per;
+    if (ensure_part(m, (size_t)sp * NPAR)) return MPT_E_NOMEM;
+    const TrainBufs t{m->X,   m->H1, m->H2, m->H3, m->dY,   m->dZ1,   m->dZ2,
+                      m->dZ3, m->Z1, m->Z2, m->Z3, m->diff, m->lpart, m->lcnt};
+    const int tiles = (nrows + TR - 1) / TR;
+    hipLaunchKernelGGL(k_train_forward, dim3(tiles), dim3(256), 0, st, s, b, rows, nrows, target, use, m->wb, m->wf,
+                       m->w, t);
+    hipLaunchKernelGGL(k_train_backward, dim3(tiles), dim3(256), 0, st, nrows, tiles, m->wf, t, d_loss);
+    hipLaunchKernelGGL(k_train_weights, dim3(WT_TILES, sp), dim3(256), 0, st, nrows, rows_per, t, m->part);
+    hipLaunchKernelGGL(k_reduce_splits, dim3((unsigned)((NPAR + 255) / 256)), dim3(256), 0, st, m->part, sp,
+                       (size_t)NPAR, m->g);
     return hipGetLastError() == hipSuccess ? MPT_OK : MPT_E_DEVICE;
 }
 
@@ -1060,15 +1382,9 @@ mpt_status mlp_grad_f32_dev(MlpState *m, const SceneDev &s, const BatchDev &b, c
     hipLaunchKernelGGL(k_loss_partial, dim3(nblk), dim3(256), 0, st, s, b, rows, nrows, m->Y, target, use, m->diff,
                        m->lpart, m->lcnt);
     hipLaunchKernelGGL(k_loss_final, dim3(std::min(256, (nrows * F_OUTP + 255) / 256)), dim3(256), 0, st, m->lpart,
-                       m->lcnt, nblk, m->diff, nrows, (bf16 *)nullptr, d_loss, m->dYf);
+                       m->lcnt, nblk, m->diff, nrows, d_loss, m->dYf);
     const int splits = nrows >= 4096 ? 16 : (nrows >= 1024 ? 4 : 1);
-    const size_t need = (size_t)splits * HID * HID;
-    if (m->part_cap < need) {
-        if (m->part) hipFree(m->part);
-        m->part = nullptr;
-        if (hipMalloc((void **)&m->part, need * 4) != hipSuccess) return MPT_E_NOMEM;
-        m->part_cap = need;
-    }
+    if (ensure_part(m, (size_t)splits * HID * HID)) return MPT_E_NOMEM;
     auto wgrad = [&](int Mo, int Ni, const float *dZ, int ldz, const float *Xin, int ldx, float *gout) {
         EpiF eg{};
         eg.ldc = Ni;

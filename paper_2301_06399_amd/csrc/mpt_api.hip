@@ -687,8 +687,7 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
     // per-order cursors in counters 5..9, the length in counter 30
     int *rows = (net && opts->init == MPT_INIT_LEARNED) ? (int *)kp.pol_list : nullptr, *rows_cnt = ctr + 30;
     if (timed) hipEventRecord(c->ev[0], s);
-    launch_zero(ctr, kCounters, s);
-    launch_bin(bd, kp.out, c->s, ctr + 0, ctr + 32, (int *)kp.perm, kp.rows != nullptr, rows, ctr + 5, s);
+    launch_bin(bd, kp.out, c->s, ctr, kCounters, (int *)kp.perm, kp.rows != nullptr, rows, ctr + 5, s);
     const int mode = fp64 ? MODE_PLAIN64 : MODE_FP32;
     launch_start(mode, form_used, kp, s);
     if (timed) hipEventRecord(c->ev[1], s);
@@ -719,6 +718,10 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
                 // a small batch gets a wave per path: what it waits for is its
                 // longest descent, which lanes of other types only slow down
                 g = resident_grid(c, k, blk, n, blk / 64, lds ? rec_bytes : 0);
+                // and one wave per SIMD while its lanes hold the whole batch: two
+                // would only take turns
+                const int64_t one = (int64_t)c->cu * 256 / blk;
+                if (n <= one * blk && g > one) g = (int)one;
                 if (first && gdiv > 1) g = (g + gdiv - 1) / gdiv;
             }
             launch_lm(md, ord, lds, form, c->refr, rec_bytes, kp, g, blk, where);

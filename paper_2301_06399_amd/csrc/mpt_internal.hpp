@@ -92,8 +92,8 @@ int bin_key_count();
 // the list's length
 // by_solve: perm receives each solve's bin slot (-1: invalid), else each
 // slot's solve
-void launch_bin(const BatchDev &b, const OutDev &out, const SceneDev &s, int *bin_cnt, int *keys, int *perm,
-                bool by_solve, int *rows, int *curved, hipStream_t st);
+void launch_bin(const BatchDev &b, const OutDev &out, const SceneDev &s, int *ctr, int n_ctr, int *perm, bool by_solve,
+                int *rows, int *curved, hipStream_t st);
 const void *lm_kernel(int mode, int order, bool lds, int form, bool refr);
 void launch_lm(int mode, int order, bool lds, int form, bool refr, size_t lds_bytes, const KParams &kp, int grid,
                int block, hipStream_t st);

@@ -158,6 +158,17 @@ __device__ inline int bin_key(const SolveIds &r, int a, int bb, int c)
     return kKeyBase[r.ord] + code;
 }
 
+// The results of an invalid solve.
+__device__ __forceinline__ void bad_solve(const BatchDev &b, const OutDev &out, int64_t i)
+{
+    for (int q = 0; q < kRow; q++) out.x[(size_t)i * kRow + q] = 0.0;
+    out.cost[i] = __builtin_huge_val();
+    out.iters[i] = 0;
+    out.status[i] = ST_BAD;
+    if (out.stage)
+        for (int q = 0; q < 4; q++) out.stage[(size_t)q * b.n + i] = 0;
+}
+
 __global__ void __launch_bounds__(kBinBlock) k_bin_count(BatchDev b, OutDev out, int n_all, int n_pl, int n_pl_ln,
                                                           int n_pl_ln_q, int *__restrict__ key_cnt)
 {
@@ -181,12 +192,7 @@ __global__ void __launch_bounds__(kBinBlock) k_bin_count(BatchDev b, OutDev out,
         const int64_t i = base + (int64_t)j * kBinBlock + threadIdx.x;
         if (i >= b.n) break;
         if (r[j].ord < 0) {
-            for (int q = 0; q < kRow; q++) out.x[(size_t)i * kRow + q] = 0.0;
-            out.cost[i] = __builtin_huge_val();
-            out.iters[i] = 0;
-            out.status[i] = ST_BAD;
-            if (out.stage)
-                for (int q = 0; q < 4; q++) out.stage[(size_t)q * b.n + i] = 0;
+            bad_solve(b, out, i);
         } else {
             // the later stages' iteration counts are zero: written here,
             // coalesced, so that the solver kernels store only what a path
@@ -325,6 +331,77 @@ __global__ void __launch_bounds__(kBinBlock) k_bin_scatter(BatchDev b, int n_all
             perm[slot] = (int)i;
         }
         if (crank[j] >= 0) rows[cbase[r[j].ord - 1] + crank[j]] = (int)i;
+    }
+}
+
+// The whole binning of a small batch by one block: clears the workspace's
+// counters, counts the keys, scans them and places the solves, with the keys
+// and ranks in LDS.  Bound by the latency of its loads.  Four launches (clear,
+// count, offsets, scatter) took 26 us and the gaps between them on 16,384
+// solves, this one 24.6 us (5.4 us on 64); with more solves the one block's
+// loads cost more than the launches.
+constexpr int kSmallBin = 16384;
+constexpr int kSmallItems = kSmallBin / 1024;
+
+__global__ void __launch_bounds__(1024) k_bin_small(BatchDev b, OutDev out, int n_all, int n_pl, int n_pl_ln,
+                                                     int n_pl_ln_q, int *__restrict__ ctr, int n_ctr,
+                                                     int *__restrict__ perm, int by_solve)
+{
+    __shared__ int cnt[2048];        // key counts, then offsets
+    __shared__ int wsum[16];
+    __shared__ uint16_t skey[kSmallBin], srank[kSmallBin];
+    const int t = threadIdx.x, lane = t & 63;
+    for (int i = t; i < n_ctr; i += 1024)
+        if (i >= kMaxN) ctr[i] = 0;  // the first five receive the orders' totals below
+    cnt[t] = cnt[t + 1024] = 0;
+    __syncthreads();
+    for (int j0 = 0; j0 < kSmallItems; j0 += 4) {
+        if ((int64_t)j0 * 1024 >= b.n) break;  // block-uniform
+        SolveIds r[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int64_t i = (int64_t)(j0 + j) * 1024 + t;
+            if (i < b.n) load_ids(b, i, r[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int64_t i = (int64_t)(j0 + j) * 1024 + t;
+            if (i >= b.n) continue;
+            check_ids(b, n_all, r[j]);
+            skey[i] = 0xffffu;
+            if (r[j].ord < 0) {
+                bad_solve(b, out, i);
+            } else {
+                if (out.stage)
+                    for (int q = 1; q < 4; q++) out.stage[(size_t)q * b.n + i] = 0;
+                const int key = bin_key(r[j], n_pl, n_pl_ln, n_pl_ln_q);
+                skey[i] = (uint16_t)key;
+                srank[i] = (uint16_t)atomicAdd(&cnt[key], 1);
+            }
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the counts, two per thread
+    const int a0 = cnt[2 * t], a1 = cnt[2 * t + 1];
+    int incl = a0 + a1;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int v = __shfl_up(incl, d);
+        if (lane >= d) incl += v;
+    }
+    if (lane == 63) wsum[t >> 6] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < (t >> 6); w++) before += wsum[w];
+    cnt[2 * t] = before + incl - a0 - a1;
+    cnt[2 * t + 1] = before + incl - a1;
+    __syncthreads();
+    if (t < kMaxN) ctr[t] = cnt[t + 1 < kMaxN ? kKeyBase[t + 2] : kNumKeys] - cnt[kKeyBase[t + 1]];
+    for (int64_t i = t; i < b.n; i += 1024) {
+        const int key = skey[i];
+        const int slot = key != 0xffff ? cnt[key] + srank[i] : -1;
+        if (by_solve) perm[i] = slot;
+        else if (slot >= 0) perm[slot] = (int)i;
     }
 }
 
@@ -888,6 +965,32 @@ __global__ void __launch_bounds__(256) k_accept_list(BatchDev b, const uint8_t *
             if (r[c][j] >= 0) list[bbase + r[c][j]] = (int)(base + (int64_t)(c * kAccItems + j) * 256 + threadIdx.x);
 }
 
+// The test on solve i of order ord.
+template <bool REFR>
+__device__ __forceinline__ bool accept_solve(const SceneDev &s, const BatchDev &b, const OutDevC &in, int64_t i,
+                                             int ord, double tau_res, double min_seg)
+{
+    const int ri = b.rx_index[i];
+    double rx[3], X[3 * kMaxN];
+    int id[kMaxN], ty[kMaxN];
+    for (int j = 0; j < 3; j++) rx[j] = b.rx[3 * (size_t)ri + j];
+    for (int j = 0; j < 3 * kMaxN; j++) X[j] = (j < 3 * ord) ? in.x[(size_t)i * kRow + j] : 0.0;
+    bool okid = true;
+    for (int k = 0; k < kMaxN; k++) {
+        id[k] = (k < ord) ? b.prim[(size_t)k * b.n + i] : 0;
+        okid = okid && id[k] >= 0 && id[k] < s.n_all;
+        ty[k] = prim_type(id[k], s.n_pl, s.n_pl_ln, s.n_pl_ln_q);
+    }
+    if (!okid) return false;
+    switch (ord) {
+    case 1: return accept_path<1, REFR>(s, rx, id, ty, X, tau_res, min_seg);
+    case 2: return accept_path<2, REFR>(s, rx, id, ty, X, tau_res, min_seg);
+    case 3: return accept_path<3, REFR>(s, rx, id, ty, X, tau_res, min_seg);
+    case 4: return accept_path<4, REFR>(s, rx, id, ty, X, tau_res, min_seg);
+    default: return accept_path<5, REFR>(s, rx, id, ty, X, tau_res, min_seg);
+    }
+}
+
 // Pass 2: the test on the listed solves (grid-stride over the list).
 template <bool REFR>
 __global__ void __launch_bounds__(256) k_accept_eval(SceneDev s, BatchDev b, OutDevC in, double tau_res,
@@ -897,32 +1000,65 @@ __global__ void __launch_bounds__(256) k_accept_eval(SceneDev s, BatchDev b, Out
     const int m = *cnt;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < m; t += gridDim.x * blockDim.x) {
         const int64_t i = list[t];
+        acc[i] = accept_solve<REFR>(s, b, in, i, b.order[i], tau_res, min_seg) ? 1 : 0;
+    }
+}
+
+// Accepted solves among a block's 256.
+__device__ __forceinline__ int block_count(bool a)
+{
+    __shared__ int wcnt[4];
+    const uint64_t m = __ballot(a);
+    if (__lane_id() == 0) wcnt[threadIdx.x >> 6] = (int)__popcll(m);
+    __syncthreads();
+    return wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+}
+
+// A batch of at most kSmallAccept solves: the test with a thread per solve and
+// the blocks' counts in one launch, then k_accept_place.  The six launches below
+// are bound by the list's serial passes while a block holds few solves: they took
+// 52 us and the gaps between them on 16,384 solves, these two 13 us; on 262,144
+// 56 us against 27.  On 1,048,576 it is 95 us against 112: there the few
+// converged lanes of a wave cost more than the list of them.
+constexpr int64_t kSmallAccept = 1 << 18;
+
+template <bool REFR>
+__global__ void __launch_bounds__(256) k_accept_small(SceneDev s, BatchDev b, OutDevC in, double tau_res,
+                                                       double min_seg, uint8_t *__restrict__ acc,
+                                                       int *__restrict__ block_cnt)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    bool a = false;
+    if (i < b.n) {
         const int ord = b.order[i];
-        bool a = false;
-        {
-            const int ri = b.rx_index[i];
-            double rx[3], X[3 * kMaxN];
-            int id[kMaxN], ty[kMaxN];
-            for (int j = 0; j < 3; j++) rx[j] = b.rx[3 * (size_t)ri + j];
-            for (int j = 0; j < 3 * kMaxN; j++) X[j] = (j < 3 * ord) ? in.x[(size_t)i * kRow + j] : 0.0;
-            bool okid = true;
-            for (int k = 0; k < kMaxN; k++) {
-                id[k] = (k < ord) ? b.prim[(size_t)k * b.n + i] : 0;
-                okid = okid && id[k] >= 0 && id[k] < s.n_all;
-                ty[k] = prim_type(id[k], s.n_pl, s.n_pl_ln, s.n_pl_ln_q);
-            }
-            if (okid) {
-                switch (ord) {
-                case 1: a = accept_path<1, REFR>(s, rx, id, ty, X, tau_res, min_seg); break;
-                case 2: a = accept_path<2, REFR>(s, rx, id, ty, X, tau_res, min_seg); break;
-                case 3: a = accept_path<3, REFR>(s, rx, id, ty, X, tau_res, min_seg); break;
-                case 4: a = accept_path<4, REFR>(s, rx, id, ty, X, tau_res, min_seg); break;
-                default: a = accept_path<5, REFR>(s, rx, id, ty, X, tau_res, min_seg); break;
-                }
-            }
-        }
+        if (ord >= 1 && ord <= kMaxN && (in.status[i] & 0x7f) == ST_CONV)
+            a = accept_solve<REFR>(s, b, in, i, ord, tau_res, min_seg);
         acc[i] = a ? 1 : 0;
     }
+    const int c = block_count(a);
+    if (threadIdx.x == 0) block_cnt[blockIdx.x] = c;
+}
+
+// The accepted ids in order: each block adds up the counts before it.
+__global__ void __launch_bounds__(256) k_accept_place(const uint8_t *__restrict__ acc, int64_t n,
+                                                       const int *__restrict__ block_cnt, int *__restrict__ idx,
+                                                       int *__restrict__ count)
+{
+    __shared__ int before[4], wcnt[4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int c = 0;
+    for (int q = threadIdx.x; q < (int)blockIdx.x; q += 256) c += block_cnt[q];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d);
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool a = i < n && acc[i];
+    const uint64_t m = __ballot(a);
+    if (lane == 0) before[w] = c, wcnt[w] = (int)__popcll(m);
+    __syncthreads();
+    int base = before[0] + before[1] + before[2] + before[3];
+    for (int j = 0; j < w; j++) base += wcnt[j];
+    if (a) idx[base + (int)__popcll(m & ((1ull << lane) - 1ull))] = (int)i;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 255) *count = base + (int)__popcll(m);
 }
 
 // Pass 3: accepted solves per block of 256 (for the ordered compaction).
@@ -930,16 +1066,8 @@ __global__ void __launch_bounds__(256) k_accept_count(const uint8_t *__restrict_
                                                        int *__restrict__ block_cnt)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool a = (i < n) && acc[i];
-    __shared__ int wcnt[4];
-    const uint64_t m = __ballot(a);
-    if (__lane_id() == 0) wcnt[threadIdx.x >> 6] = (int)__popcll(m);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); w++) t += wcnt[w];
-        block_cnt[blockIdx.x] = t;
-    }
+    const int c = block_count((i < n) && acc[i]);
+    if (threadIdx.x == 0) block_cnt[blockIdx.x] = c;
 }
 
 // Exclusive scan of the per-block counts by one block; total -> *count.
@@ -1029,16 +1157,24 @@ void launch_zero(int *p, int n, hipStream_t st)
 
 int bin_key_count() { return kNumKeys; }
 
-// keys: [3][kNumKeys] ints (counts, offsets, cursors), zeroed by the caller
-void launch_bin(const BatchDev &b, const OutDev &out, const SceneDev &s, int *bin_cnt, int *keys, int *perm,
-                bool by_solve, int *rows, int *curved, hipStream_t st)
+// ctr: the workspace's n_ctr counters, cleared here; the first five receive
+// the solves per order, those from 32 on are [3][kNumKeys] (counts, offsets,
+// cursors).
+void launch_bin(const BatchDev &b, const OutDev &out, const SceneDev &s, int *ctr, int n_ctr, int *perm, bool by_solve,
+                int *rows, int *curved, hipStream_t st)
 {
+    if (b.n > 0 && b.n <= kSmallBin && !rows) {
+        hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(1024), 0, st, b, out, s.n_all, s.n_pl, s.n_pl_ln, s.n_pl_ln_q,
+                           ctr, n_ctr, perm, by_solve ? 1 : 0);
+        return;
+    }
+    launch_zero(ctr, n_ctr, st);
     if (b.n == 0) return;
     const unsigned g = (unsigned)((b.n + kBinPerBlock - 1) / kBinPerBlock);
-    int *kcnt = keys, *koff = keys + kNumKeys, *kcur = keys + 2 * kNumKeys;
+    int *kcnt = ctr + 32, *koff = kcnt + kNumKeys, *kcur = kcnt + 2 * kNumKeys;
     hipLaunchKernelGGL(k_bin_count, dim3(g), dim3(kBinBlock), 0, st, b, out, s.n_all, s.n_pl, s.n_pl_ln, s.n_pl_ln_q,
                        kcnt);
-    hipLaunchKernelGGL(k_bin_offsets, dim3(1), dim3(1024), 0, st, kcnt, koff, bin_cnt, rows ? curved : nullptr);
+    hipLaunchKernelGGL(k_bin_offsets, dim3(1), dim3(1024), 0, st, kcnt, koff, ctr, rows ? curved : nullptr);
     hipLaunchKernelGGL(k_bin_scatter, dim3(g), dim3(kBinBlock), 0, st, b, s.n_all, s.n_pl, s.n_pl_ln, s.n_pl_ln_q,
                        koff, kcur, perm, by_solve ? 1 : 0, rows, curved);
 }
@@ -1095,6 +1231,12 @@ void launch_accept(const SceneDev &s, const BatchDev &b, const OutDevC &in, doub
     const int nblk = (int)((b.n + 255) / 256);
     if (nblk == 0) {
         hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, count, 1);
+        return;
+    }
+    if (b.n <= kSmallAccept) {
+        if (refr) hipLaunchKernelGGL(k_accept_small<true>, dim3(nblk), dim3(256), 0, st, s, b, in, tau_res, min_seg, acc, block_cnt);
+        else hipLaunchKernelGGL(k_accept_small<false>, dim3(nblk), dim3(256), 0, st, s, b, in, tau_res, min_seg, acc, block_cnt);
+        hipLaunchKernelGGL(k_accept_place, dim3(nblk), dim3(256), 0, st, acc, b.n, block_cnt, idx, count);
         return;
     }
     int *lcnt = block_cnt + nblk;

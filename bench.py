@@ -83,11 +83,11 @@ def type_codes(scene, batch):
 
 def algorithmic_flops(table, order, code, iters, kind, kept=False):
     """FLOPs of `iters` iterations of each path at its order and types.
-    kept: the FP32 solver of orders 1-3 keeps the normal equations after a
-    rejected step and skips their assembly in the next iteration; the
-    number of such iterations is not recorded, so they are bounded from
-    below: every iteration after a path's first is charged without its
-    assembly (a lower bound of the work done)."""
+    kept: the solver assembles the normal equations once per iteration, at
+    the trial point, whose cost comes with them, so an iteration is less than
+    the table's (assembly, step and a cost of its own); of orders 1-3 every
+    iteration after a path's first is charged without its assembly (a lower
+    bound of the work done, since an assembly is more than a cost)."""
     tot = 0
     for n in range(1, 6):
         m = order == n

@@ -1017,7 +1017,8 @@ static void count_one(const int32_t *types, int64_t out[4], bool param, int64_t 
         U[2 * k + 1] = (types[k] == MPT_PLANE || types[k] == MPT_QUADRIC) ? Cnt(rnd()) : Cnt(0.0);
     }
     tally() = FlopTally();
-    assemble_param<Cnt, N, false>(sc, p, U, Ap, gp, C, rinf);
+    bool guard;
+    assemble_param<Cnt, N, false>(sc, p, U, Ap, gp, C, rinf, guard);
     if (asm_flops) *asm_flops = tally().flops();
     for (int i = 0; i < 2 * N; i++) {
         const bool real = (i % 2 == 0) || types[i / 2] == MPT_PLANE || types[i / 2] == MPT_QUADRIC;
@@ -1026,7 +1027,6 @@ static void count_one(const int32_t *types, int64_t out[4], bool param, int64_t 
     }
     chol_band<Cnt, N, 2>(Ap);
     chol_solve_band<Cnt, N, 2>(Ap, gp);
-    bool guard;
     eval_cost_param<Cnt, N, false>(sc, p, U, gp, Ct, rt, guard);
     out[0] = tally().flops();
     out[3] = tally().sqrt + tally().div;

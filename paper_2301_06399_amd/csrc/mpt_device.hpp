@@ -724,10 +724,11 @@ __host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3],
 }
 
 // Normal equations of the parametric form: band of J^T J (2 x 2 blocks) and
-// J^T I, with J = dI/dX . dX/dU by the chain rule.
+// J^T I, with J = dI/dX . dX/dU by the chain rule, and whether every point
+// stays in the guard box.
 template <typename T, int N, bool REFR = true>
 __host__ __device__ __forceinline__ bool assemble_param(const SceneT<T> &sc, const PathIn<T, N> &p, const T *U, T *A,
-                                               T *g, T &C, T &rinf)
+                                               T *g, T &C, T &rinf, bool &guard)
 {
     constexpr int M = 2 * N;
 #pragma unroll
@@ -745,7 +746,10 @@ __host__ __device__ __forceinline__ bool assemble_param(const SceneT<T> &sc, con
     auto map = [&](int j) {
         ok = param_map<T>(p.ty[j], sc.rec + (size_t)p.id[j] * kRec, U[2 * j], U[2 * j + 1], Xw[j % 3], Tw[j % 3]) &&
              ok;
+#pragma unroll
+        for (int i = 0; i < 3; i++) guard = guard && (Xw[j % 3][i] >= sc.glo[i]) && (Xw[j % 3][i] <= sc.ghi[i]);
     };
+    guard = true;
     map(0);
     C = T(0);
     rinf = T(0);

@@ -4,15 +4,15 @@
 //                    enough of them are idle (FP64 plain, FP32 stage or FP64
 //                    fallback)
 //
-// What bounds them: VALU issue (an order-5 FP32 iteration is about 2400 vector
+// What bounds them: VALU issue (an order-5 FP32 iteration is about 2000 vector
 // instructions, four cycles each) and, at one or two waves per SIMD, the
 // latency of the chain.  So the loop holds nothing but iterations: starts and
 // ends of paths are kernels of their own (k_start, k_finish), a lane reads and
 // writes one 128-byte state row, and finished lanes are saved together.  With
-// them in the loop an order-5 kernel was 78 KB of code at 256 registers, now
-// 33 KB at 185, and the stress workload's pass took 18.0 ms (with start and end
-// of the paths) against 10.7 ms (and 2.5 + 1.7 ms in k_start and k_finish); the
-// street canyon's (262,144 paths of orders 1-3) 466 us against 330.
+// them in the loop an order-5 kernel was 78 KB of code at 256 registers, and the
+// stress workload's pass (16.8 M paths of orders 3-5) took 18.0 ms, now 8.8 ms
+// (and 2.5 + 1.7 ms in k_start and k_finish); the street canyon's (262,144
+// paths of orders 1-3) 466 us, now 295.
 //  k_lm_low          the same over orders 1-3
 //  k_lm_one          one order's bin
 // The file is compiled once per (mode, form, scene in LDS or not), MPT_LM_MODE
@@ -30,209 +30,152 @@ struct LMOpts {
     T frac, tol_step, tol_res, tau_root, lambda0, stat_tol;
 };
 
-// State of one lane's path: the unknowns (D = 3N points, or 2N parameters
-// in the parametric form) and the Levenberg-Marquardt scalars.
-template <typename T, int N, int D = 3 * N>
+// What the next pass of a lane does: a step, or only the normal equations of
+// a new path's start (a path that was parked has passed its iteration's
+// checks already).
+enum : int { LANE_STEP = 0, LANE_NEW = 1, LANE_RESUMED = 2 };
+
+// State of one lane's path: the unknowns (3N points, or 2N parameters in the
+// parametric form), the normal equations, gradient and cost there, and the
+// Levenberg-Marquardt scalars.
+template <typename T, int N, int FORM>
 struct Lane {
-    T X[D];
+    static constexpr int B = FORM ? 2 : 3, D = B * N, S = Band<N, B>::SIZE;
+    T X[D], A[S], g[D];
     T lam, Cref, C, rinf;
-    int it, stat;
-    // The normal equations, gradient and cost of the current point, kept
-    // after a rejected step: the point has not moved, so the next iteration
-    // would rebuild the same values (only the damping changes).  FP32 and
-    // orders 1-3, whose copies fit in registers beside the order-5 code (the
-    // FP64 kernels already spill).
-    static constexpr bool kKeep = N <= 3 && sizeof(T) == 4;
-    static constexpr int kS = kKeep ? D * (D + 1) / 2 : 1;
-    static constexpr int kM = kKeep ? D : 1;
-    T A0[kS], g0[kM], C0, r0;
-    bool keep;
+    int it, stat, win_it, phase;  // win_it: the iteration of the next plateau test
 };
 
-// One Levenberg-Marquardt iteration on the cost of Eq. (12) with the
-// rescaled rows; returns ST_RUNNING or the final status.  REFR: the scene
-// has refracting facets (their rows are compiled in).
-template <typename T, int N, bool REFR>
-__device__ __forceinline__ int lm_step(const SceneT<T> &sc, const PathIn<T, N> &p, Lane<T, N> &L,
-                                       const LMOpts<T> &o)
+// x / 10, correctly rounded while the quotient is a normal number: the
+// remainder of the product with the rounded tenth corrects it (Markstein; the
+// product is within one unit in the last place).  Three instructions for the
+// ten (FP32) or more of a division.
+template <typename T>
+__device__ __forceinline__ T tenth(T x)
 {
-    constexpr int M = 3 * N;
-    using LT = Lane<T, N>;
-    L.it++;
-    T A[Band<N>::SIZE], g[M], C, rinf;
-    if (LT::kKeep && L.keep) {
-#pragma unroll
-        for (int i = 0; i < Band<N>::SIZE; i++) A[i] = L.A0[i % LT::kS];
-#pragma unroll
-        for (int i = 0; i < M; i++) g[i] = L.g0[i % LT::kM];
-        C = L.C0;
-        rinf = L.r0;
-    } else {
-        if (!assemble<T, N, REFR>(sc, p, L.X, A, g, C, rinf)) return ST_DEGEN;
-        if constexpr (LT::kKeep) {
-#pragma unroll
-            for (int i = 0; i < Band<N>::SIZE; i++) L.A0[i] = A[i];
-#pragma unroll
-            for (int i = 0; i < M; i++) L.g0[i] = g[i];
-            L.C0 = C;
-            L.r0 = rinf;
-        }
-    }
-    L.keep = false;
-    L.C = C;
-    L.rinf = rinf;
-    T dmax = T(0);
-#pragma unroll
-    for (int i = 0; i < M; i++) dmax = fmax(dmax, A[Band<N>::at(i, i)]);
-    if (L.it == 1) {
-        L.lam = o.lambda0 * dmax;
-        L.Cref = C;
-    }
-    if (rinf <= o.tol_res) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-    if (o.win > 0 && L.it > 1 && (L.it - 1) % o.win == 0) {
-        if (C > o.frac * L.Cref) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-        L.Cref = C;
-    }
-    const T floor_d = T(1e-12) * dmax;
-#pragma unroll
-    for (int i = 0; i < M; i++) A[Band<N>::at(i, i)] += L.lam * fmax(A[Band<N>::at(i, i)], floor_d);
-    if (!chol_band<T, N>(A)) {
-        L.lam *= T(10);
-        if (L.lam > T(1e12) * dmax) return ST_STALL;
-        L.keep = LT::kKeep;
-        return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
-    }
-#pragma unroll
-    for (int i = 0; i < M; i++) g[i] = -g[i];
-    const T pred = chol_solve_band<T, N>(A, g);  // g <- dx; pred = -g^T dx
-    if (o.stat_win > 0 && p.planar) {
-        // planes and straight edges: the descent has stalled when the damped
-        // model predicts too small a decrease several iterations in a row
-        L.stat = (pred < o.stat_tol * C) ? L.stat + 1 : 0;
-        if (L.stat >= o.stat_win) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-    }
-    T xinf = T(0), dinf = T(0);
-    bool guard = true;
-#pragma unroll
-    for (int k = 0; k < N; k++)
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            xinf = fmax(xinf, fabs(L.X[3 * k + i]));
-            dinf = fmax(dinf, fabs(g[3 * k + i]));
-            const T xt = L.X[3 * k + i] + g[3 * k + i];
-            guard = guard && (xt >= sc.glo[i]) && (xt <= sc.ghi[i]);
-        }
-    const bool small = dinf <= o.tol_step * (T(1) + xinf);
-    T Ct = T(0), rt = T(0);
-    bool okt = guard && eval_cost<T, N, REFR>(sc, p, L.X, g, Ct, rt);
-    if (okt && Ct < C) {
-#pragma unroll
-        for (int i = 0; i < M; i++) L.X[i] += g[i];
-        L.C = Ct;
-        L.rinf = rt;
-        L.lam = fmax(L.lam / T(10), T(1e-15) * dmax);
-        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-    } else {
-        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-        L.lam *= T(10);
-        if (L.lam > T(1e12) * dmax) return ST_STALL;
-        L.keep = LT::kKeep;
-    }
-    return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
+    const T q = x * T(0.1), r = fma(T(-10), q, x);
+    return fma(r, T(0.1), q);
 }
 
-// One Levenberg-Marquardt iteration of the parametric form (Eq. (15)), with
-// the same rules; the placeholder parameter of an edge is held fixed.
-template <typename T, int N, bool REFR>
-__device__ __forceinline__ int lm_step_param(const SceneT<T> &sc, const PathIn<T, N> &p, Lane<T, N, 2 * N> &L,
-                                             const LMOpts<T> &o)
+// One pass of the Levenberg-Marquardt iteration on the cost of Eq. (12) with
+// the rescaled rows (FORM 1: of Eq. (15), where the placeholder parameter of
+// an edge is held fixed): the step from the lane's normal equations, then
+// the normal equations at the trial point, which are the next pass's if the
+// step is taken, then the tests that open the next iteration.  The trial's
+// cost comes with its normal equations: a pass that evaluated the cost first
+// and assembled an accepted point in the next iteration mapped every point and
+// formed every direction twice and took 2.62 against 1.76 ms (1,048,576
+// paths among curved objects, FP32 parametric), 606 against 410 us (45,769
+// planar paths of orders 1-3, FP64 implicit) and 330 against 295 us (262,144
+// planar paths, where the longest chains bound it).
+// Returns ST_RUNNING or the final status.  REFR: the scene has refracting
+// facets (their rows are compiled in).
+template <typename T, int N, int FORM, bool REFR>
+__device__ __forceinline__ int lm_pass(const SceneT<T> &sc, const PathIn<T, N> &p, Lane<T, N, FORM> &L,
+                                       const LMOpts<T> &o)
 {
-    constexpr int M = 2 * N;
-    using LT = Lane<T, N, 2 * N>;
-    L.it++;
-    T A[Band<N, 2>::SIZE], g[M], C, rinf;
-    if (LT::kKeep && L.keep) {
+    using LT = Lane<T, N, FORM>;
+    constexpr int B = LT::B, M = LT::D;
+    using Bd = Band<N, B>;
+    const bool stepping = L.phase == LANE_STEP;
+    bool real[M];  // the edges' placeholder parameters are not
 #pragma unroll
-        for (int i = 0; i < Band<N, 2>::SIZE; i++) A[i] = L.A0[i % LT::kS];
+    for (int i = 0; i < M; i++) real[i] = !(FORM && (i & 1)) || is_surface(p.ty[i / B]);
+    T xt[M], dmax = T(0);
 #pragma unroll
-        for (int i = 0; i < M; i++) g[i] = L.g0[i % LT::kM];
-        C = L.C0;
-        rinf = L.r0;
-    } else {
-        if (!assemble_param<T, N, REFR>(sc, p, L.X, A, g, C, rinf)) return ST_DEGEN;
-        if constexpr (LT::kKeep) {
+    for (int i = 0; i < M; i++) xt[i] = L.X[i];
+    bool go = true, small = false;  // go: there is a trial point
+    if (stepping) {
+        T F[LT::S];
 #pragma unroll
-            for (int i = 0; i < Band<N, 2>::SIZE; i++) L.A0[i] = A[i];
+        for (int i = 0; i < M; i++) dmax = real[i] ? fmax(dmax, L.A[Bd::at(i, i)]) : dmax;
+        const T floor_d = T(1e-12) * dmax;
 #pragma unroll
-            for (int i = 0; i < M; i++) L.g0[i] = g[i];
-            L.C0 = C;
-            L.r0 = rinf;
+        for (int i = 0; i < M; i++)
+#pragma unroll
+            for (int j = 0; j <= i; j++) {
+                if (!Bd::in(i, j)) continue;
+                const T a = L.A[Bd::at(i, j)];
+                if (i != j) F[Bd::at(i, j)] = a;
+                else if (FORM) F[Bd::at(i, i)] = real[i] ? a + L.lam * fmax(a, floor_d) : T(1);
+                else F[Bd::at(i, i)] = a + L.lam * fmax(a, floor_d);
+            }
+        go = chol_band<T, N, B>(F);
+        if (go) {
+            T d[M];
+#pragma unroll
+            for (int i = 0; i < M; i++) d[i] = -L.g[i];
+            const T pred = chol_solve_band<T, N, B>(F, d);  // d <- dx; pred = -g^T dx
+            if (o.stat_win > 0 && p.planar) {
+                // planes and straight edges: the descent has stalled when the damped
+                // model predicts too small a decrease several iterations in a row
+                L.stat = (pred < o.stat_tol * L.C) ? L.stat + 1 : 0;
+                if (L.stat >= o.stat_win) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+            }
+            T xinf = T(0), dinf = T(0);
+#pragma unroll
+            for (int i = 0; i < M; i++) {
+                xinf = fmax(xinf, fabs(L.X[i]));
+                dinf = fmax(dinf, fabs(d[i]));
+                xt[i] = L.X[i] + d[i];
+                if constexpr (!FORM) go = go && (xt[i] >= sc.glo[i % 3]) && (xt[i] <= sc.ghi[i % 3]);
+            }
+            small = dinf <= o.tol_step * (T(1) + xinf);
         }
     }
-    L.keep = false;
-    L.C = C;
-    L.rinf = rinf;
-    bool real[M];
+    bool take = false;
+    if (go) {
+        T A1[LT::S], g1[M], C1, r1;
+        if constexpr (FORM) {
+            bool guard;
+            take = assemble_param<T, N, REFR>(sc, p, xt, A1, g1, C1, r1, guard) && (!stepping || (guard && C1 < L.C));
+        } else {
+            take = assemble<T, N, REFR>(sc, p, xt, A1, g1, C1, r1) && (!stepping || C1 < L.C);
+        }
+        if (take) {
 #pragma unroll
-    for (int k = 0; k < N; k++) {
-        real[2 * k] = true;
-        real[2 * k + 1] = p.ty[k] == TP || p.ty[k] == TQ;
-    }
-    T dmax = T(0);
+            for (int i = 0; i < M; i++)
 #pragma unroll
-    for (int i = 0; i < M; i++) dmax = real[i] ? fmax(dmax, A[Band<N, 2>::at(i, i)]) : dmax;
-    if (L.it == 1) {
-        L.lam = o.lambda0 * dmax;
-        L.Cref = C;
-    }
-    if (rinf <= o.tol_res) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-    if (o.win > 0 && L.it > 1 && (L.it - 1) % o.win == 0) {
-        if (C > o.frac * L.Cref) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-        L.Cref = C;
-    }
-    const T floor_d = T(1e-12) * dmax;
+                for (int j = 0; j <= i; j++)
+                    if (Bd::in(i, j)) L.A[Bd::at(i, j)] = A1[Bd::at(i, j)];
 #pragma unroll
-    for (int i = 0; i < M; i++) {
-        const T a = A[Band<N, 2>::at(i, i)];
-        A[Band<N, 2>::at(i, i)] = real[i] ? a + L.lam * fmax(a, floor_d) : T(1);
+            for (int i = 0; i < M; i++) {
+                L.X[i] = xt[i];
+                L.g[i] = g1[i];
+            }
+            L.C = C1;
+            L.rinf = r1;
+        }
     }
-    if (!chol_band<T, N, 2>(A)) {
-        L.lam *= T(10);
-        if (L.lam > T(1e12) * dmax) return ST_STALL;
-        L.keep = LT::kKeep;
-        return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
-    }
-#pragma unroll
-    for (int i = 0; i < M; i++) g[i] = -g[i];
-    const T pred = chol_solve_band<T, N, 2>(A, g);  // g <- dU (zero on the placeholders)
-    if (o.stat_win > 0 && p.planar) {
-        L.stat = (pred < o.stat_tol * C) ? L.stat + 1 : 0;
-        if (L.stat >= o.stat_win) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-    }
-    T xinf = T(0), dinf = T(0);
-#pragma unroll
-    for (int i = 0; i < M; i++) {
-        xinf = fmax(xinf, fabs(L.X[i]));
-        dinf = fmax(dinf, fabs(g[i]));
-    }
-    const bool small = dinf <= o.tol_step * (T(1) + xinf);
-    T Ct = T(0), rt = T(0);
-    bool guard = true;
-    bool okt = eval_cost_param<T, N, REFR>(sc, p, L.X, g, Ct, rt, guard) && guard;
-    if (okt && Ct < C) {
-#pragma unroll
-        for (int i = 0; i < M; i++) L.X[i] += g[i];
-        L.C = Ct;
-        L.rinf = rt;
-        L.lam = fmax(L.lam / T(10), T(1e-15) * dmax);
+    if (stepping) {
         if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-    } else {
-        if (small) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
-        L.lam *= T(10);
-        if (L.lam > T(1e12) * dmax) return ST_STALL;
-        L.keep = LT::kKeep;
+        if (take) {
+            L.lam = fmax(tenth(L.lam), T(1e-15) * dmax);
+        } else {
+            L.lam *= T(10);
+            if (L.lam > T(1e12) * dmax) return ST_STALL;
+        }
+        if (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) return ST_MAXIT;
     }
-    return (L.it >= (p.planar ? o.max_iter_planar : o.max_iter)) ? ST_MAXIT : ST_RUNNING;
+    // the next iteration's tests
+    if (L.phase != LANE_RESUMED) {
+        L.it++;
+        if (!stepping) {
+            if (!take) return ST_DEGEN;
+#pragma unroll
+            for (int i = 0; i < M; i++) dmax = real[i] ? fmax(dmax, L.A[Bd::at(i, i)]) : dmax;
+            L.lam = o.lambda0 * dmax;
+            L.Cref = L.C;
+        }
+        if (L.rinf <= o.tol_res) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+        if (L.it == L.win_it) {
+            if (L.C > o.frac * L.Cref) return (L.rinf <= o.tau_root) ? ST_CONV : ST_LOCALMIN;
+            L.Cref = L.C;
+            L.win_it += o.win;
+        }
+    }
+    L.phase = LANE_STEP;
+    return ST_RUNNING;
 }
 
 // ------------------------------------------------------------------ persistent LM kernel
@@ -249,20 +192,19 @@ __device__ __forceinline__ int lm_step_param(const SceneT<T> &sc, const PathIn<T
 // larger variants made it slower (0.516 -> 0.556 ms).
 template <typename T, int N, int FORM, int CODE>
 __device__ __forceinline__ int lm_step_fixed(const SceneT<T> &sc, const PathIn<T, N> &p,
-                                             Lane<T, N, FORM ? 2 * N : 3 * N> &L, const LMOpts<T> &o)
+                                             Lane<T, N, FORM> &L, const LMOpts<T> &o)
 {
     PathIn<T, N> q = p;
 #pragma unroll
     for (int k = 0; k < N; k++) q.ty[k] = (CODE >> (2 * k)) & 3;
     q.planar = true;  // planes and straight edges: no refracting facet
-    if constexpr (FORM) return lm_step_param<T, N, false>(sc, q, L, o);
-    else return lm_step<T, N, false>(sc, q, L, o);
+    return lm_pass<T, N, FORM, false>(sc, q, L, o);
 }
 
 // The fixed-type step for the planar sequence `code` of orders 1-3.
 template <typename T, int N, int FORM>
 __device__ __forceinline__ int lm_step_uniform(int code, const SceneT<T> &sc, const PathIn<T, N> &p,
-                                               Lane<T, N, FORM ? 2 * N : 3 * N> &L, const LMOpts<T> &o)
+                                               Lane<T, N, FORM> &L, const LMOpts<T> &o)
 {
 #define MPT_FIXED(c) \
     case c: return lm_step_fixed<T, N, FORM, c>(sc, p, L, o);
@@ -361,7 +303,7 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
     o.stat_win = FB ? 0 : kp.o.stat_win;
     o.stat_tol = (T)kp.o.stat_tol;
 
-    Lane<T, N, D> L;
+    Lane<T, N, FORM> L;
     PathIn<T, N> p;
     int slot = 0, code = 0;
     int ridx = 0;       // the path's state row (FP32) or solve id
@@ -443,7 +385,7 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
                     L.it = 0;
                     L.stat = 0;
                     L.lam = T(0);
-                    L.keep = false;
+                    L.phase = LANE_NEW;
                     L.C = T(__builtin_huge_val());
                     L.rinf = T(__builtin_huge_val());
                     L.Cref = L.C;
@@ -533,6 +475,9 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
                         }
                     }
                     it0 = L.it;
+                    if (resume && it0 > 0) L.phase = LANE_RESUMED;  // else parked before its first pass
+                    // the plateau test opens iterations 1 + win, 1 + 2 win, ...
+                    L.win_it = o.win > 0 ? (resume ? (it0 - 1) / o.win : 0) * o.win + o.win + 1 : 0;
                     if constexpr (REFR) {
                         if (active) {
 #pragma unroll
@@ -600,8 +545,7 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
 #pragma unroll
             for (int k = 0; k < N; k++) p.ty[k] = (code >> (2 * k)) & 3;
             if constexpr (!REFR) p.planar = (code & 0x2AA) == 0;
-            if constexpr (FORM) st = lm_step_param<T, N, REFR>(sc, p, L, o);
-            else st = lm_step<T, N, REFR>(sc, p, L, o);
+            st = lm_pass<T, N, FORM, REFR>(sc, p, L, o);
         }
         if (active && st != ST_RUNNING) {
             active = false;
@@ -612,28 +556,29 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
 }
 
 // Waves per SIMD each kernel is compiled for: as many as its registers allow
-// without spills (VGPRs per lane of orders 1-5: FP32 parametric 93 / 141 / 198
-// / 160 / 191, implicit 118 / 159 / 218 / 189 / 225; FP64 parametric 122 / 182 /
-// 223 / 261 / 301, implicit 142 / 220 / 280 / 344 / 400).
+// without spills (VGPRs per lane of orders 1-5: FP32 parametric 93 / 126 / 168 /
+// 198 / 228, implicit 99 / 149 / 220 / 279 / 340; FP64 parametric 136 / 218 / 298 /
+// 354 / 411, implicit 163 / 282 / 409 / 512 / 512, the last two with spills).
+// Two sets of normal equations are alive while a trial point is assembled; the
+// implicit orders 4 and 5 pay for that with one wave instead of two, and
+// still gain: 91,571 paths of random starts 0.94 ms at one wave, 1.78 at two
+// with 103 spilled registers, 1.24 at two with the trial's cost evaluated alone.
 template <int MODE, int N, int FORM = 0> struct Occ { static constexpr int W = 1; };
 template <> struct Occ<MODE_FP32, 1, 0> { static constexpr int W = 4; };
 template <> struct Occ<MODE_FP32, 2, 0> { static constexpr int W = 3; };
 template <> struct Occ<MODE_FP32, 3, 0> { static constexpr int W = 2; };
-template <> struct Occ<MODE_FP32, 4, 0> { static constexpr int W = 2; };
-template <> struct Occ<MODE_FP32, 5, 0> { static constexpr int W = 2; };
+
 template <> struct Occ<MODE_PLAIN64, 1, 0> { static constexpr int W = 3; };
-template <> struct Occ<MODE_PLAIN64, 2, 0> { static constexpr int W = 2; };
 template <> struct Occ<MODE_FP32, 1, 1> { static constexpr int W = 4; };
 template <> struct Occ<MODE_FP32, 2, 1> { static constexpr int W = 3; };
 template <> struct Occ<MODE_FP32, 3, 1> { static constexpr int W = 2; };
-template <> struct Occ<MODE_FP32, 4, 1> { static constexpr int W = 3; };
+template <> struct Occ<MODE_FP32, 4, 1> { static constexpr int W = 2; };
 template <> struct Occ<MODE_FP32, 5, 1> { static constexpr int W = 2; };
-template <> struct Occ<MODE_PLAIN64, 1, 1> { static constexpr int W = 4; };
+template <> struct Occ<MODE_PLAIN64, 1, 1> { static constexpr int W = 3; };
 template <> struct Occ<MODE_PLAIN64, 2, 1> { static constexpr int W = 2; };
-template <> struct Occ<MODE_PLAIN64, 3, 1> { static constexpr int W = 2; };
 
-// The mixed-order kernels (and the one of orders 1-3).
-template <int MODE, int FORM> struct OccAll { static constexpr int W = (MODE == MODE_FP32) ? 2 : 1; };
+// The mixed-order kernels: order 5's.
+template <int MODE, int FORM> struct OccAll { static constexpr int W = (MODE == MODE_FP32 && FORM) ? 2 : 1; };
 
 // Scene records staged in LDS by every block of a persistent launch (the
 // whole scene: 651 primitives x 18 floats = 47 KB for the street canyon).

@@ -28,8 +28,7 @@ struct mpt_ctx {
     size_t lds_max = 65536;  // dynamic LDS a block may use
     // scene
     double *raw = nullptr, *rec64 = nullptr, *wd = nullptr, *sd = nullptr, *rfd = nullptr;
-    float *rec32 = nullptr, *occ = nullptr;
-    size_t occ_cap = 0;
+    float *rec32 = nullptr;
     size_t scene_cap = 0, raw_cap = 0, wd_cap = 0, sd_cap = 0, rfd_cap = 0;
     // candidate generation: sample points, their counts, path counts / offsets
     double *samp = nullptr;
@@ -199,7 +198,6 @@ mpt_status mpt_destroy(mpt_ctx *c)
     hipFree(c->raw);
     hipFree(c->rec64);
     hipFree(c->rec32);
-    hipFree(c->occ);
     hipFree(c->wd);
     hipFree(c->sd);
     hipFree(c->rfd);
@@ -308,10 +306,11 @@ mpt_status mpt_scene_upload(mpt_ctx *c, const mpt_scene_desc *d)
     mpt_status st;
     if ((st = ensure(c, (void **)&c->raw, &c->raw_cap, raw_n, sizeof(double)))) return st;
     size_t cap64 = c->scene_cap, cap32 = c->scene_cap;
-    if ((st = ensure(c, (void **)&c->rec64, &cap64, n_all * kRec, sizeof(double)))) return st;
-    if ((st = ensure(c, (void **)&c->rec32, &cap32, n_all * kRec, sizeof(float)))) return st;
+    // the FP64 records, then the occluders' boxes (8 floats each)
+    const size_t n_rec = n_all * (kRec + 4);
+    if ((st = ensure(c, (void **)&c->rec64, &cap64, n_rec, sizeof(double)))) return st;
+    if ((st = ensure(c, (void **)&c->rec32, &cap32, n_rec, sizeof(float)))) return st;
     c->scene_cap = cap64 < cap32 ? cap64 : cap32;
-    if ((st = ensure(c, (void **)&c->occ, &c->occ_cap, ((size_t)np + nq) * 8, sizeof(float)))) return st;
     std::vector<double> host(raw_n ? raw_n : 1);
     size_t o = 0;
     memcpy(host.data() + o, d->planes, (size_t)np * 13 * 8), o += (size_t)np * 13;
@@ -335,7 +334,7 @@ mpt_status mpt_scene_upload(mpt_ctx *c, const mpt_scene_desc *d)
     s.side = sides ? c->sd : nullptr;
     s.rec64 = c->rec64;
     s.rec32 = c->rec32;
-    s.occ = c->occ;
+    s.occ = (const float *)(c->rec64 + n_all * kRec);
     s.n_pl = np;
     s.n_pl_ln = np + nl;
     s.n_pl_ln_q = np + nl + nq;

@@ -673,12 +673,15 @@ __host__ __device__ __forceinline__ bool eval_cost_param(const SceneT<T> &sc, co
 // with respect to the parameters of interactions k-1, k, k+1 by the chain
 // rule (Tp, Tk, Tn: dX/dU of the three), added to the band and the gradient.
 // K: parameters of interaction k itself (1 for an edge, whose second slot is
-// a placeholder with a zero column).
+// a placeholder with a zero column), Kp and Kn: those of its neighbours to
+// be added (2 where their types are not known to the compiler: a column of
+// zeros then, which changes no sum).
 template <typename T, int N, int R, int K>
 __host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3], const T (*Jk)[3], const T (*Jn)[3],
                                                         const T (*Tp)[2], const T (*Tk)[2], const T (*Tn)[2],
-                                                        const T *u, T *A, T *g, T &C, T &rinf)
+                                                        int Kp, int Kn, const T *u, T *A, T *g, T &C, T &rinf)
 {
+    const int par[3] = {Kp, K, Kn};
 #pragma unroll
     for (int row = 0; row < R; row++) {
         C += u[row] * u[row];
@@ -689,9 +692,9 @@ __host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3],
             T vp = T(0), vk = T(0), vn = T(0);
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                if (k > 0) vp += Jp[row][j] * Tp[j][c];
+                if (k > 0 && c < Kp) vp += Jp[row][j] * Tp[j][c];
                 if (c < K) vk += Jk[row][j] * Tk[j][c];
-                if (k + 1 < N) vn += Jn[row][j] * Tn[j][c];
+                if (k + 1 < N && c < Kn) vn += Jn[row][j] * Tn[j][c];
             }
             jr[c] = vp;
             jr[2 + c] = vk;
@@ -703,7 +706,7 @@ __host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3],
             if (Bi < 0 || Bi >= N) continue;
 #pragma unroll
             for (int ci = 0; ci < 2; ci++) {
-                if (bi == 1 && ci >= K) continue;
+                if (ci >= par[bi]) continue;
                 const int gi = 2 * Bi + ci;
                 g[gi] += jr[2 * bi + ci] * u[row];
 #pragma unroll
@@ -712,7 +715,7 @@ __host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3],
                     if (Bj < 0 || Bj >= N) continue;
 #pragma unroll
                     for (int cj = 0; cj < 2; cj++) {
-                        if (bj == 1 && cj >= K) continue;
+                        if (cj >= par[bj]) continue;
                         const int gj = 2 * Bj + cj;
                         if (gj > gi) continue;
                         A[Band<N, 2>::at(gi, gj)] += jr[2 * bi + ci] * jr[2 * bj + cj];
@@ -725,8 +728,9 @@ __host__ __device__ __forceinline__ void add_param_rows(int k, const T (*Jp)[3],
 
 // Normal equations of the parametric form: band of J^T J (2 x 2 blocks) and
 // J^T I, with J = dI/dX . dX/dU by the chain rule, and whether every point
-// stays in the guard box.
-template <typename T, int N, bool REFR = true>
+// stays in the guard box.  FIXED: the path's types are known to the compiler
+// (the columns of the edges' placeholders are left out).
+template <typename T, int N, bool REFR = true, bool FIXED = false>
 __host__ __device__ __forceinline__ bool assemble_param(const SceneT<T> &sc, const PathIn<T, N> &p, const T *U, T *A,
                                                T *g, T &C, T &rinf, bool &guard)
 {
@@ -761,14 +765,18 @@ __host__ __device__ __forceinline__ bool assemble_param(const SceneT<T> &sc, con
         const Dirs<T> D = directions(Xp, Xw[k % 3], Xn);
         const T *r = sc.rec + (size_t)p.id[k] * kRec;
         ok = ok && D.valid;
+        const int Kp = (FIXED && k > 0 && !is_surface(p.ty[k > 0 ? k - 1 : 0])) ? 1 : 2;
+        const int Kn = (FIXED && k + 1 < N && !is_surface(p.ty[k + 1 < N ? k + 1 : 0])) ? 1 : 2;
         if (is_surface(p.ty[k])) {
             T u[4], Jp[3][3], Jk[3][3], Jn[3][3], Jg[3];
             ok = surface_rows<T, true, REFR>(p.ty[k], r, D, Xw[k % 3], u, Jp, Jk, Jn, Jg) && ok;
-            add_param_rows<T, N, 3, 2>(k, Jp, Jk, Jn, Tw[(k + 2) % 3], Tw[k % 3], Tw[(k + 1) % 3], u, A, g, C, rinf);
+            add_param_rows<T, N, 3, 2>(k, Jp, Jk, Jn, Tw[(k + 2) % 3], Tw[k % 3], Tw[(k + 1) % 3], Kp, Kn, u, A, g, C,
+                                        rinf);
         } else {
             T u[3], Jp[1][3], Jk[1][3], Jn[1][3], Jo[2][3];
             ok = edge_rows<T, true>(p.ty[k], r, D, Xw[k % 3], u, Jp[0], Jk[0], Jn[0], Jo) && ok;
-            add_param_rows<T, N, 1, 1>(k, Jp, Jk, Jn, Tw[(k + 2) % 3], Tw[k % 3], Tw[(k + 1) % 3], u, A, g, C, rinf);
+            add_param_rows<T, N, 1, 1>(k, Jp, Jk, Jn, Tw[(k + 2) % 3], Tw[k % 3], Tw[(k + 1) % 3], Kp, Kn, u, A, g, C,
+                                        rinf);
         }
     }
     return ok;
@@ -776,27 +784,31 @@ __host__ __device__ __forceinline__ bool assemble_param(const SceneT<T> &sc, con
 
 // In-place banded Cholesky of the packed lower band; false if not SPD.  The
 // diagonal slots receive the INVERSE of L's diagonal (the solves multiply).
+// real (or null: all): the unknowns; the rows and columns of the others, an
+// identity's, are not touched.
 template <typename T, int N, int B = 3>
-__host__ __device__ __forceinline__ bool chol_band(T *A)
+__host__ __device__ __forceinline__ bool chol_band(T *A, const bool *real = nullptr)
 {
     constexpr int M = B * N;
     bool ok = true;
 #pragma unroll
     for (int j = 0; j < M; j++) {
+        if (real && !real[j]) continue;
         T d = A[Band<N, B>::at(j, j)];
 #pragma unroll
         for (int k = 0; k < j; k++)
-            if (Band<N, B>::in(j, k)) d -= A[Band<N, B>::at(j, k)] * A[Band<N, B>::at(j, k)];
+            if (Band<N, B>::in(j, k) && !(real && !real[k])) d -= A[Band<N, B>::at(j, k)] * A[Band<N, B>::at(j, k)];
         ok = ok && (d > T(0));
         const T inv = drsqrt(d > T(0) ? d : T(1));
         A[Band<N, B>::at(j, j)] = inv;
 #pragma unroll
         for (int i = j + 1; i < M; i++) {
-            if (!Band<N, B>::in(i, j)) continue;
+            if (!Band<N, B>::in(i, j) || (real && !real[i])) continue;
             T v = A[Band<N, B>::at(i, j)];
 #pragma unroll
             for (int k = 0; k < j; k++)
-                if (Band<N, B>::in(i, k) && Band<N, B>::in(j, k)) v -= A[Band<N, B>::at(i, k)] * A[Band<N, B>::at(j, k)];
+                if (Band<N, B>::in(i, k) && Band<N, B>::in(j, k) && !(real && !real[k]))
+                    v -= A[Band<N, B>::at(i, k)] * A[Band<N, B>::at(j, k)];
             A[Band<N, B>::at(i, j)] = v * inv;
         }
     }
@@ -807,25 +819,27 @@ __host__ __device__ __forceinline__ bool chol_band(T *A)
 // Returns |y|^2 of the forward substitution L y = b: with b = -g this is
 // -g^T x, the decrease the damped model predicts for the step x.
 template <typename T, int N, int B = 3>
-__host__ __device__ __forceinline__ T chol_solve_band(const T *L, T *b)
+__host__ __device__ __forceinline__ T chol_solve_band(const T *L, T *b, const bool *real = nullptr)
 {
     constexpr int M = B * N;
     T ysq = T(0);
 #pragma unroll
     for (int i = 0; i < M; i++) {
+        if (real && !real[i]) continue;  // b[i] is 0
         T v = b[i];
 #pragma unroll
         for (int k = 0; k < i; k++)
-            if (Band<N, B>::in(i, k)) v -= L[Band<N, B>::at(i, k)] * b[k];
+            if (Band<N, B>::in(i, k) && !(real && !real[k])) v -= L[Band<N, B>::at(i, k)] * b[k];
         b[i] = v * L[Band<N, B>::at(i, i)];
         ysq += b[i] * b[i];
     }
 #pragma unroll
     for (int i = M - 1; i >= 0; i--) {
+        if (real && !real[i]) continue;
         T v = b[i];
 #pragma unroll
         for (int k = i + 1; k < M; k++)
-            if (Band<N, B>::in(k, i)) v -= L[Band<N, B>::at(k, i)] * b[k];
+            if (Band<N, B>::in(k, i) && !(real && !real[k])) v -= L[Band<N, B>::at(k, i)] * b[k];
         b[i] = v * L[Band<N, B>::at(i, i)];
     }
     return ysq;

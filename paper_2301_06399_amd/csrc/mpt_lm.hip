@@ -70,7 +70,8 @@ __device__ __forceinline__ T tenth(T x)
 // planar paths, where the longest chains bound it).
 // Returns ST_RUNNING or the final status.  REFR: the scene has refracting
 // facets (their rows are compiled in).
-template <typename T, int N, int FORM, bool REFR>
+// FIXED: p.ty is known to the compiler.
+template <typename T, int N, int FORM, bool REFR, bool FIXED = false>
 __device__ __forceinline__ int lm_pass(const SceneT<T> &sc, const PathIn<T, N> &p, Lane<T, N, FORM> &L,
                                        const LMOpts<T> &o)
 {
@@ -100,12 +101,12 @@ __device__ __forceinline__ int lm_pass(const SceneT<T> &sc, const PathIn<T, N> &
                 else if (FORM) F[Bd::at(i, i)] = real[i] ? a + L.lam * fmax(a, floor_d) : T(1);
                 else F[Bd::at(i, i)] = a + L.lam * fmax(a, floor_d);
             }
-        go = chol_band<T, N, B>(F);
+        go = chol_band<T, N, B>(F, FIXED ? real : nullptr);
         if (go) {
             T d[M];
 #pragma unroll
             for (int i = 0; i < M; i++) d[i] = -L.g[i];
-            const T pred = chol_solve_band<T, N, B>(F, d);  // d <- dx; pred = -g^T dx
+            const T pred = chol_solve_band<T, N, B>(F, d, FIXED ? real : nullptr);  // d <- dx; pred = -g^T dx
             if (o.stat_win > 0 && p.planar) {
                 // planes and straight edges: the descent has stalled when the damped
                 // model predicts too small a decrease several iterations in a row
@@ -128,7 +129,8 @@ __device__ __forceinline__ int lm_pass(const SceneT<T> &sc, const PathIn<T, N> &
         T A1[LT::S], g1[M], C1, r1;
         if constexpr (FORM) {
             bool guard;
-            take = assemble_param<T, N, REFR>(sc, p, xt, A1, g1, C1, r1, guard) && (!stepping || (guard && C1 < L.C));
+            take = assemble_param<T, N, REFR, FIXED>(sc, p, xt, A1, g1, C1, r1, guard) &&
+                   (!stepping || (guard && C1 < L.C));
         } else {
             take = assemble<T, N, REFR>(sc, p, xt, A1, g1, C1, r1) && (!stepping || C1 < L.C);
         }
@@ -188,8 +190,10 @@ __device__ __forceinline__ int lm_pass(const SceneT<T> &sc, const PathIn<T, N> &
 // or select is left in the code.  Bins are type-homogeneous, so most waves
 // hold one planar sequence and run one of these variants only.  Used by the
 // parametric FP32 kernel: there it shortens an iteration (street canyon LM
-// stage 0.550 -> 0.484 ms, room 0.157 -> 0.119 ms); the implicit kernel's
-// larger variants made it slower (0.516 -> 0.556 ms).
+// stage 0.550 -> 0.484 ms, room 0.157 -> 0.119 ms, and without the columns of
+// the edges' placeholder parameters, which the compiler may not drop by
+// itself, 0.295 -> 0.278 and 0.086 -> 0.080 ms); the implicit kernel's larger
+// variants made it slower (0.516 -> 0.556 ms).
 template <typename T, int N, int FORM, int CODE>
 __device__ __forceinline__ int lm_step_fixed(const SceneT<T> &sc, const PathIn<T, N> &p,
                                              Lane<T, N, FORM> &L, const LMOpts<T> &o)
@@ -198,7 +202,7 @@ __device__ __forceinline__ int lm_step_fixed(const SceneT<T> &sc, const PathIn<T
 #pragma unroll
     for (int k = 0; k < N; k++) q.ty[k] = (CODE >> (2 * k)) & 3;
     q.planar = true;  // planes and straight edges: no refracting facet
-    return lm_pass<T, N, FORM, false>(sc, q, L, o);
+    return lm_pass<T, N, FORM, false, true>(sc, q, L, o);
 }
 
 // The fixed-type step for the planar sequence `code` of orders 1-3.

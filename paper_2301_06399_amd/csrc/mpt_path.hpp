@@ -69,13 +69,65 @@ __device__ inline bool in_guard(const SceneDev &s, const double *X, int n)
     return ok;
 }
 
+// A packed record in registers: what a straight edge has (its six first
+// values), and of the other types the rest.  The kernels before and after the
+// solver read the records of random objects, a cache line per lane, and are
+// bound by those accesses: each record is read once, in 16-byte loads, instead
+// of a few values wherever a branch needs them.
+typedef double f64x2 __attribute__((ext_vector_type(2), aligned(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(8), may_alias));
+typedef float f32x2 __attribute__((ext_vector_type(2), aligned(8), may_alias));
+
+template <int J0, int J1>  // r[2 J0 .. 2 J1 - 1]
+__device__ __forceinline__ void load_pairs(const double *rec, double *r)
+{
+#pragma unroll
+    for (int j = J0; j < J1; j++) {
+        const f64x2 v = reinterpret_cast<const f64x2 *>(rec)[j];
+        r[2 * j] = v[0];
+        r[2 * j + 1] = v[1];
+    }
+}
+
+__device__ __forceinline__ void load_record(const double *rec, int id, int ty, double *r)
+{
+    const double *p = rec + (size_t)id * kRec;
+    load_pairs<0, 3>(p, r);
+    if (ty != TL) load_pairs<3, kRec / 2>(p, r);
+}
+
+__device__ __forceinline__ void load_record(const float *rec, int id, int ty, float *r)
+{
+    const float *p = rec + (size_t)id * kRec;
+    const f32x4 a = *(const f32x4 *)p;
+    const f32x2 b = *(const f32x2 *)(p + 4);
+    r[0] = a[0], r[1] = a[1], r[2] = a[2], r[3] = a[3], r[4] = b[0], r[5] = b[1];
+    if (ty == TL) return;
+#pragma unroll
+    for (int j = 6; j < kRec; j += 4) {
+        const f32x4 v = *(const f32x4 *)(p + j);
+#pragma unroll
+        for (int q = 0; q < 4; q++) r[j + q] = v[q];
+    }
+}
+
+// (double)a / (double)b for 1 <= a <= b <= 6 without the division.
+__device__ __forceinline__ double small_ratio(int a, int b)
+{
+    double q = (double)a / 6.0;
+    q = b == 5 ? (double)a / 5.0 : q;
+    q = b == 4 ? (double)a / 4.0 : q;
+    q = b == 3 ? (double)a / 3.0 : q;
+    return b == 2 ? (double)a / 2.0 : q;
+}
+
 // Fraction along TX -> RX of the straight-line start of interaction k of N:
 // k+1 over N+1, or, on a refracting facet (which the ray crosses), the
 // point where the segment meets its plane when it does.
 __device__ __forceinline__ double line_fraction(int ty, const double *r, const double *tx, const double *rx, int k,
                                                 int N)
 {
-    double a = (double)(k + 1) / (double)(N + 1);
+    double a = small_ratio(k + 1, N + 1);
     if (ty == TP && r[16] > 0.0) {
         const double den = r[0] * (rx[0] - tx[0]) + r[1] * (rx[1] - tx[1]) + r[2] * (rx[2] - tx[2]);
         const double c = (den != 0.0) ? (r[3] - (r[0] * tx[0] + r[1] * tx[1] + r[2] * tx[2])) / den : -1.0;
@@ -98,45 +150,60 @@ template <> struct ModeT<MODE_FALLBACK64> { using T = double; };
 // it, off it by more than 1e-9 m), and the two sides differ, no root exists.
 // Plain IEEE FP64 without contraction: an exactly parallel pair is found
 // parallel whatever the scaling of its normals.
-__device__ __forceinline__ bool const_side(const SceneDev &s, int id, int ty, const double *n, const double *o,
-                                           double &side)
+__device__ __forceinline__ double plane_side(const double *n, const double *o, const double *x)
 {
 #pragma clang fp contract(off)
-    const double *r = s.rec64 + (size_t)id * kRec;
+    return n[0] * (x[0] - o[0]) + n[1] * (x[1] - o[1]) + n[2] * (x[2] - o[2]);
+}
+
+// r: the first seven values of the other object's record.
+__device__ __forceinline__ bool const_side(const double *r, int ty, const double *n, const double *o, double &side)
+{
+#pragma clang fp contract(off)
     if (ty == TP) {
         // normals parallel: every point of the other plane is n.(o' - o) off
         if (n[1] * r[2] - n[2] * r[1] != 0.0 || n[2] * r[0] - n[0] * r[2] != 0.0 || n[0] * r[1] - n[1] * r[0] != 0.0)
             return false;
-        side = n[0] * (r[4] - o[0]) + n[1] * (r[5] - o[1]) + n[2] * (r[6] - o[2]);
+        side = plane_side(n, o, r + 4);
     } else if (ty == TL) {
         if (n[0] * r[3] + n[1] * r[4] + n[2] * r[5] != 0.0) return false;
-        side = n[0] * (r[0] - o[0]) + n[1] * (r[1] - o[1]) + n[2] * (r[2] - o[2]);
+        side = plane_side(n, o, r);
     } else {
         return false;
     }
     return fabs(side) > 1e-9;
 }
 
-__device__ __forceinline__ bool sides_forbid_root(const SceneDev &s, int n, const int *id, const int *ty,
-                                                  const double *rx)
+// The certificate over the objects of a path, given one after the other.
+struct Sides {
+    double r[7], a;  // the last object's record and, of a mirror, the side the ray comes from
+    int ty;
+    bool mirror, known, forbid;
+};
+
+__device__ __forceinline__ bool opposite(double a, double b) { return (a < 0.0 && b > 0.0) || (a > 0.0 && b < 0.0); }
+
+__device__ __forceinline__ void sides_next(Sides &c, int k, int n, int ty, const double *r, const double *tx,
+                                           const double *rx)
 {
-#pragma clang fp contract(off)
-    bool forbid = false;
-#pragma unroll
-    for (int k = 0; k < kMaxN; k++) {
-        if (k >= n || ty[k] != TP) continue;
-        const double *r = s.rec64 + (size_t)id[k] * kRec;
-        if (r[16] > 0.0) continue;  // a refracting facet passes the ray to its other side
-        const double nv[3] = {r[0], r[1], r[2]}, o[3] = {r[4], r[5], r[6]};
-        double a = 0.0, b = 0.0;
-        bool ka = true, kb = true;
-        if (k == 0) a = nv[0] * (s.tx[0] - o[0]) + nv[1] * (s.tx[1] - o[1]) + nv[2] * (s.tx[2] - o[2]);
-        else ka = const_side(s, id[k > 0 ? k - 1 : 0], ty[k > 0 ? k - 1 : 0], nv, o, a);
-        if (k == n - 1) b = nv[0] * (rx[0] - o[0]) + nv[1] * (rx[1] - o[1]) + nv[2] * (rx[2] - o[2]);
-        else kb = const_side(s, id[k + 1 < kMaxN ? k + 1 : k], ty[k + 1 < kMaxN ? k + 1 : k], nv, o, b);
-        forbid = forbid || (ka && kb && ((a < 0.0 && b > 0.0) || (a > 0.0 && b < 0.0)));
+    double a = 0.0, b = 0.0;
+    if (k == 0) c.forbid = c.mirror = false;
+    if (c.mirror && const_side(r, ty, c.r, c.r + 4, b)) c.forbid = c.forbid || (c.known && opposite(c.a, b));
+    // a refracting facet passes the ray to its other side
+    const bool mirror = ty == TP && !(r[16] > 0.0);
+    bool known = true;
+    if (mirror) {
+        if (k == 0) a = plane_side(r, r + 4, tx);
+        else known = const_side(c.r, c.ty, r, r + 4, a);
+        if (k == n - 1) c.forbid = c.forbid || (known && opposite(a, plane_side(r, r + 4, rx)));
     }
-    return forbid;
+    c.mirror = mirror;
+    c.known = known;
+    c.a = a;
+    c.ty = ty;
+#pragma unroll
+    for (int j = 0; j < 7; j++)
+        if (j < 6 || ty != TL) c.r[j] = r[j];
 }
 
 // True when some point lies outside its object's finite extent by more
@@ -185,11 +252,14 @@ __device__ __forceinline__ int start_path(const KParams &kp, int64_t sid, int n,
                                           const double *rx, const double *sh, const double *x0, T *L)
 {
     bool ok = true, inside = true;
+    Sides sides;
     const bool rnd = kp.o.init == INIT_RANDOM;
 #pragma unroll
     for (int k = 0; k < kMaxN; k++) {
         if (k >= n) continue;
-        const double *r64 = kp.s.rec64 + (size_t)id[k] * kRec;
+        double r64[kRec];
+        load_record(kp.s.rec64, id[k], ty[k], r64);
+        if constexpr (MODE != MODE_FALLBACK64) sides_next(sides, k, n, ty[k], r64, kp.s.tx, rx);
         double Xk[3];
         if (x0) {
 #pragma unroll
@@ -236,7 +306,7 @@ __device__ __forceinline__ int start_path(const KParams &kp, int64_t sid, int n,
         for (int i = 0; i < 3; i++) inside = inside && (Xk[i] >= kp.s.glo[i]) && (Xk[i] <= kp.s.ghi[i]);
     }
     int st = !ok ? ST_BAD : !inside ? ST_DIVERGED : ST_RUNNING;
-    if (MODE != MODE_FALLBACK64 && st == ST_RUNNING && sides_forbid_root(kp.s, n, id, ty, rx)) st = ST_LOCALMIN;
+    if (MODE != MODE_FALLBACK64 && st == ST_RUNNING && sides.forbid) st = ST_LOCALMIN;
     return st;
 }
 
@@ -254,8 +324,9 @@ __device__ __forceinline__ void world_points(const T *rec, int n, const int *id,
             continue;
         }
         if constexpr (FORM) {
-            T Xk[3], Tm[3][2];
-            param_map<T>(ty[k], rec + (size_t)id[k] * kRec, L[2 * k], L[2 * k + 1], Xk, Tm);
+            T Xk[3], Tm[3][2], r[kRec];
+            load_record(rec, id[k], ty[k], r);
+            param_map<T>(ty[k], r, L[2 * k], L[2 * k + 1], Xk, Tm);
 #pragma unroll
             for (int i = 0; i < 3; i++) Xw[3 * k + i] = (double)Xk[i] + sh[i];
         } else {
@@ -292,7 +363,6 @@ enum : int { RW_C = 16, RW_IT = 18, RW_ST = 19, RW_RX = 20, RW_CODE = 23, RW_ID 
 
 typedef float f32a __attribute__((may_alias));
 typedef int i32a __attribute__((may_alias));
-typedef float f32x4 __attribute__((ext_vector_type(4), aligned(8), may_alias));
 
 // The state row of bin slot `slot` / solve `sid`.
 __device__ __forceinline__ f32a *state_row(const KParams &kp, int64_t slot, int64_t sid)
@@ -300,12 +370,77 @@ __device__ __forceinline__ f32a *state_row(const KParams &kp, int64_t slot, int6
     return kp.rows ? (f32a *)kp.rows + slot * kState : (f32a *)(kp.out.x + sid * kRow);
 }
 
+// Rows of 128 bytes (state and point rows) between a wave's lanes, one row
+// each, and memory, through LDS.  A lane that stores its own row touches one
+// line in each of eight instructions, 64 lines apiece, which the memory pipe
+// takes one by one and hands on as eight partial lines; with eight lanes on a
+// row an instruction moves eight whole lines.  In LDS a row takes 36 words, so
+// that the lanes' 16-byte accesses spread over the banks, and its address
+// follows it.  All lanes of the wave call these together.
+constexpr int kRowWords = 36;
+constexpr int kWaveRows = 64 * kRowWords;  // words of LDS per wave
+
+typedef float f32x4l __attribute__((ext_vector_type(4), aligned(16), may_alias));
+typedef uint64_t u64a __attribute__((may_alias));
+
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Stores the lanes' rows, each at its dst (null: none).
+__device__ __forceinline__ void rows_store(float *w, void *dst)
+{
+    const int lane = __lane_id(), part = (lane & 7) * 4;
+    *(u64a *)(w + lane * kRowWords + 32) = (uint64_t)dst;
+    wave_sync();
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const float *row = w + (j * 8 + (lane >> 3)) * kRowWords;
+        float *p = (float *)*(const u64a *)(row + 32);
+        const f32x4l v = *(const f32x4l *)(row + part);
+        if (p) *(f32x4 *)(p + part) = v;
+    }
+    wave_sync();
+}
+
+// Loads the lanes' rows from src (a readable row in every lane).
+__device__ __forceinline__ void rows_load(float *w, const void *src)
+{
+    const int lane = __lane_id(), part = (lane & 7) * 4;
+    *(u64a *)(w + lane * kRowWords + 32) = (uint64_t)src;
+    wave_sync();
+    f32x4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const float *p = (const float *)*(const u64a *)(w + (j * 8 + (lane >> 3)) * kRowWords + 32);
+        v[j] = *(const f32x4 *)(p + part);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; j++) *(f32x4l *)(w + (j * 8 + (lane >> 3)) * kRowWords + part) = v[j];
+    wave_sync();
+}
+
+// A path's point row (write_row) in LDS.
+template <int N>
+__device__ __forceinline__ void stage_row(float *mine, const double *X)
+{
+    f64x2 *row = (f64x2 *)mine;
+#pragma unroll
+    for (int j = 0; j < kRow; j += 2)
+        row[j / 2] = f64x2{j < 3 * N ? X[j < 3 * N ? j : 0] : 0.0, j + 1 < 3 * N ? X[j + 1 < 3 * N ? j + 1 : 0] : 0.0};
+}
+
 // The start of solve `sid` (bin slot `slot`): its unknowns where the solver
 // reads them, status ST_RUNNING; or, when no iteration is to run, its
 // results: the start points as the solver holds them (zeros for bad input).
+// Called by all lanes of a wave, live: the lane has a path; w: kWaveRows words
+// of LDS for the wave.
 template <int MODE, int FORM>
-__device__ __forceinline__ void begin_path(const KParams &kp, int64_t slot, int64_t sid, int n, const int *id,
-                                           const int *ty, const double *rx, const double *x0)
+__device__ __forceinline__ void begin_path(const KParams &kp, bool live, int64_t slot, int64_t sid, int n,
+                                           const int *id, const int *ty, const double *rx, const double *x0,
+                                           float *w)
 {
     using T = typename ModeT<MODE>::T;
     constexpr int D = (FORM ? 2 : 3) * kMaxN;
@@ -315,36 +450,47 @@ __device__ __forceinline__ void begin_path(const KParams &kp, int64_t slot, int6
     T L[(D + 3) / 4 * 4];
 #pragma unroll
     for (int j = 0; j < (D + 3) / 4 * 4; j++) L[j] = T(0);
-    const int st = start_path<MODE, FORM>(kp, sid, n, id, ty, rx, sh, x0, L);
-    double *out = kp.out.x + (size_t)sid * kRow;
-    kp.out.status[sid] = (uint8_t)st;
-    if (st == ST_RUNNING) {
-        if constexpr (MODE == MODE_FP32) {
-            f32a *rf = state_row(kp, slot, sid);
+    float *mine = w + __lane_id() * kRowWords;
+    void *dst = nullptr;
+    if (live) {
+        const int st = start_path<MODE, FORM>(kp, sid, n, id, ty, rx, sh, x0, L);
+        dst = kp.out.x + (size_t)sid * kRow;
+        kp.out.status[sid] = (uint8_t)st;
+        if (st != ST_RUNNING) {
+            if (MODE == MODE_FP32 && kp.rows) state_row(kp, slot, sid)[RW_CODE] = __int_as_float(-1);
+            const T *rec = (MODE == MODE_FP32) ? (const T *)kp.s.rec32 : (const T *)kp.s.rec64;
+            double Xs[3 * kMaxN];
+            world_points<kMaxN, FORM, T>(rec, st == ST_BAD ? 0 : n, id, ty, L, sh, Xs);
+            stage_row<kMaxN>(mine, Xs);
+            kp.out.cost[sid] = __builtin_huge_val();
+            kp.out.iters[sid] = 0;
+            if (kp.out.stage) kp.out.stage[sid] = 0;
+        } else if constexpr (MODE == MODE_FP32) {
+            dst = state_row(kp, slot, sid);
             int code = 0;
 #pragma unroll
             for (int k = 0; k < kMaxN; k++) code |= (k < n ? ty[k] : 0) << (2 * k);
+            f32x4l *row = (f32x4l *)mine;
 #pragma unroll
-            for (int j = 0; j < D; j += 4) *(f32x4 *)(rf + j) = f32x4{L[j], L[j + 1], L[j + 2], L[j + 3]};
-            *(f32x4 *)(rf + RW_RX) = f32x4{(T)(rx[0] - sh[0]), (T)(rx[1] - sh[1]), (T)(rx[2] - sh[2]),
-                                           __int_as_float(code)};
-            *(f32x4 *)(rf + RW_ID) = f32x4{__int_as_float(id[0]), __int_as_float(id[1]), __int_as_float(id[2]),
-                                           __int_as_float(id[3])};
-            rf[RW_ID + 4] = __int_as_float(id[4]);
+            for (int j = 0; j < RW_C; j += 4) {
+                f32x4l v;
+#pragma unroll
+                for (int q = 0; q < 4; q++) v[q] = j + q < D ? L[j + q < D ? j + q : 0] : 0.0f;
+                row[j / 4] = v;
+            }
+            row[RW_C / 4] = f32x4l{0.0f, 0.0f, 0.0f, 0.0f};
+            row[RW_RX / 4] = f32x4l{(T)(rx[0] - sh[0]), (T)(rx[1] - sh[1]), (T)(rx[2] - sh[2]), __int_as_float(code)};
+            row[RW_ID / 4] = f32x4l{__int_as_float(id[0]), __int_as_float(id[1]), __int_as_float(id[2]),
+                                    __int_as_float(id[3])};
+            row[RW_ID / 4 + 1] = f32x4l{__int_as_float(id[4]), 0.0f, 0.0f, 0.0f};
         } else {
+            double Xr[3 * kMaxN];
 #pragma unroll
-            for (int j = 0; j < D; j++) out[j] = L[j];
+            for (int j = 0; j < 3 * kMaxN; j++) Xr[j] = j < D ? L[j < D ? j : 0] : 0.0;
+            stage_row<kMaxN>(mine, Xr);
         }
-        return;
     }
-    if (MODE == MODE_FP32 && kp.rows) state_row(kp, slot, sid)[RW_CODE] = __int_as_float(-1);
-    const T *rec = (MODE == MODE_FP32) ? (const T *)kp.s.rec32 : (const T *)kp.s.rec64;
-    double Xs[3 * kMaxN];
-    world_points<kMaxN, FORM, T>(rec, st == ST_BAD ? 0 : n, id, ty, L, sh, Xs);
-    write_row<kMaxN>(out, Xs);
-    kp.out.cost[sid] = __builtin_huge_val();
-    kp.out.iters[sid] = 0;
-    if (kp.out.stage) kp.out.stage[sid] = 0;
+    rows_store(w, dst);
 }
 
 }  // namespace mpt

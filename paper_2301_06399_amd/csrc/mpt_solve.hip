@@ -516,22 +516,32 @@ __device__ __forceinline__ bool served(const KParams &kp, const PathRef &p)
     return net;
 }
 
+// Bound by the memory pipe (78% busy) and the FP64 arithmetic of four types in
+// one wave (52%): each record is read once (load_record) and the rows leave
+// through LDS (rows_store).  16.8 M paths 2.55 -> 1.43 ms, 4.5 M 0.29 -> 0.19 ms.
 template <int MODE, int FORM>
 __global__ void __launch_bounds__(kStartBlock) k_start(KParams kp)
 {
+    __shared__ float rows[kStartBlock / 64 * kWaveRows];
     const int64_t i = (int64_t)blockIdx.x * kStartBlock + threadIdx.x;
-    if (i >= kp.b.n) return;
     int slot = -1;
-    if (kp.rows) {
-        slot = kp.perm[i];
-        if (slot < 0) return;
-    } else if (valid_order(kp.b, i, kp.s.n_all) < 0) {
-        return;
+    bool live = i < kp.b.n;
+    if (live) {
+        if (kp.rows) {
+            slot = kp.perm[i];
+            live = slot >= 0;
+        } else {
+            live = valid_order(kp.b, i, kp.s.n_all) >= 0;
+        }
     }
-    const PathRef p = path_ref(kp.s, kp.b, i);
-    if (served(kp, p)) return;
+    PathRef p;
+    if (live) {
+        p = path_ref(kp.s, kp.b, i);
+        live = !served(kp, p);
+    }
+    if (!__any(live)) return;
     const double *x0 = (kp.o.init == INIT_USER) ? kp.b.x0 + (size_t)i * kRow : nullptr;
-    begin_path<MODE, FORM>(kp, slot, i, p.n, p.id, p.ty, p.rx, x0);
+    begin_path<MODE, FORM>(kp, live, slot, i, p.n, p.id, p.ty, p.rx, x0, rows + (threadIdx.x >> 6) * kWaveRows);
 }
 
 // The learned starts: begin the served paths from the chosen points.
@@ -539,13 +549,24 @@ template <int MODE, int FORM>
 __global__ void __launch_bounds__(kStartBlock) k_learned_begin(KParams kp, const int *__restrict__ list,
                                                                const int *__restrict__ count)
 {
+    __shared__ float rows[kStartBlock / 64 * kWaveRows];
     const int64_t m = list ? (int64_t)*count : kp.b.n;
-    for (int64_t t = (int64_t)blockIdx.x * kStartBlock + threadIdx.x; t < m; t += (int64_t)gridDim.x * kStartBlock) {
-        const int64_t i = list ? list[t] : t;
-        const int slot = kp.rows ? kp.perm[i] : -1;
-        if (kp.rows ? slot < 0 : valid_order(kp.b, i, kp.s.n_all) < 0) continue;
-        const PathRef p = path_ref(kp.s, kp.b, i);
-        begin_path<MODE, FORM>(kp, slot, i, p.n, p.id, p.ty, p.rx, kp.x0_learned + (size_t)i * kRow);
+    // all lanes of a wave go round together
+    for (int64_t t0 = (int64_t)blockIdx.x * kStartBlock + (threadIdx.x & ~63); t0 < m;
+         t0 += (int64_t)gridDim.x * kStartBlock) {
+        const int64_t t = t0 + (threadIdx.x & 63);
+        bool live = t < m;
+        int64_t i = 0;
+        int slot = -1;
+        PathRef p;
+        if (live) {
+            i = list ? list[t] : t;
+            slot = kp.rows ? kp.perm[i] : -1;
+            live = kp.rows ? slot >= 0 : valid_order(kp.b, i, kp.s.n_all) >= 0;
+            if (live) p = path_ref(kp.s, kp.b, i);
+        }
+        begin_path<MODE, FORM>(kp, live, slot, i, p.n, p.id, p.ty, p.rx, kp.x0_learned + (size_t)i * kRow,
+                               rows + (threadIdx.x >> 6) * kWaveRows);
     }
 }
 
@@ -580,6 +601,10 @@ void launch_learned_begin(int mode, int form, const KParams &kp, const int *list
 // points and scalars), routes it, and lists the paths to polish, grouped by
 // order.  One thread per solve in solve order, so that every result is
 // written coalesced and only the state row is gathered (a whole line).
+// The rows go through LDS (rows_load, rows_store): a wave's gather of 64
+// rows and store of 64 others cost the memory pipe eight lines an instruction
+// instead of 64.  16.8 M paths 1.67 -> 1.51 ms (the pipe 73% busy, most of it
+// the records of the extent test), 4.5 M 0.42 -> 0.35 ms.
 //
 // Routing: FP32 end points whose residual is below the gate look like roots
 // and are polished in FP64; the others are final (no path).  FP64 re-solves
@@ -591,28 +616,33 @@ void launch_learned_begin(int mode, int form, const KParams &kp, const int *list
 // refracting facet has a unique root (the optical length is convex), so a
 // descent that ends far from a root goes to the FP64 fallback as well.
 constexpr int kFinBlock = 256;
-// slots per thread at most: a block takes its places in the polish list with
-// one device-wide atomic per order, and atomics on one counter are served one
-// at a time (8192 blocks' atomics took 0.29 ms on the stress workload)
-constexpr int kFinItems = 16;
+// slots per thread at most: a block takes its places in the polish and the
+// fallback lists with one device-wide atomic per order, and atomics on one
+// counter are served one at a time (8192 blocks' atomics took 0.29 ms on the
+// stress workload; an atomic per path to the fallback, 9,200 of them, 0.06 ms of
+// the 0.11 ms on 262,144 paths through glass)
+constexpr int kFinItems = 16;  // four bits of a thread's word each
 
+enum : int { END_POLISH = 0, END_FALLBACK = 1, END_FINAL = 2 };
+
+// One path's end: its results, and the list it goes to.
 template <int FORM, bool REFR>
-__device__ __forceinline__ bool finish_path(const KParams &kp, int64_t i, const int *off, int &order)
+__device__ __forceinline__ int finish_path(const KParams &kp, int64_t i, int &order, float *mine)
 {
     constexpr int D = (FORM ? 2 : 3) * kMaxN;
     const double sh[3] = {kp.s.tx[0], kp.s.tx[1], kp.s.tx[2]};
-    const f32a *rf = state_row(kp, kp.rows ? kp.perm[i] : 0, i);
+    const f32x4l *rf = (const f32x4l *)mine;  // the state row
     float L[(D + 3) / 4 * 4];
 #pragma unroll
     for (int j = 0; j < D; j += 4) {
-        const f32x4 v = *(const f32x4 *)(rf + j);
+        const f32x4l v = rf[j / 4];
 #pragma unroll
         for (int q = 0; q < 4; q++) L[j + q] = v[q];
     }
-    const f32x4 e = *(const f32x4 *)(rf + RW_C);
+    const f32x4l e = rf[RW_C / 4];
     const float C = e[0], rinf = e[1];
     const int it = __float_as_int(e[2]), st = __float_as_int(e[3]);
-    const int late = kp.spill_t > 0 ? it - ((const i32a *)rf)[RW_ID] : 0;
+    const int late = kp.spill_t > 0 ? it - ((const i32a *)mine)[RW_ID] : 0;
     const PathRef p = path_ref(kp.s, kp.b, i);
     order = p.n;
     bool planar = true, refr_path = false;
@@ -623,9 +653,10 @@ __device__ __forceinline__ bool finish_path(const KParams &kp, int64_t i, const 
             planar = planar && (p.ty[k] == TL || (p.ty[k] == TP && !refr));
             refr_path = refr_path || refr;
         }
-    double Xw[3 * kMaxN];
+    // the point row replaces the state row
+    double *Xw = (double *)mine;
     world_points<kMaxN, FORM, float>(kp.s.rec32, p.n, p.id, p.ty, L, sh, Xw);
-    write_row<kMaxN>(kp.out.x + (size_t)i * kRow, Xw);
+    Xw[kRow - 1] = 0.0;
     kp.out.cost[i] = (double)C;
     kp.out.iters[i] = it;
     if (kp.out.stage) {
@@ -675,53 +706,50 @@ __device__ __forceinline__ bool finish_path(const KParams &kp, int64_t i, const 
                : (st == ST_MAXIT)                             ? ROUTE_POLISH_MAXIT
                                                               : ROUTE_POLISH_LOCALMIN;
     } else if (to_fb && kp.o.fallback) {
-        const int q = atomicAdd(&kp.fb_cnt[p.n - 1], 1);
-        kp.fb_list[off[p.n] + q] = (int)i;
         code = ST_RUNNING;
     }
     kp.out.status[i] = (uint8_t)code;
-    return to_polish;
+    return to_polish ? END_POLISH : code == ST_RUNNING ? END_FALLBACK : END_FINAL;
 }
 
 template <int FORM, bool REFR>
-__global__ void __launch_bounds__(kFinBlock) k_finish(KParams kp, int items)
+__global__ void __launch_bounds__(kFinBlock, 4) k_finish(KParams kp, int items)
 {
-    // per listed solve: its id within the block's solves and its order
-    __shared__ uint16_t list[kFinBlock * kFinItems];
-    __shared__ int lcnt[kMaxN], lbase[kMaxN], off[kMaxN + 1], total;
-    if (threadIdx.x <= kMaxN) {
-        off[threadIdx.x] = threadIdx.x ? bin_offset(kp.bin_cnt, threadIdx.x) : 0;
-        if (threadIdx.x < kMaxN) lcnt[threadIdx.x] = 0;
-        else total = 0;
-    }
+    __shared__ float rows[kFinBlock / 64 * kWaveRows];
+    __shared__ int lcnt[2 * kMaxN], lbase[2 * kMaxN];  // polish lists, then fallback lists
+    float *w = rows + (threadIdx.x >> 6) * kWaveRows;
+    if (threadIdx.x < 2 * kMaxN) lcnt[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t b0 = (int64_t)blockIdx.x * kFinBlock * items;
+    const int64_t b0 = (int64_t)blockIdx.x * kFinBlock * items + threadIdx.x;
+    uint64_t listed = 0;  // four bits per item: 1 + the path's list, or 0
+#pragma nounroll
     for (int j = 0; j < items; j++) {
-        const int loc = j * kFinBlock + (int)threadIdx.x;
-        const int64_t i = b0 + loc;
-        int ord = 0;
-        bool pol = false;
-        if (i < kp.b.n && kp.out.status[i] == ST_RUNNING) pol = finish_path<FORM, REFR>(kp, i, off, ord);
-        const uint64_t m = __ballot(pol);
-        if (m) {
-            int base = 0;
-            if (__lane_id() == 0) base = atomicAdd(&total, (int)__popcll(m));
-            base = __shfl(base, 0);
-            if (pol) {
-                list[base + (int)__popcll(m & ((1ull << __lane_id()) - 1ull))] = (uint16_t)(loc << 3 | ord);
-                atomicAdd(&lcnt[ord - 1], 1);
+        const int64_t i = b0 + j * kFinBlock;
+        const bool live = i < kp.b.n && kp.out.status[i] == ST_RUNNING;
+        if (!__any(live)) continue;
+        rows_load(w, live ? state_row(kp, kp.rows ? kp.perm[i] : 0, i) : state_row(kp, 0, 0));
+        if (live) {
+            int ord;
+            const int end = finish_path<FORM, REFR>(kp, i, ord, w + __lane_id() * kRowWords);
+            if (end != END_FINAL) {
+                const int q = end * kMaxN + ord - 1;
+                listed |= (uint64_t)(q + 1) << (4 * j);
+                atomicAdd(&lcnt[q], 1);
             }
         }
+        rows_store(w, live ? kp.out.x + (size_t)i * kRow : nullptr);
     }
     __syncthreads();
-    if (threadIdx.x < kMaxN) {
-        const int c = lcnt[threadIdx.x];
-        lbase[threadIdx.x] = off[threadIdx.x + 1] + (c ? atomicAdd(&kp.pol_cnt[threadIdx.x], c) : 0);
+    if (threadIdx.x < 2 * kMaxN) {
+        const bool fb = threadIdx.x >= kMaxN;
+        const int c = lcnt[threadIdx.x], ord = (int)threadIdx.x - (fb ? kMaxN : 0) + 1;
+        int *cnt = fb ? kp.fb_cnt : kp.pol_cnt;
+        lbase[threadIdx.x] = bin_offset(kp.bin_cnt, ord) + (c ? atomicAdd(&cnt[ord - 1], c) : 0);
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < total; q += kFinBlock) {
-        const int v = list[q];
-        kp.pol_list[atomicAdd(&lbase[(v & 7) - 1], 1)] = (int)(b0 + (v >> 3));
+    for (int j = 0; j < items; j++) {
+        const int q = (int)(listed >> (4 * j)) & 15;
+        if (q) (q > kMaxN ? kp.fb_list : kp.pol_list)[atomicAdd(&lbase[q - 1], 1)] = (int)(b0 + j * kFinBlock);
     }
 }
 

@@ -423,12 +423,12 @@ __device__ int64_t walk_tail(const CandGraph &G, const uint32_t *Ur, const int *
     return WRITE ? pos : c;
 }
 
-// Successors v2 of v1 in increasing order into an LDS list: the first wave
-// tests 64 objects at a time.
-__device__ __forceinline__ int list_succ(const CandGraph &G, int v1, uint16_t *list)
+// The objects of a row of bits (null: none) in increasing order into an LDS list
+// by the block: the first wave tests 64 objects at a time.
+__device__ __forceinline__ int list_bits(const CandGraph &G, const uint32_t *row, uint16_t *list)
 {
     __shared__ int nlist;
-    const uint32_t *row = succ(G, v1);
+    __syncthreads();  // readers of the last list
     if (threadIdx.x < 64) {
         int c = 0;
         for (int v0 = 0; row && v0 < G.n; v0 += 64) {
@@ -461,7 +461,6 @@ __device__ __forceinline__ int64_t block_scan_i64(int64_t v, int64_t *red)
 }
 
 constexpr int kCandBlock = 256;
-constexpr int kMaxObjCand = 4096;
 
 // last[r][v]: the successors of v that see receiver r.
 __global__ void __launch_bounds__(256) k_cand_last(CandGraph G, int n_rx, int *__restrict__ last)
@@ -512,29 +511,40 @@ __global__ void __launch_bounds__(256) k_cand_count(CandGraph G, int n_rx, const
     }
 }
 
-// Writes the paths.  blockIdx.y splits the successors of a first object into
-// kFillParts consecutive parts for orders up to 3 (few first objects see BS, and
-// one block per first object left most of the device idle); the deeper orders
-// are walked by the first part's block.
+// Writes the paths of orders up to 3, or (DEEP) of the orders beyond.  The
+// blocks that are resident at once list the first objects that see BS and stride
+// over (receiver, first object, part): with a block for every object the device
+// was mostly busy starting blocks that had nothing to write.  For order 3 a
+// first object's successors are split into up to kFillParts consecutive parts
+// while that leaves each block about half a part (a part repeats the counts
+// before it and its block's scans: 16 receivers' 4.4 M paths took 161 us in 2
+// parts, 191 in 4, 279 in 8 and 452 in 16; one thread per path that searched
+// its successor and object, in the registers of the deep walk, 528).  Bound by
+// the latency of those steps; the stores alone would take 26 us.
 constexpr int kFillParts = 8;
 
+template <bool DEEP>
 __global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx, const int *__restrict__ last,
                                                           const int64_t *__restrict__ off, int64_t cap,
                                                           int32_t *__restrict__ rx_index, int32_t *__restrict__ order,
                                                           int32_t *__restrict__ prim)
 {
-    __shared__ uint16_t list[kMaxObjCand];
+    extern __shared__ uint16_t ids[];  // the first objects, one's successors and, per wave, the ends of one's paths
+    uint16_t *first = ids, *list = ids + G.n;
     __shared__ int64_t red[kCandBlock];
-    const int64_t items = (int64_t)n_rx * G.n;
-    const int part = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint16_t *ends = ids + (size_t)(2 + wave) * G.n;
+    const int nf = list_bits(G, G.B, first);
+    if (nf == 0) return;
+    const int64_t pairs = (int64_t)n_rx * nf;
+    const int parts = DEEP || G.maxo < 3 ? 1 : (int)max((int64_t)1, min((int64_t)kFillParts, gridDim.x / (2 * pairs)));
+    const int64_t items = pairs * parts;
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const int r = (int)(it / G.n), v1 = (int)(it % G.n);
-        if (!bit(G.B, v1)) continue;
+        const int part = (int)(it % parts), r = (int)(it / parts / nf), v1 = first[it / parts % nf];
         const uint32_t *Ur = G.U + (size_t)r * G.W;
         const int *lr = last + (size_t)r * G.n;
-        __syncthreads();  // the previous item's readers of list and red
-        const int nl = list_succ(G, v1, list);
-        for (int o = 1; o <= G.maxo; o++) {
+        const int nl = list_bits(G, succ(G, v1), list);
+        for (int o = DEEP ? 4 : 1; o <= (DEEP ? G.maxo : min(G.maxo, 3)); o++) {
             int64_t base = off[((size_t)r * G.maxo + (o - 1)) * G.n + v1];
             if (o == 1) {
                 if (part == 0 && threadIdx.x == 0 && bit(Ur, v1)) {
@@ -544,12 +554,12 @@ __global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx,
                 }
                 continue;
             }
-            if (part && o != 3) continue;
+            if (part && o == 2) continue;
             // this block's part of the list, and what the parts before it write
             int e_lo = 0, e_hi = nl;
             if (o == 3) {
-                e_lo = (int)((int64_t)nl * part / kFillParts);
-                e_hi = (int)((int64_t)nl * (part + 1) / kFillParts);
+                e_lo = (int)((int64_t)nl * part / parts);
+                e_hi = (int)((int64_t)nl * (part + 1) / parts);
                 int64_t before = 0;
                 for (int e = threadIdx.x; e < e_lo; e += blockDim.x) {
                     const int path[2] = {v1, list[e]};
@@ -567,55 +577,57 @@ __global__ void __launch_bounds__(kCandBlock) k_cand_fill(CandGraph G, int n_rx,
                 int v2 = -1;
                 if (e < e_hi) {
                     v2 = list[e];
-                    if (o == 2) {
-                        c = bit(Ur, v2);
-                    } else {
-                        int path[kMaxN] = {v1, v2};
-                        c = walk_tail<false>(G, Ur, lr, path, 2, o, r, 0, 0, nullptr, nullptr, nullptr);
-                    }
+                    int path[kMaxN] = {v1, v2};
+                    if constexpr (DEEP) c = walk_tail<false>(G, Ur, lr, path, 2, o, r, 0, 0, nullptr, nullptr, nullptr);
+                    else c = o == 2 ? bit(Ur, v2) : count_last(G, Ur, lr, path, 2);
                 }
                 const int64_t incl = block_scan_i64(c, red);
                 const int64_t chunk = red[blockDim.x - 1];
-                if (o == 3) {
-                    // consecutive threads write consecutive paths: path q of
-                    // the chunk belongs to the first successor whose inclusive
-                    // count exceeds q, and is the rank-th object after it
+                if (!DEEP && o == 3) {
+                    // a wave per successor: each lane lists the objects of one
+                    // word of its row, and consecutive lanes write consecutive
+                    // paths
                     const int ne = min((int)blockDim.x, e_hi - e0);
-                    for (int64_t q = threadIdx.x; q < chunk; q += blockDim.x) {
-                        int lo = 0, hi = ne - 1;
-                        while (lo < hi) {
-                            const int mid = (lo + hi) >> 1;
-                            if (red[mid] > q) hi = mid;
-                            else lo = mid + 1;
-                        }
-                        const int w2 = list[e0 + lo];
-                        int rank = (int)(q - (lo ? red[lo - 1] : 0));
+                    for (int z = wave; z < ne; z += kCandBlock / 64) {
+                        const int64_t at = z ? red[z - 1] : 0;
+                        const int m3 = (int)(red[z] - at);
+                        if (m3 == 0) continue;
+                        const int w2 = list[e0 + z];
                         const uint32_t *row2 = G.V + (size_t)w2 * G.W;
-                        int v3 = -1;
-                        for (int w = 0; w < G.W && v3 < 0; w++) {
-                            uint32_t m = row2[w] & Ur[w];
+                        int run = 0;
+                        for (int w0 = 0; w0 < G.W; w0 += 64) {
+                            const int w = w0 + lane;
+                            uint32_t m = w < G.W ? row2[w] & Ur[w] : 0u;
                             if ((v1 >> 5) == w) m &= ~(1u << (v1 & 31));
                             if ((w2 >> 5) == w) m &= ~(1u << (w2 & 31));
                             const int pc = __popc(m);
-                            if (rank < pc) {
-                                for (int z = 0; z < rank; z++) m &= m - 1u;
-                                v3 = (w << 5) + (__ffs(m) - 1);
+                            int upto = pc;
+#pragma unroll
+                            for (int d = 1; d < 64; d <<= 1) {
+                                const int v = __shfl_up(upto, d);
+                                if (lane >= d) upto += v;
                             }
-                            rank -= pc;
+                            for (int q = run + upto - pc; m; m &= m - 1u)
+                                ends[q++] = (uint16_t)((w << 5) + (__ffs(m) - 1));
+                            run += __shfl(upto, 63);
                         }
-                        const int64_t pos = base + q;
-                        rx_index[pos] = r;
-                        order[pos] = 3;
-                        prim[pos] = v1;
-                        prim[(size_t)cap + pos] = w2;
-                        prim[(size_t)2 * cap + pos] = v3;
-                        prim[(size_t)3 * cap + pos] = -1;
-                        prim[(size_t)4 * cap + pos] = -1;
+                        wave_sync();
+                        for (int q = lane; q < m3; q += 64) {
+                            const int64_t pos = base + at + q;
+                            rx_index[pos] = r;
+                            order[pos] = 3;
+                            prim[pos] = v1;
+                            prim[(size_t)cap + pos] = w2;
+                            prim[(size_t)2 * cap + pos] = ends[q];
+                            prim[(size_t)3 * cap + pos] = -1;
+                            prim[(size_t)4 * cap + pos] = -1;
+                        }
+                        wave_sync();
                     }
                 } else if (c > 0) {
                     int path[kMaxN] = {v1, v2};
                     const int64_t pos = base + incl - c;
-                    if (o == 2) {
+                    if constexpr (!DEEP) {
                         rx_index[pos] = r;
                         order[pos] = 2;
                         for (int q = 0; q < kMaxN; q++) prim[(size_t)q * cap + pos] = q < 2 ? path[q] : -1;
@@ -780,8 +792,13 @@ void launch_cand_fill(const SceneDev &s, const uint32_t *V, const uint32_t *B, c
 {
     const CandGraph G = graph_of(s, V, B, U, W, maxo, edge_last);
     const int64_t items = (int64_t)n_rx * s.n_all;
-    hipLaunchKernelGGL(k_cand_fill, dim3((unsigned)std::min<int64_t>(items, (int64_t)cu * 32), maxo >= 3 ? kFillParts : 1),
-                       dim3(kCandBlock), 0, st, G, n_rx, last, off, cap, rx_index, order, prim);
+    if (items == 0) return;
+    const size_t bytes = (size_t)(2 + kCandBlock / 64) * s.n_all * sizeof(uint16_t);
+    hipLaunchKernelGGL(k_cand_fill<false>, dim3((unsigned)std::min<int64_t>(items * kFillParts, (int64_t)cu * 8)),
+                       dim3(kCandBlock), bytes, st, G, n_rx, last, off, cap, rx_index, order, prim);
+    if (maxo > 3)
+        hipLaunchKernelGGL(k_cand_fill<true>, dim3((unsigned)std::min<int64_t>(items, (int64_t)cu * 3)),
+                           dim3(kCandBlock), bytes, st, G, n_rx, last, off, cap, rx_index, order, prim);
 }
 
 }  // namespace mpt

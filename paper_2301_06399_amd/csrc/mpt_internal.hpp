@@ -82,6 +82,13 @@ struct KParams {
     double *spill_f;           // [3][n] damping, plateau reference and stall count of a parked FP64 path
 };
 
+// LDS written by lanes of the wave before it is read by others after it.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 void launch_pack(const double *raw, const double *refr, const SceneDev &s, int n_pl, int n_ln, int n_q, int n_c,
                  hipStream_t st);
 void launch_occluders(const SceneDev &s, hipStream_t st);

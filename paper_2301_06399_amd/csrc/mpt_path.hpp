@@ -383,12 +383,6 @@ constexpr int kWaveRows = 64 * kRowWords;  // words of LDS per wave
 typedef float f32x4l __attribute__((ext_vector_type(4), aligned(16), may_alias));
 typedef uint64_t u64a __attribute__((may_alias));
 
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Stores the lanes' rows, each at its dst (null: none).
 __device__ __forceinline__ void rows_store(float *w, void *dst)
 {

@@ -591,16 +591,28 @@ static mpt_status check_opts(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solv
 // the workspace of n paths, in ints.
 static size_t state_offset(size_t n) { return (kCounters + 4 * n + 31) / 32 * 32; }
 
-// Work buffers of a solve of n paths (sized before any graph capture).
+static void drop_graph(mpt_ctx *c)
+{
+    if (c->gexec) hipGraphExecDestroy(c->gexec);
+    c->gexec = nullptr;
+    c->gkey.clear();
+}
+
+// Work buffers of a solve of n paths (sized before any graph capture).  The
+// kernels of a captured solve hold the addresses of both buffers, and a solve
+// of another size or precision may need larger ones, so a captured solve does
+// not outlive the buffers it was captured with.
 static mpt_status size_buffers(mpt_ctx *c, int64_t n, const mpt_solve_opts *o)
 {
     const size_t m = (size_t)(n > 0 ? n : 1);
     const bool learned = o->init == MPT_INIT_LEARNED || o->init == MPT_INIT_LEARNED_ALL;
-    mpt_status st;
+    const int *ws = c->ws;
+    const double *x0l = c->x0l;
     const size_t state = (o->precision == MPT_FP64_PLAIN ? 6 : 32) * m;
-    if ((st = ensure(c, (void **)&c->ws, &c->ws_cap, state_offset(m) + state, sizeof(int)))) return st;
-    if (learned && (st = ensure(c, (void **)&c->x0l, &c->x0l_cap, MPT_ROW * m, sizeof(double)))) return st;
-    return MPT_OK;
+    mpt_status st = ensure(c, (void **)&c->ws, &c->ws_cap, state_offset(m) + state, sizeof(int));
+    if (!st && learned) st = ensure(c, (void **)&c->x0l, &c->x0l_cap, MPT_ROW * m, sizeof(double));
+    if (c->ws != ws || c->x0l != x0l) drop_graph(c);
+    return st;
 }
 
 // Workspace of one solve: counters and lists (int32), state rows of the FP32
@@ -810,7 +822,7 @@ mpt_status mpt_solve_batch(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_
     // graph mode: capture once per (batch, options, outputs, scene) and replay
     std::vector<unsigned char> key = graph_key(b, opts, out, sched, block, gdiv, spill, form, c->s);
     if (!c->gexec || key != c->gkey) {
-        if (c->gexec) hipGraphExecDestroy(c->gexec), c->gexec = nullptr;
+        drop_graph(c);
         if (!c->cap) HIPCHK(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
         // buffers are sized before capture: no allocation inside it
         if ((st = size_buffers(c, b->n, opts))) return st;

@@ -480,8 +480,10 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
                     }
                     it0 = L.it;
                     if (resume && it0 > 0) L.phase = LANE_RESUMED;  // else parked before its first pass
-                    // the plateau test opens iterations 1 + win, 1 + 2 win, ...
-                    L.win_it = o.win > 0 ? (resume ? (it0 - 1) / o.win : 0) * o.win + o.win + 1 : 0;
+                    // the plateau test opens iterations 1 + win, 1 + 2 win, ...;
+                    // the next of them after iteration it0 (1 at the least: the
+                    // first iteration only sets the reference)
+                    L.win_it = o.win > 0 ? (it0 > 1 ? (it0 - 1) / o.win : 0) * o.win + o.win + 1 : 0;
                     if constexpr (REFR) {
                         if (active) {
 #pragma unroll

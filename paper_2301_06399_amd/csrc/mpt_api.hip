@@ -788,9 +788,10 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
 }
 
 static std::vector<unsigned char> graph_key(const mpt_batch_desc *b, const mpt_solve_opts *o, const mpt_solve_out *out,
-                                            int sched, int block, int gdiv, int spill, int form, const SceneDev &s)
+                                            int sched, int block, int gdiv, int spill, int form, bool refr,
+                                            const SceneDev &s)
 {
-    std::vector<unsigned char> k(sizeof *b + sizeof *o + sizeof *out + 5 * sizeof(int) + sizeof s);
+    std::vector<unsigned char> k(sizeof *b + sizeof *o + sizeof *out + 6 * sizeof(int) + sizeof s);
     unsigned char *p = k.data();
     memcpy(p, b, sizeof *b), p += sizeof *b;
     memcpy(p, o, sizeof *o), p += sizeof *o;
@@ -800,6 +801,8 @@ static std::vector<unsigned char> graph_key(const mpt_batch_desc *b, const mpt_s
     memcpy(p, &gdiv, sizeof gdiv), p += sizeof gdiv;
     memcpy(p, &spill, sizeof spill), p += sizeof spill;
     memcpy(p, &form, sizeof form), p += sizeof form;
+    const int refracting = refr;  // other kernels; the indices are record values, not part of s
+    memcpy(p, &refracting, sizeof refracting), p += sizeof refracting;
     memcpy(p, &s, sizeof s);
     return k;
 }
@@ -820,7 +823,7 @@ mpt_status mpt_solve_batch(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_
     if (!opts->graph) return enqueue_solve(c, b, opts, out, c->stream, c->timing, sched, block, gdiv, spill, form);
 
     // graph mode: capture once per (batch, options, outputs, scene) and replay
-    std::vector<unsigned char> key = graph_key(b, opts, out, sched, block, gdiv, spill, form, c->s);
+    std::vector<unsigned char> key = graph_key(b, opts, out, sched, block, gdiv, spill, form, c->refr, c->s);
     if (!c->gexec || key != c->gkey) {
         drop_graph(c);
         if (!c->cap) HIPCHK(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));

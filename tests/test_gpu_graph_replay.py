@@ -58,3 +58,32 @@ def test_replay_after_the_workspace_grew(graph, between, grow):
     finally:
         ctx.close()
         ref_ctx.close()
+
+
+@pytest.mark.parametrize("prec,form", [(1, 2), (1, 0), (0, 2)])
+def test_replay_after_facets_start_to_refract(prec, form):
+    """The same geometry uploaded with and without refractive indices: the
+    scene's buffers and sizes stay, the kernels of the solve do not."""
+    import dataclasses
+    from paper_2301_06399_amd import mpt
+    glass, b = W.config6(n_rx=64)
+    mirrors = dataclasses.replace(glass, refraction=np.zeros((0, 2)))
+    db = mpt.DeviceBatch(b)
+    want = []
+    for sc in (mirrors, glass):
+        ref = mpt.Context(0)
+        ref.upload_scene(sc)
+        want.append(ref.solve(db, mpt.default_opts(precision=prec, form=form)).numpy())
+        ref.close()
+    assert not same(want[0], want[1])
+    ctx = mpt.Context(0)
+    out = mpt.DeviceOut(b.n)
+    for rep in range(4):
+        ctx.upload_scene((mirrors, glass)[rep % 2])
+        for again in range(2):
+            out.x.fill_(-1.0)
+            out.status.fill_(99)
+            ctx.solve(db, mpt.default_opts(precision=prec, form=form, graph=1), out)
+            ctx.synchronize()
+            assert same(out.numpy(), want[rep % 2]), (rep, again)
+    ctx.close()

@@ -4,7 +4,7 @@
 // a wedged straight edge must leave it into free space.
 //
 //  k_vis_list   compacts the accepted solves into a list, clears visible[]
-//  k_visible    one wave per accepted solve: every segment against every
+//  k_visible    a group of lanes per accepted solve: every segment against every
 //               facet and patch (a lane each) and the edges' wedges
 #include "mpt_internal.hpp"
 #include "mpt_geom.hpp"
@@ -45,13 +45,19 @@ __global__ void __launch_bounds__(256) k_vis_list(const uint8_t *__restrict__ ac
     for (int q = threadIdx.x; q < total; q += 256) list[1 + base + q] = (int)(b0 + loc[q]);
 }
 
-// One wave per accepted solve of the list: visible[i] = 1 when no segment is
+// G lanes per accepted solve of the list: visible[i] = 1 when no segment is
 // blocked.  A lane tests one facet or patch at a time, its box against the
-// segment first, and the path ends at its first blocked segment (most kept
-// paths of a city scene have one; a thread per path walked every facet for the
-// slowest path of its wave: 0.76 ms against 0.40 ms on the accepted paths of
-// 16 receivers' candidates in the street canyon, 0.29 against 0.04 ms on the
-// 32,000 of its 262,144 random lists).  Plane and quadric records are staged in LDS when `lds` is set.
+// segment first, and the path ends at its first blocked segment.  In a city scene
+// most kept paths have one, and a thread per path walked every facet for the
+// slowest path of its wave: 0.76 ms against 0.40 ms with a wave per path on the
+// accepted paths of 16 receivers' candidates in the street canyon (251 facets),
+// 0.29 against 0.04 ms on the 32,000 of its 262,144 random lists.  With few
+// occluders a wave per path leaves most lanes idle and the paths' loads one after
+// the other: the call on 655,360 kept paths of the room (6 facets) takes 855 us
+// that way, 168 with four lanes each (a thread each: 389), on 107,202 among 40
+// patches 205 and 147.  Plane and quadric records are staged in LDS when `lds` is
+// set.
+template <int G>
 __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC in, const int *__restrict__ list,
                                                  double min_seg, uint8_t *__restrict__ vis, int *__restrict__ count,
                                                  int lds)
@@ -61,7 +67,8 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
     double *srec = reinterpret_cast<double *>(smem_raw);
     const int npl = s.n_pl, nq = s.n_pl_ln_q - s.n_pl_ln, nocc = npl + nq;
     const int na = list[0];
-    if ((int)(blockIdx.x * (blockDim.x >> 6)) >= na) return;  // block-uniform
+    constexpr int kPaths = 64 / G;  // of a wave
+    if ((int)(blockIdx.x * (blockDim.x >> 6)) * kPaths >= na) return;  // block-uniform
     if (threadIdx.x == 0) kept = 0;
     if (lds) {
         for (int j = threadIdx.x; j < npl * kRec; j += blockDim.x) srec[j] = s.rec64[j];
@@ -71,10 +78,13 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
     __syncthreads();
     const double *prec = lds ? srec : s.rec64;
     const double *qrec = lds ? srec + (size_t)npl * kRec : s.rec64 + (size_t)s.n_pl_ln * kRec;
-    const int lane = threadIdx.x & 63, nwave = (int)((gridDim.x * blockDim.x) >> 6);
+    const int lane = threadIdx.x & (G - 1), nwave = (int)((gridDim.x * blockDim.x) >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    // this path's lanes in a ballot (the lanes of one path stay together)
+    const uint64_t group = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull) << ((threadIdx.x & 63) & ~(G - 1));
     int mine = 0;
-    for (int t = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6)); t < na;
-         t += nwave) {
+    for (int t = G == 64 ? wave : wave * kPaths + (int)((threadIdx.x & 63) / G); t < na;
+         t += nwave * kPaths) {
         const int64_t i = list[1 + t];
         const int n = b.order[i], ri = b.rx_index[i];
         bool ok = true;
@@ -94,7 +104,7 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
             if (ok) {
                 const float p[3] = {(float)P[0], (float)P[1], (float)P[2]}, q[3] = {(float)Q[0], (float)Q[1], (float)Q[2]};
                 const Shaft sh = shaft_between(p, p, q, q);
-                for (int o0 = 0; ok && o0 < nocc; o0 += 64) {
+                for (int o0 = 0; ok && o0 < nocc; o0 += G) {
                     const int o = o0 + lane;
                     bool hit = false;
                     if (o < nocc) {
@@ -103,7 +113,7 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
                         const float box[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                         if (!outside_shaft(sh, box)) hit = blocks(s, prec, qrec, o, g, ip, iq);
                     }
-                    ok = !__any(hit);
+                    ok = (__ballot(hit) & group) == 0;
                 }
             }
             for (int c = 0; c < 3; c++) P[c] = Q[c];
@@ -119,6 +129,21 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
     if (threadIdx.x == 0 && kept) atomicAdd(count, kept);
 }
 
+template <int G>
+static void launch_visible_lanes(const SceneDev &s, const BatchDev &b, const OutDevC &in, const int *list,
+                                 double min_seg, uint8_t *vis, int *count, size_t lds_max, int cu, hipStream_t st)
+{
+    const size_t bytes = (size_t)(s.n_pl + (s.n_pl_ln_q - s.n_pl_ln)) * kRec * sizeof(double);
+    const int lds = bytes <= lds_max && bytes <= 64 * 1024;
+    if (lds) hipFuncSetAttribute((const void *)k_visible<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    // the accepted count is on the device: the blocks that fit at once, each
+    // looping over the list
+    const int64_t fit = lds ? std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(lds_max / (bytes + 64)))) : 8;
+    const int64_t per = 4 * (64 / G);
+    const unsigned g = (unsigned)std::min<int64_t>((b.n + per - 1) / per, (int64_t)cu * fit);
+    hipLaunchKernelGGL(k_visible<G>, dim3(g), dim3(256), lds ? bytes : 0, st, s, b, in, list, min_seg, vis, count, lds);
+}
+
 void launch_visible(const SceneDev &s, const BatchDev &b, const OutDevC &in, const uint8_t *acc, double min_seg,
                     uint8_t *vis, int *count, int *list, size_t lds_max, int cu, hipStream_t st)
 {
@@ -129,14 +154,10 @@ void launch_visible(const SceneDev &s, const BatchDev &b, const OutDevC &in, con
     const int items = (int)std::min<int64_t>(kListItems, (b.n + 256 * (int64_t)cu * 4 - 1) / (256 * (int64_t)cu * 4));
     hipLaunchKernelGGL(k_vis_list, dim3((unsigned)((b.n + 256 * items - 1) / (256 * items))), dim3(256), 0, st, acc,
                        b.n, list, vis, items);
-    const size_t bytes = (size_t)(s.n_pl + (s.n_pl_ln_q - s.n_pl_ln)) * kRec * sizeof(double);
-    const int lds = bytes <= lds_max && bytes <= 64 * 1024;
-    if (lds) hipFuncSetAttribute((const void *)k_visible, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    // the accepted count is on the device: the blocks that fit at once, each
-    // looping over the list
-    const int64_t fit = lds ? std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(lds_max / (bytes + 64)))) : 8;
-    const unsigned g = (unsigned)std::min<int64_t>((b.n + 3) / 4, (int64_t)cu * fit);
-    hipLaunchKernelGGL(k_visible, dim3(g), dim3(256), lds ? bytes : 0, st, s, b, in, list, min_seg, vis, count, lds);
+    // few occluders: four lanes a path; many: a wave (the line lies between 81
+    // occluders, where a call takes 100 us and 104, and 200, 296 and 267)
+    const bool few = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln) <= 96;
+    (few ? launch_visible_lanes<4> : launch_visible_lanes<64>)(s, b, in, list, min_seg, vis, count, lds_max, cu, st);
 }
 
 }  // namespace mpt

@@ -40,17 +40,11 @@ __global__ void __launch_bounds__(64) k_samples(SceneDev s, int k, double *__res
         else z1[i - n0] = 0u;
     }
     if (g >= s.n_all) return;
-    double *pts = samp + (size_t)g * sample_cap(k) * 3;
-    const int m = obj_samples(s, g, k, pts);
-    cnt[g] = m;
+    double lo[3], hi[3];
+    cnt[g] = obj_samples(s, g, k, samp + (size_t)g * sample_cap(k) * 3, lo, hi);
     for (int c = 0; c < 3; c++) {
-        double lo = pts[c], hi = pts[c];
-        for (int j = 1; j < m; j++) {
-            lo = fmin(lo, pts[3 * j + c]);
-            hi = fmax(hi, pts[3 * j + c]);
-        }
-        box[(size_t)g * 8 + c] = (float)lo;
-        box[(size_t)g * 8 + 4 + c] = (float)hi;
+        box[(size_t)g * 8 + c] = (float)lo[c];
+        box[(size_t)g * 8 + 4 + c] = (float)hi[c];
     }
 }
 

@@ -128,9 +128,20 @@ __device__ __forceinline__ double revolution_kappa(const double *r)
     return (kap > 0.0 && err <= 1e-9 * (1.0 + kap)) ? kap : -1.0;
 }
 
-__device__ inline int obj_samples(const SceneDev &s, int g, int k, double *pts)
+// Returns their number; lo, hi: their bounding box, taken as they are made
+// (read back from memory at 16 samples a side it took longer than making them).
+__device__ inline int obj_samples(const SceneDev &s, int g, int k, double *pts, double lo[3], double hi[3])
 {
 #pragma clang fp contract(off)
+    for (int c = 0; c < 3; c++) {
+        lo[c] = __builtin_huge_val();
+        hi[c] = -__builtin_huge_val();
+    }
+    const auto put = [&](int j, int c, double x) {
+        pts[3 * j + c] = x;
+        lo[c] = fmin(lo[c], x);
+        hi[c] = fmax(hi[c], x);
+    };
     const double *r = s.rec64 + (size_t)g * kRec;
     const int t = prim_type(g, s.n_pl, s.n_pl_ln, s.n_pl_ln_q);
     int m = 0;
@@ -138,20 +149,20 @@ __device__ inline int obj_samples(const SceneDev &s, int g, int k, double *pts)
         for (int a = 0; a < k; a++)
             for (int b = 0; b < k; b++) {
                 const double u = (double)(2 * a + 1) / (double)(2 * k), v = (double)(2 * b + 1) / (double)(2 * k);
-                for (int c = 0; c < 3; c++) pts[3 * m + c] = (r[4 + c] + u * r[7 + c]) + v * r[10 + c];
+                for (int c = 0; c < 3; c++) put(m, c, (r[4 + c] + u * r[7 + c]) + v * r[10 + c]);
                 m++;
             }
     } else if (t == TL) {
         for (int a = 0; a < k; a++) {
             const double f = (double)(2 * a + 1) / (double)(2 * k);
             const double sp = r[6] + f * (r[7] - r[6]);
-            for (int c = 0; c < 3; c++) pts[3 * m + c] = r[c] + sp * r[3 + c];
+            for (int c = 0; c < 3; c++) put(m, c, r[c] + sp * r[3 + c]);
             m++;
         }
     } else if (t == TQ) {
         const double kap = revolution_kappa(r);
         if (kap < 0.0) {
-            for (int c = 0; c < 3; c++) pts[c] = r[c];
+            for (int c = 0; c < 3; c++) put(0, c, r[c]);
             return 1;
         }
         double e1[3], e2[3];
@@ -162,7 +173,7 @@ __device__ inline int obj_samples(const SceneDev &s, int g, int k, double *pts)
                 if (ia * ia + ib * ib >= k * k) continue;
                 const double u = r[16] * ((double)ia / (double)k), v = r[16] * ((double)ib / (double)k);
                 const double h = kap * (u * u + v * v);
-                for (int c = 0; c < 3; c++) pts[3 * m + c] = ((r[c] + u * e1[c]) + v * e2[c]) + h * r[13 + c];
+                for (int c = 0; c < 3; c++) put(m, c, ((r[c] + u * e1[c]) + v * e2[c]) + h * r[13 + c]);
                 m++;
             }
     } else {
@@ -173,8 +184,8 @@ __device__ inline int obj_samples(const SceneDev &s, int g, int k, double *pts)
             const double den = 1.0 + tt * tt;
             const double x = (1.0 - tt * tt) / den, y = (2.0 * tt) / den;
             for (int c = 0; c < 3; c++) {
-                pts[3 * m + c] = r[c] + r[6] * (x * u1[c] + y * u2[c]);
-                pts[3 * (m + 1) + c] = r[c] + r[6] * ((-x) * u1[c] + (-y) * u2[c]);
+                put(m, c, r[c] + r[6] * (x * u1[c] + y * u2[c]));
+                put(m + 1, c, r[c] + r[6] * ((-x) * u1[c] + (-y) * u2[c]));
             }
             m += 2;
         }

@@ -448,6 +448,15 @@ static mpt_status batch_dev(mpt_ctx *c, const mpt_batch_desc *b, BatchDev &bd)
     return MPT_OK;
 }
 
+// The waves a launch of the FP32 implicit kernels gets on each CU: one while the
+// lanes of one hold the batch, two while the lanes of two do, else one per SIMD
+// (4).  Launches that run side by side share the batch.
+static int implicit_waves(const mpt_ctx *c, int sched, int64_t n)
+{
+    const int64_t m = sched == MPT_SCHED_PERSISTENT ? n : n / 4, lanes = (int64_t)c->cu * 64;
+    return m <= lanes ? 1 : m <= 2 * lanes ? 2 : 4;
+}
+
 // Blocks of a persistent launch: as many as can be resident at once, and no
 // more than n paths can use at `per_block` paths a block.
 static int resident_grid(mpt_ctx *c, const void *kern, int block, int64_t n, int per_block, size_t lds = 0)
@@ -534,6 +543,7 @@ static void choose(mpt_ctx *c, const mpt_solve_opts *o, int64_t n, int &sched, i
 {
     default_choice(o->precision, sched, block, gdiv, spill);
     form = resolved_form(c, o);
+    bool tuned = false;
     if (load) tune_load(c);
     for (auto &t : c->tune)
         if (t.prec == o->precision && t.form == form && t.nbucket == nbucket(n) && t.scene == c->scene_hash) {
@@ -541,13 +551,27 @@ static void choose(mpt_ctx *c, const mpt_solve_opts *o, int64_t n, int &sched, i
             block = t.block;
             gdiv = t.gdiv;
             spill = t.spill;
+            tuned = true;
         }
     if (o->sched != MPT_SCHED_AUTO) sched = o->sched;
-    if (o->block) block = o->block;
     if (o->spill >= 0) spill = o->spill;
     // the rows of refracting facets are compiled into the mixed-order
     // kernel only
     if (c->refr) sched = MPT_SCHED_PERSISTENT, gdiv = 1;
+    // Small batches in the FP32 implicit kernels: blocks of one wave, one or two
+    // of them on a CU.  The mixed-order kernel's 88 KB of code are more than the
+    // instruction cache that two CUs share, and a type is a branch of its own, so
+    // waves at different points of an iteration evict each other's code; and
+    // orders 4 and 5 (279 and 340 registers) cannot run side by side on one SIMD.
+    // Among curved objects 16,384 paths take 1886 us with four waves of 16 paths
+    // on a CU and 1226 with one of 64, 32,768 paths 1641 with four and 1332 with
+    // two; one launch per order 2586 and 1859 (65,536 paths: 2622 and 1804).  The
+    // parametric kernels, whose planar sequences have code of their own each, gain
+    // from fewer paths to a wave instead (4000 of the room: 222 us with four waves
+    // on a CU, 250 with one).
+    if (!tuned && o->precision != MPT_FP64_PLAIN && form == MPT_FORM_IMPLICIT && implicit_waves(c, sched, n) < 4)
+        block = 64;
+    if (o->block) block = o->block;
 }
 
 static mpt_status check_opts(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_opts *opts, const mpt_solve_out *out)
@@ -731,8 +755,10 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
                 g = resident_grid(c, k, blk, n, blk / 64, lds ? rec_bytes : 0);
                 // and one wave per SIMD while its lanes hold the whole batch: two
                 // would only take turns
-                const int64_t one = (int64_t)c->cu * 256 / blk;
-                if (n <= one * blk && g > one) g = (int)one;
+                const bool impl32 = md == MODE_FP32 && form == MPT_FORM_IMPLICIT;
+                const int waves = impl32 && blk == 64 ? implicit_waves(c, sch, n) : 4;
+                const int64_t most = (int64_t)c->cu * waves * 64 / blk;
+                if ((waves < 4 || n <= (int64_t)c->cu * 256) && g > most) g = (int)most;
                 if (first && gdiv > 1) g = (g + gdiv - 1) / gdiv;
             }
             launch_lm(md, ord, lds, form, c->refr, rec_bytes, kp, g, blk, where);
@@ -890,14 +916,21 @@ mpt_status mpt_autotune(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_opt
     struct Cand { int sched, block, gdiv, spill, form; };
     std::vector<Cand> cands;
     for (int fm : forms) {
+        // blocks of one wave: what an untuned small batch in the FP32 implicit
+        // form gets
+        auto blocks = [&](int sch) {
+            const bool small = opts->precision != MPT_FP64_PLAIN && fm == MPT_FORM_IMPLICIT &&
+                               implicit_waves(c, sch, b->n) < 4;
+            return small ? std::vector<int>{64, 128, 256} : std::vector<int>{128, 256};
+        };
         for (int sp : {0, 8, 16, 32})
-            for (int blk : {128, 256}) cands.push_back({MPT_SCHED_PERSISTENT, blk, 1, sp, fm});
+            for (int blk : blocks(MPT_SCHED_PERSISTENT)) cands.push_back({MPT_SCHED_PERSISTENT, blk, 1, sp, fm});
         if (c->refr) continue;  // refracting facets: the mixed-order kernel only
         for (int sp : {0, 16})
             for (int blk : {64, 128, 256})
                 for (int gd : {1, 2}) cands.push_back({MPT_SCHED_PER_ORDER, blk, gd, sp, fm});
         for (int sp : {0, 16})
-            for (int blk : {128, 256}) cands.push_back({MPT_SCHED_SPLIT, blk, 1, sp, fm});
+            for (int blk : blocks(MPT_SCHED_SPLIT)) cands.push_back({MPT_SCHED_SPLIT, blk, 1, sp, fm});
     }
     float best = 1e30f;
     Cand bc = cands[0];

@@ -71,7 +71,6 @@ struct mpt_ctx {
     std::vector<Tune> tune;
     bool tune_loaded = false;
     // captured graph of the last solve (replayed while the key matches)
-    hipStream_t cap = nullptr;
     hipGraphExec_t gexec = nullptr;
     std::vector<unsigned char> gkey;
 };
@@ -220,7 +219,6 @@ mpt_status mpt_destroy(mpt_ctx *c)
         for (int j = 0; j < 2; j++)
             if (c->kev[i][j]) hipEventDestroy(c->kev[i][j]);
     if (c->gexec) hipGraphExecDestroy(c->gexec);
-    if (c->cap) hipStreamDestroy(c->cap);
     if (c->own) hipStreamDestroy(c->own);
     delete c;
     return MPT_OK;
@@ -852,13 +850,17 @@ mpt_status mpt_solve_batch(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_
     std::vector<unsigned char> key = graph_key(b, opts, out, sched, block, gdiv, spill, form, c->refr, c->s);
     if (!c->gexec || key != c->gkey) {
         drop_graph(c);
-        if (!c->cap) HIPCHK(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
+        // captured on order 1's stream, which the launches side by side would
+        // fork from it anyway: a stream of its own, created at the first captured
+        // solve, took 150 to 450 us of it (a first captured solve of the room, 16,384 paths: 950 us,
+        // now 590)
+        hipStream_t cap = c->aux[0];
         // buffers are sized before capture: no allocation inside it
         if ((st = size_buffers(c, b->n, opts))) return st;
-        HIPCHK(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
-        st = enqueue_solve(c, b, opts, out, c->cap, false, sched, block, gdiv, spill, form);
+        HIPCHK(c, hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
+        st = enqueue_solve(c, b, opts, out, cap, false, sched, block, gdiv, spill, form);
         hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(c->cap, &g);
+        hipError_t e = hipStreamEndCapture(cap, &g);
         if (st) {
             if (g) hipGraphDestroy(g);
             return st;

@@ -44,11 +44,12 @@ struct mpt_ctx {
     bool refr = false;       // some facet of the scene refracts
     bool param_ok = true;    // every quadric is a paraboloid of revolution
     uint64_t scene_hash = 0; // FNV-1a of the uploaded records and TX: the tuning key
-    // workspace: counters | perm | polish, fallback and straggler lists | state
-    // rows of the FP32 pass [n][32], or the parked FP64 stragglers' damping,
-    // plateau reference and stall count [3][n]
+    // workspace: counters | perm | polish, fallback and straggler lists | the
+    // parked FP64 stragglers' damping, plateau reference and stall count [3][n]
     int *ws = nullptr;
     size_t ws_cap = 0;  // ints
+    float *rows = nullptr;  // state rows of the FP32 pass [n][32] of large batches
+    size_t rows_cap = 0;
     int *blk = nullptr;
     size_t blk_cap = 0;
     double *x0l = nullptr;
@@ -206,6 +207,7 @@ mpt_status mpt_destroy(mpt_ctx *c)
     hipFree(c->csum);
     hipFree(c->vlist);
     hipFree(c->ws);
+    hipFree(c->rows);
     hipFree(c->blk);
     hipFree(c->x0l);
     mlp_free(c->mlp);
@@ -609,10 +611,6 @@ static mpt_status check_opts(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solv
     return MPT_OK;
 }
 
-// Where the state rows (whole 128-byte lines) or the parked FP64 state lie in
-// the workspace of n paths, in ints.
-static size_t state_offset(size_t n) { return (kCounters + 4 * n + 31) / 32 * 32; }
-
 static void drop_graph(mpt_ctx *c)
 {
     if (c->gexec) hipGraphExecDestroy(c->gexec);
@@ -620,35 +618,50 @@ static void drop_graph(mpt_ctx *c)
     c->gkey.clear();
 }
 
-// Work buffers of a solve of n paths (sized before any graph capture).  The
-// kernels of a captured solve hold the addresses of both buffers, and a solve
-// of another size or precision may need larger ones, so a captured solve does
-// not outlive the buffers it was captured with.
-static mpt_status size_buffers(mpt_ctx *c, int64_t n, const mpt_solve_opts *o)
-{
-    const size_t m = (size_t)(n > 0 ? n : 1);
-    const bool learned = o->init == MPT_INIT_LEARNED || o->init == MPT_INIT_LEARNED_ALL;
-    const int *ws = c->ws;
-    const double *x0l = c->x0l;
-    const size_t state = (o->precision == MPT_FP64_PLAIN ? 6 : 32) * m;
-    mpt_status st = ensure(c, (void **)&c->ws, &c->ws_cap, state_offset(m) + state, sizeof(int));
-    if (!st && learned) st = ensure(c, (void **)&c->x0l, &c->x0l_cap, MPT_ROW * m, sizeof(double));
-    if (c->ws != ws || c->x0l != x0l) drop_graph(c);
-    return st;
-}
-
 // Workspace of one solve: counters and lists (int32), state rows of the FP32
-// pass (FP32), parked straggler state and network start points (FP64); null
-// when unused.
+// pass (FP32; null: in the caller's output rows), parked straggler state and
+// network start points (FP64; null when unused).
 struct Work {
     int *ws;
     float *rows;
     double *spf, *x0l;
 };
 
+// Above this many paths the FP32 pass keeps its state rows in a buffer of its
+// own, in bin order, so that neighbouring lanes read and write neighbouring lines
+// (16.8 M paths in the mixed-order schedule 14.19 -> 14.40 ms without, 4.2 M among
+// curved objects 9.27 -> 9.41).  Below, the output rows do as well (1.0 M paths
+// 2.91 ms with the buffer and 2.83 without), and a context's first solve does not
+// wait for the allocation (0.1 to 0.3 ms from 16,384 paths on).
+static const int64_t kRowsAbove = 1 << 21;
+
+// Work buffers of a solve of n paths (sized before any graph capture).  The
+// kernels of a captured solve hold their addresses, and a solve of another size or
+// precision may need larger ones, so a captured solve does not outlive the buffers
+// it was captured with.  The state rows are four fifths of a large FP32 solve's
+// memory; where they do not fit the solve runs without them.
+static mpt_status size_buffers(mpt_ctx *c, int64_t n, const mpt_solve_opts *o, Work &w)
+{
+    const size_t m = (size_t)(n > 0 ? n : 1);
+    const bool learned = o->init == MPT_INIT_LEARNED || o->init == MPT_INIT_LEARNED_ALL;
+    const bool fp64 = o->precision == MPT_FP64_PLAIN;
+    const int *ws = c->ws;
+    const float *rows = c->rows;
+    const double *x0l = c->x0l;
+    const size_t spf = (kCounters + 4 * m + 1) / 2 * 2;  // in ints
+    mpt_status st = ensure(c, (void **)&c->ws, &c->ws_cap, spf + (fp64 ? 6 * m : 0), sizeof(int));
+    if (!st && learned) st = ensure(c, (void **)&c->x0l, &c->x0l_cap, MPT_ROW * m, sizeof(double));
+    const bool use_rows = !fp64 && n > kRowsAbove &&
+                          !ensure(c, (void **)&c->rows, &c->rows_cap, 32 * m, sizeof(float));
+    if (!st && !fp64 && n > kRowsAbove && !use_rows) hipGetLastError();  // handled
+    if (c->ws != ws || c->rows != rows || c->x0l != x0l) drop_graph(c);
+    w = Work{c->ws, use_rows ? c->rows : nullptr, fp64 ? (double *)(c->ws + spf) : nullptr, c->x0l};
+    return st;
+}
+
 // Enqueue the whole solve on stream s (no host synchronisation).  With
 // `timed`, HIP events mark the stage boundaries (not inside graph capture).
-// The workspace is the context's own (sized here) unless `w` brings one.
+// The workspace is the context's own, sized here, unless `w` brings one.
 static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_opts *opts,
                                 const mpt_solve_out *out, hipStream_t s, bool timed, int sched, int block,
                                 int gdiv, int spill, int form_used, const Work *w = nullptr)
@@ -662,12 +675,10 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
     const bool fp64 = opts->precision == MPT_FP64_PLAIN;
     Work own{nullptr, nullptr, nullptr, nullptr};
     if (!w) {
-        if ((st = size_buffers(c, n, opts))) return st;
-        int *state = c->ws + state_offset((size_t)(n > 0 ? n : 1));
-        own = Work{c->ws, fp64 ? nullptr : (float *)state, fp64 ? (double *)state : nullptr, c->x0l};
+        if ((st = size_buffers(c, n, opts, own))) return st;
         w = &own;
     }
-    if ((learned && !w->x0l) || (spill > 0 && (fp64 ? !w->spf : !w->rows)))
+    if ((learned && !w->x0l) || (spill > 0 && fp64 && !w->spf))
         return fail(c, MPT_E_INVALID_ARG, "workspace too small");
     if (!timed) c->timed = c->kev_valid = false;  // no stale stage timings
     int *ctr = w->ws;
@@ -856,9 +867,10 @@ mpt_status mpt_solve_batch(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_
         // now 590)
         hipStream_t cap = c->aux[0];
         // buffers are sized before capture: no allocation inside it
-        if ((st = size_buffers(c, b->n, opts))) return st;
+        Work w;
+        if ((st = size_buffers(c, b->n, opts, w))) return st;
         HIPCHK(c, hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-        st = enqueue_solve(c, b, opts, out, cap, false, sched, block, gdiv, spill, form);
+        st = enqueue_solve(c, b, opts, out, cap, false, sched, block, gdiv, spill, form, &w);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(cap, &g);
         if (st) {

@@ -727,7 +727,9 @@ __global__ void __launch_bounds__(kFinBlock, 4) k_finish(KParams kp, int items)
         const int64_t i = b0 + j * kFinBlock;
         const bool live = i < kp.b.n && kp.out.status[i] == ST_RUNNING;
         if (!__any(live)) continue;
-        rows_load(w, live ? state_row(kp, kp.rows ? kp.perm[i] : 0, i) : state_row(kp, 0, 0));
+        // a lane without a path reads a row that no other wave writes: its own, or
+        // the batch's last, which is this wave's as well
+        rows_load(w, state_row(kp, live && kp.rows ? kp.perm[i] : 0, min(i, kp.b.n - 1)));
         if (live) {
             int ord;
             const int end = finish_path<FORM, REFR>(kp, i, ord, w + __lane_id() * kRowWords);

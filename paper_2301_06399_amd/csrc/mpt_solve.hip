@@ -522,7 +522,7 @@ __device__ __forceinline__ bool served(const KParams &kp, const PathRef &p)
 template <int MODE, int FORM>
 __global__ void __launch_bounds__(kStartBlock) k_start(KParams kp)
 {
-    __shared__ float rows[kStartBlock / 64 * kWaveRows];
+    __shared__ __align__(16) float rows[kStartBlock / 64 * kWaveRows];
     const int64_t i = (int64_t)blockIdx.x * kStartBlock + threadIdx.x;
     int slot = -1;
     bool live = i < kp.b.n;
@@ -549,7 +549,7 @@ template <int MODE, int FORM>
 __global__ void __launch_bounds__(kStartBlock) k_learned_begin(KParams kp, const int *__restrict__ list,
                                                                const int *__restrict__ count)
 {
-    __shared__ float rows[kStartBlock / 64 * kWaveRows];
+    __shared__ __align__(16) float rows[kStartBlock / 64 * kWaveRows];
     const int64_t m = list ? (int64_t)*count : kp.b.n;
     // all lanes of a wave go round together
     for (int64_t t0 = (int64_t)blockIdx.x * kStartBlock + (threadIdx.x & ~63); t0 < m;
@@ -715,7 +715,7 @@ __device__ __forceinline__ int finish_path(const KParams &kp, int64_t i, int &or
 template <int FORM, bool REFR>
 __global__ void __launch_bounds__(kFinBlock, 4) k_finish(KParams kp, int items)
 {
-    __shared__ float rows[kFinBlock / 64 * kWaveRows];
+    __shared__ __align__(16) float rows[kFinBlock / 64 * kWaveRows];
     __shared__ int lcnt[2 * kMaxN], lbase[2 * kMaxN];  // polish lists, then fallback lists
     float *w = rows + (threadIdx.x >> 6) * kWaveRows;
     if (threadIdx.x < 2 * kMaxN) lcnt[threadIdx.x] = 0;

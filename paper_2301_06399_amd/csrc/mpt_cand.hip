@@ -92,6 +92,7 @@ __device__ __forceinline__ void cull_tile(const SceneDev &s, const Shaft &sh, in
     const int nocc = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln), lane = threadIdx.x & 63;
     c.tile = tile;
     c.n = 0;
+    wave_sync();  // readers of the last list
     const int hi = min(kTile, nocc - tile * kTile);
     for (int q = 0; q < hi; q += 64) {
         const int o = q + lane;
@@ -106,8 +107,7 @@ __device__ __forceinline__ void cull_tile(const SceneDev &s, const Shaft &sh, in
         if (keep) c.list[c.n + (int)__popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)o;
         c.n += (int)__popcll(m);
     }
-    // the list is written and read by one wave: its LDS accesses are in order
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 }
 
 // The lanes (of `alive`) whose segment no occluder blocks.
@@ -122,7 +122,6 @@ __device__ __forceinline__ bool unblocked(const SceneDev &s, const Occluders &oc
             const int o = tile * kTile + __builtin_amdgcn_readfirstlane((int)c.list[q]);
             if (alive && blocks(s, oc.prec, oc.qrec, o, g, gi, gj)) alive = false;
         }
-        __builtin_amdgcn_wave_barrier();
     }
     return alive;
 }

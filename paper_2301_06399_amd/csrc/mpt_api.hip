@@ -355,7 +355,6 @@ mpt_status mpt_scene_upload(mpt_ctx *c, const mpt_scene_desc *d)
                                  c->stream));
     }
     launch_pack(c->raw, refr ? c->rfd : nullptr, s, np, nl, nq, nc, c->stream);
-    launch_occluders(s, c->stream);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->s = s;

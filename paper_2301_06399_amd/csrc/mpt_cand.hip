@@ -3,7 +3,6 @@
 // Figs. 3-4), and the enumeration of every simple path BS -> objects -> UE
 // of at most max_order objects as interaction lists.
 //
-//  k_occluders      bounding boxes of the facets and patches (scene upload)
 //  k_samples        sample points of every object (mpt_geom.hpp)
 //  k_vis_pairs      one wave per object and group of objects: lanes test sample
 //                   pairs (sides / wedges, then the facets and patches whose
@@ -19,16 +18,6 @@
 #include "mpt_geom.hpp"
 
 namespace mpt {
-
-// Boxes of the facets and patches (scene upload).
-__global__ void __launch_bounds__(64) k_occluders(SceneDev s, float *__restrict__ occ)
-{
-    const int o = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nq = s.n_pl_ln_q - s.n_pl_ln;
-    if (o >= s.n_pl + nq) return;
-    const int g = o < s.n_pl ? o : s.n_pl_ln + (o - s.n_pl);
-    occluder_box(o < s.n_pl ? TP : TQ, s.rec64 + (size_t)g * kRec, occ + (size_t)o * 8);
-}
 
 __global__ void __launch_bounds__(64) k_samples(SceneDev s, int k, double *__restrict__ samp, int *__restrict__ cnt,
                                                 float *__restrict__ box, uint32_t *__restrict__ z0, int64_t n0,
@@ -696,13 +685,6 @@ static int lds_choice(const void *kern, const SceneDev &s, size_t lds_max, size_
     if (lds) hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     else bytes = 0;
     return lds;
-}
-
-void launch_occluders(const SceneDev &s, hipStream_t st)
-{
-    const int n = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln);
-    if (n == 0) return;
-    hipLaunchKernelGGL(k_occluders, dim3((n + 63) / 64), dim3(64), 0, st, s, (float *)s.occ);
 }
 
 void launch_samples(const SceneDev &s, int k, double *samp, int *cnt, float *box, uint32_t *z0, int64_t n0,

@@ -1,7 +1,8 @@
 // Kernels around the Levenberg-Marquardt solver of the batched Min-Path-Tracing
 // solve (gfx950, wave64); the solver itself is in mpt_lm.hip.
 //
-//  k_pack            scene records -> packed FP64 world + FP32 TX-local records
+//  k_pack            scene records -> packed FP64 world + FP32 TX-local records,
+//                    boxes of the facets and patches
 //  k_bin_count       histogram of path orders (invalid solves finished here)
 //  k_bin_scatter     solve ids grouped by order (one bin per order)
 //  k_start           start points and unknowns of the binned paths
@@ -9,6 +10,7 @@
 //  k_polish          FP64 Gauss-Newton polish of the FP32 end points
 //  k_accept_*        FP64 acceptance test and ordered compaction
 #include "mpt_path.hpp"
+#include "mpt_geom.hpp"
 
 namespace mpt {
 
@@ -17,7 +19,7 @@ namespace mpt {
 // orthonormal basis, revisited", JCGT 2017).
 __global__ void k_pack(const double *__restrict__ raw, const double *__restrict__ refr, int n_pl, int n_ln, int n_q,
                        int n_c, double tx0, double tx1, double tx2, double *__restrict__ rec64,
-                       float *__restrict__ rec32)
+                       float *__restrict__ rec32, float *__restrict__ occ)
 {
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
     const int n_all = n_pl + n_ln + n_q + n_c;
@@ -71,6 +73,8 @@ __global__ void k_pack(const double *__restrict__ raw, const double *__restrict_
         for (int i = 0; i < 3; i++) l[i] = o[i] - tx[i];
     }
     for (int i = 0; i < kRec; i++) rec32[(size_t)id * kRec + i] = (float)l[i];
+    // the box of a facet or patch
+    if (t == TP || t == TQ) occluder_box(t, o, occ + (size_t)(t == TP ? id : id - n_ln) * 8);
 }
 
 // ------------------------------------------------------------------ workspace counters
@@ -1177,7 +1181,7 @@ void launch_pack(const double *raw, const double *refr, const SceneDev &s, int n
     const int n = n_pl + n_ln + n_q + n_c;
     if (n == 0) return;
     hipLaunchKernelGGL(k_pack, dim3((n + 127) / 128), dim3(128), 0, st, raw, refr, n_pl, n_ln, n_q, n_c, s.tx[0],
-                       s.tx[1], s.tx[2], (double *)s.rec64, (float *)s.rec32);
+                       s.tx[1], s.tx[2], (double *)s.rec64, (float *)s.rec32, (float *)s.occ);
 }
 
 void launch_zero(int *p, int n, hipStream_t st)

@@ -92,7 +92,6 @@ __device__ __forceinline__ void wave_sync()
 void launch_pack(const double *raw, const double *refr, const SceneDev &s, int n_pl, int n_ln, int n_q, int n_c,
                  hipStream_t st);
 void launch_zero(int *p, int n, hipStream_t st);
-int bin_key_count();
 // rows (or null): the list of the solves with a paraboloid or a circle,
 // grouped by order; curved: [5] per-order cursors, and curved[25] receives
 // the list's length

@@ -1189,8 +1189,6 @@ void launch_zero(int *p, int n, hipStream_t st)
     hipLaunchKernelGGL(k_zero_i32, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
 }
 
-int bin_key_count() { return kNumKeys; }
-
 // ctr: the workspace's n_ctr counters, cleared here; the first five receive
 // the solves per order, those from 32 on are [3][kNumKeys] (counts, offsets,
 // cursors).

@@ -311,7 +311,7 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
     PathIn<T, N> p;
     int slot = 0, code = 0;
     int ridx = 0;       // the path's state row (FP32) or solve id
-    int it0 = 0;        // iteration count at the start of a resumed path
+    int it0 = 0;        // a resumed path's iteration: opened, its step not yet taken
     int fin = 0;        // final status of a finished path that is not saved yet
     bool active = false, done = false;
     // wave-uniform chunk [cbase, cend) of the bin
@@ -342,7 +342,8 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
                         *(f32x4 *)(rf + j) = v;
                     }
                     *(f32x4 *)(rf + RW_C) = f32x4{L.C, L.rinf, __int_as_float(L.it), __int_as_float(fin)};
-                    if (kp.spill_t > 0) rf[RW_ID] = __int_as_float(resume ? it0 : L.it);
+                    // iterations the first launch finished
+                    if (kp.spill_t > 0) rf[RW_ID] = __int_as_float(resume ? max(it0 - 1, 0) : L.it);
                 } else {
                     int ty[N];
 #pragma unroll
@@ -354,7 +355,7 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
                     kp.out.iters[ridx] = FB ? L.it + kp.out.iters[ridx] : L.it;
                     if (kp.out.stage) {
                         kp.out.stage[(FB ? (size_t)2 * kp.b.n : 0) + ridx] = L.it;
-                        if (resume) kp.out.stage[(size_t)3 * kp.b.n + ridx] = L.it - it0;
+                        if (resume) kp.out.stage[(size_t)3 * kp.b.n + ridx] = L.it - max(it0 - 1, 0);
                     }
                     kp.out.status[ridx] = (uint8_t)(FB ? fin | 0x80 : fin);
                 }

@@ -82,12 +82,9 @@ def type_codes(scene, batch):
 
 
 def algorithmic_flops(table, order, code, iters, kind, kept=False):
-    """FLOPs of `iters` iterations of each path at its order and types.
-    kept: the solver assembles the normal equations once per iteration, at
-    the trial point, whose cost comes with them, so an iteration is less than
-    the table's (assembly, step and a cost of its own); of orders 1-3 every
-    iteration after a path's first is charged without its assembly (a lower
-    bound of the work done, since an assembly is more than a cost)."""
+    """FLOPs of `iters` iterations of each path at its order and types, each
+    with an assembly, a step and a trial cost of its own.  kept: iterations of
+    orders 1-3 after a path's first without their assembly."""
     tot = 0
     for n in range(1, 6):
         m = order == n
@@ -98,6 +95,31 @@ def algorithmic_flops(table, order, code, iters, kind, kept=False):
                 f = f - table[n]["assembly"][code[m]] * np.maximum(it - 1, 0)
             tot += int(f.sum())
     return tot
+
+
+def solver_flops(table, order, code, iters, form):
+    """(lower, upper) FLOPs of the LM kernels for paths of `iters` iterations.
+    A kernel assembles the normal equations once per point, at the start and at
+    every trial point, whose cost comes with them; an iteration is a step
+    (damping, factorisation, solve, trial point) and that assembly.  A path's
+    last iteration may end before its step: at the least `iters` assemblies and
+    one step fewer, at the most one assembly more and `iters` steps.  (A trial
+    point outside the guard box, or none for want of a factorisation, is charged
+    its assembly all the same; both are rare.)"""
+    low = up = 0
+    for n in range(1, 6):
+        m = (order == n) & (iters > 0)
+        if m.any():
+            c, it = code[m], iters[m].astype(np.int64)
+            asm = table[n]["assembly"][c]
+            step = table[n]["lm"][c] - asm - table[n]["residual"][c]
+            if form == 0:
+                # the table's trial cost adds the step to a point wherever a row
+                # needs it (3 n - 2 points) and once more when it is taken
+                step = step - 3 * (3 * n - 2)
+            low += int((asm * it + step * (it - 1)).sum())
+            up += int((asm * (it + 1) + step * it).sum())
+    return low, up
 
 
 def opts_for(mpt, v, graph=0):
@@ -196,20 +218,20 @@ class Runner:
 
 def lm_roofline(scene, batch, r, st, prec, cfg, mpt, form=0, sched=None):
     """Roofline of the dominant solver kernel: algorithmic FLOPs of the first
-    LM pass (iterations actually run in it x FLOPs per iteration of each
-    path's order and types, in the variant's form) over its measured
-    duration."""
+    LM pass (the iterations each path ran in it, at its order and types, in the
+    variant's form) over its measured duration.  `frac` charges the least those
+    iterations can have run, `frac_upper` the most."""
     table = mpt.flops_table(form)
     code = type_codes(scene, batch)
     it1 = r["stage"][0] - r["stage"][3]   # iterations before a straggler was parked
-    kept = prec == "fp32"
     per_order_flops, per_order_upper = [], []
     for nn in range(1, 6):
         m = batch.order == nn
-        per_order_flops.append(algorithmic_flops(table, batch.order[m], code[m], it1[m], "lm", kept))
-        per_order_upper.append(algorithmic_flops(table, batch.order[m], code[m], it1[m], "lm"))
+        lo, up = solver_flops(table, batch.order[m], code[m], it1[m], form)
+        per_order_flops.append(lo)
+        per_order_upper.append(up)
     flops_pass = sum(per_order_flops)
-    flops_resume = algorithmic_flops(table, batch.order, code, r["stage"][3], "lm", kept)
+    flops_resume = solver_flops(table, batch.order, code, r["stage"][3], form)[0]
     mode = 1 if prec == "fp32" else 0
     if st.get("lm_per_order"):
         # concurrent per-order launches: they share the GPU for the whole
@@ -242,7 +264,6 @@ def lm_roofline(scene, batch, r, st, prec, cfg, mpt, form=0, sched=None):
             traffic = float(kv["hbm_bytes_per_launch"])
     return {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK[prec] / 1e12, "unit": "TFLOP/s",
             "frac": achieved / PEAK[prec],
-            # every iteration charged with its assembly: the upper bound of the work
             "frac_upper": sum(per_order_upper) / (ms_dom * 1e-3) / PEAK[prec],
             "traffic": traffic, "kernel": kname,
             "flops_per_launch": flops_dom, "launch_ms": ms_dom,

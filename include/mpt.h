@@ -499,10 +499,10 @@ mpt_status mpt_flops_per_iter(int order, const int32_t *types, int32_t form, int
 /* The part of out[0] of mpt_flops_per_iter that builds the residual, the
  * Jacobian and the banded normal equations and gradient (Sec. III-B, Eq. 12
  * with the rescaled rows; Eq. 15 with form = MPT_FORM_PARAMETRIC), in *out.
- * After a rejected step the point has not moved, so the FP32 solver of
- * orders 1-3 keeps these from the previous iteration and runs only the rest
- * of out[0] (damping, banded Cholesky, solve, trial cost); counts of the
- * algorithmic work charge such iterations out[0] minus this figure.
+ * The solver builds them once per point, at the start and at every trial
+ * point, whose cost comes with them: an iteration as it runs is this figure
+ * and the step (damping, banded Cholesky, solve), that is out[0] without its
+ * trial cost (out[2]).
  * Host only.  MPT_E_INVALID_ARG as mpt_flops_per_iter. */
 mpt_status mpt_flops_assembly(int order, const int32_t *types, int32_t form, int64_t *out);
 
@@ -513,9 +513,10 @@ mpt_status mpt_flops_assembly(int order, const int32_t *types, int32_t form, int
  * never timed.  Host only.  MPT_E_INVALID_ARG for a null context. */
 mpt_status mpt_set_timing(mpt_ctx *ctx, int32_t on);
 /* Per-stage timings of the last mpt_solve_batch in milliseconds (HIP events
- * on the context's stream; synchronises): [0] order binning, [1] learned
- * start, [2] first LM pass (FP32 or plain FP64), [3] its straggler launch,
- * [4] FP64 polish, [5] FP64 fallback.  MPT_E_INVALID_ARG when the last solve
+ * on the context's stream; synchronises): [0] order binning and the starts
+ * of the paths, [1] learned start (network, choice, the starts it serves),
+ * [2] first LM pass (FP32 or plain FP64), [3] its straggler launch, [4] ends of
+ * the FP32 pass (results, routing) and FP64 polish, [5] FP64 fallback.  MPT_E_INVALID_ARG when the last solve
  * was not timed. */
 mpt_status mpt_last_timings(mpt_ctx *ctx, float ms[6]);
 /* Durations (ms) of the per-order kernels of the first LM pass of the last

@@ -522,8 +522,8 @@ __host__ __device__ __forceinline__ void across_dir(const T *a, T u1[3], T u2[3]
 // split into three floats of 8, 11 and 24 significant bits (k p1 and k p2
 // are exact for |k| < 4096, |a| < 6400), then the Taylor series of sin to
 // r^9 and cos to r^8 on |r| <= pi/4 (truncation error below 3e-8).  The
-// library routine's wide-range reduction raised the register budget of
-// every parametric FP32 kernel (order 5: 80 -> 64 bytes of spill per lane).
+// library routine's wide-range reduction would count in the registers of every
+// parametric FP32 kernel.
 __host__ __device__ __forceinline__ void sincos32(float a, float &s, float &c)
 {
     const float k = rintf(a * 0x1.45f306p-1f);  // a / (pi/2), rounded
@@ -589,10 +589,10 @@ __host__ __device__ __forceinline__ bool param_map(int t, const T *__restrict__ 
 }
 
 // The angle of a circle's start point, out of line: inlined, the FP64
-// arctangent's registers count in every solver kernel (whose start code
-// holds it) whether or not a circle is solved; called, it costs a register
-// save only on the paths that take it.  Order-5 parametric FP32 kernel:
-// 236 -> 80 bytes of spill per lane.
+// arctangent's registers count in every kernel that starts paths (k_start,
+// k_learned_begin, and the FP64 fallback, which restarts its own) whether or not
+// a circle is among them; called, it costs a register save only on the paths that
+// take it.
 __host__ __device__ __attribute__((noinline)) inline double circle_angle(double y, double x) { return atan2(y, x); }
 
 // Parameters of a point of an object (the start points, already put on it).

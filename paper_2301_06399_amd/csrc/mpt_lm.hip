@@ -9,10 +9,11 @@
 // latency of the chain.  So the loop holds nothing but iterations: starts and
 // ends of paths are kernels of their own (k_start, k_finish), a lane reads and
 // writes one 128-byte state row, and finished lanes are saved together.  With
-// them in the loop an order-5 kernel was 78 KB of code at 256 registers, and the
-// stress workload's pass (16.8 M paths of orders 3-5) took 18.0 ms, now 8.8 ms
-// (and 2.5 + 1.7 ms in k_start and k_finish); the street canyon's (262,144
-// paths of orders 1-3) 466 us, now 295.
+// them in the loop an order-5 kernel was 78 KB of code at 256 registers.  The
+// stress workload's pass (16.8 M paths of orders 3-5) took 22.0 ms then, in its
+// tuned launch; now it takes 9.5, and k_start and k_finish, whose work it held,
+// 1.4 and 1.5.  The street canyon's (262,144 paths of orders 1-3) took 466 us, now
+// 274, 19 and 56.
 //  k_lm_low          the same over orders 1-3
 //  k_lm_one          one order's bin
 // The file is compiled once per (mode, form, scene in LDS or not), MPT_LM_MODE
@@ -537,8 +538,10 @@ __device__ __forceinline__ void lm_bin(const KParams &kp, const typename ModeT<M
         bool generic = active;
         if constexpr (TYPED && MODE == MODE_FP32 && FORM == 1 && N <= 3) {
             // every planar path takes its fixed-type step, whatever the other
-            // lanes of its wave hold, so that its result does not depend on
-            // the schedule: one sequence after the other
+            // lanes of its wave hold: one sequence after the other.  (The kernel
+            // of orders 1-3 beside orders 4 and 5 is not TYPED: its generic step
+            // adds the placeholders' columns, which are zeros, and ends in the
+            // same result.)
             generic = active && !(REFR ? p.planar : (code & 0x2AA) == 0);
             uint64_t todo = __ballot(active && !generic);
             while (todo) {

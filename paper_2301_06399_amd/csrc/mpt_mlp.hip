@@ -534,8 +534,8 @@ __global__ void k_decode(SceneDev s, BatchDev b, int nrows, const float *__restr
 // the activations the B operand (8 consecutive BF16 of one path from LDS),
 // so the accumulator holds 4 consecutive output units of one path per
 // register group and the epilogue writes them to LDS with one 8-byte store.
-// Wave w takes output units 64 (w % 4) .. +64 of paths 64 (w / 4) .. +64:
-// 2 x 2 tiles of v_mfma_f32_32x32x16_bf16.  With two waves per SIMD one
+// Wave w takes output units 64 w .. +64 of the block's 64 paths: 2 x 2 tiles of
+// v_mfma_f32_32x32x16_bf16.  With two waves per SIMD (two blocks per CU) one
 // wave's matrix work overlaps the other's epilogue.
 //
 // GELU(z) = z Phi(z) with Phi read from a table in LDS: 1024 steps of 1/64
@@ -655,7 +655,7 @@ __global__ void __launch_bounds__(256) k_mlp_fused(SceneDev s, BatchDev b, const
         const float p0 = 0.5f * erfcf(-z0 * 0.70710678118654752f), p1 = 0.5f * erfcf(-z1 * 0.70710678118654752f);
         tab[i] = make_float2(p0, p1 - p0);
     }
-    // persistent: the block walks the 128-path tiles
+    // persistent: the block walks tiles of IR paths
     for (int row0 = blockIdx.x * IR; row0 < nrows; row0 += gridDim.x * IR) {
     {
         // features, four threads per path: thread q of a path writes slot q

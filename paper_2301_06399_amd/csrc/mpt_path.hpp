@@ -349,9 +349,8 @@ __device__ __forceinline__ void write_row(double *row, const double *X)
 // the start kernel, read by a solver lane when it starts the path and written
 // when it ends, then turned into the path's results by k_finish, so that a
 // lane starts and ends a path with one contiguous access and one round trip
-// to memory.  The rows lie in bin order in the workspace (consecutive lanes,
-// consecutive rows); without a workspace row they share the path's output
-// row.
+// to memory.  In a large batch the rows lie in bin order in a buffer of their own
+// (consecutive lanes, consecutive rows); else they share the path's output row.
 //   [0..14] unknowns  [16] cost  [17] |R|_inf  [18] iterations  [19] status
 //   [20..22] receiver in the solver's frame  [23] base-4 type code, -1: ended
 //   by the start kernel  [24..28] object ids ([24] later: iterations before

@@ -52,22 +52,23 @@ __global__ void __launch_bounds__(256) k_vis_list(const uint8_t *__restrict__ ac
 // slowest path of its wave: 0.76 ms against 0.40 ms with a wave per path on the
 // accepted paths of 16 receivers' candidates in the street canyon (251 facets),
 // 0.29 against 0.04 ms on the 32,000 of its 262,144 random lists.  With few
-// occluders a wave per path leaves most lanes idle and the paths' loads one after
-// the other: the call on 655,360 kept paths of the room (6 facets) takes 855 us
-// that way, 168 with four lanes each (a thread each: 389), on 107,202 among 40
-// patches 205 and 147.  Plane and quadric records are staged in LDS when `lds` is
-// set.
+// occluders and many paths a wave per path leaves most lanes idle and the paths'
+// loads one after the other, and a path gets four lanes: the call on 655,360 kept
+// paths of the room (6 facets) takes 168 us that way, 855 with a wave each (a
+// thread each: 389), on 107,304 among 40 patches 147 and 212; but on 415 among 61
+// facets 77 and 56.  Plane and quadric records are staged in LDS when `lds` is set.
 template <int G>
 __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC in, const int *__restrict__ list,
                                                  double min_seg, uint8_t *__restrict__ vis, int *__restrict__ count,
-                                                 int lds)
+                                                 int lds, int wide)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int kept;
     double *srec = reinterpret_cast<double *>(smem_raw);
     const int npl = s.n_pl, nq = s.n_pl_ln_q - s.n_pl_ln, nocc = npl + nq;
     const int na = list[0];
-    constexpr int kPaths = 64 / G;  // of a wave
+    if (G == 64 ? na > wide : na <= wide) return;  // the other kernel's list
+    constexpr int kPaths = 64 / G;                 // of a wave
     if ((int)(blockIdx.x * (blockDim.x >> 6)) * kPaths >= na) return;  // block-uniform
     if (threadIdx.x == 0) kept = 0;
     if (lds) {
@@ -83,8 +84,7 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
     // this path's lanes in a ballot (the lanes of one path stay together)
     const uint64_t group = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull) << ((threadIdx.x & 63) & ~(G - 1));
     int mine = 0;
-    for (int t = G == 64 ? wave : wave * kPaths + (int)((threadIdx.x & 63) / G); t < na;
-         t += nwave * kPaths) {
+    for (int t = G == 64 ? wave : wave * kPaths + (int)((threadIdx.x & 63) / G); t < na; t += nwave * kPaths) {
         const int64_t i = list[1 + t];
         const int n = b.order[i], ri = b.rx_index[i];
         bool ok = true;
@@ -130,8 +130,8 @@ __global__ void __launch_bounds__(256) k_visible(SceneDev s, BatchDev b, OutDevC
 }
 
 template <int G>
-static void launch_visible_lanes(const SceneDev &s, const BatchDev &b, const OutDevC &in, const int *list,
-                                 double min_seg, uint8_t *vis, int *count, size_t lds_max, int cu, hipStream_t st)
+static void launch_lanes(const SceneDev &s, const BatchDev &b, const OutDevC &in, const int *list, double min_seg,
+                         uint8_t *vis, int *count, size_t lds_max, int cu, int wide, hipStream_t st)
 {
     const size_t bytes = (size_t)(s.n_pl + (s.n_pl_ln_q - s.n_pl_ln)) * kRec * sizeof(double);
     const int lds = bytes <= lds_max && bytes <= 64 * 1024;
@@ -141,7 +141,8 @@ static void launch_visible_lanes(const SceneDev &s, const BatchDev &b, const Out
     const int64_t fit = lds ? std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)(lds_max / (bytes + 64)))) : 8;
     const int64_t per = 4 * (64 / G);
     const unsigned g = (unsigned)std::min<int64_t>((b.n + per - 1) / per, (int64_t)cu * fit);
-    hipLaunchKernelGGL(k_visible<G>, dim3(g), dim3(256), lds ? bytes : 0, st, s, b, in, list, min_seg, vis, count, lds);
+    hipLaunchKernelGGL(k_visible<G>, dim3(g), dim3(256), lds ? bytes : 0, st, s, b, in, list, min_seg, vis, count, lds,
+                       wide);
 }
 
 void launch_visible(const SceneDev &s, const BatchDev &b, const OutDevC &in, const uint8_t *acc, double min_seg,
@@ -154,10 +155,18 @@ void launch_visible(const SceneDev &s, const BatchDev &b, const OutDevC &in, con
     const int items = (int)std::min<int64_t>(kListItems, (b.n + 256 * (int64_t)cu * 4 - 1) / (256 * (int64_t)cu * 4));
     hipLaunchKernelGGL(k_vis_list, dim3((unsigned)((b.n + 256 * items - 1) / (256 * items))), dim3(256), 0, st, acc,
                        b.n, list, vis, items);
-    // few occluders: four lanes a path; many: a wave (the line lies between 81
-    // occluders, where a call takes 100 us and 104, and 200, 296 and 267)
-    const bool few = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln) <= 96;
-    (few ? launch_visible_lanes<4> : launch_visible_lanes<64>)(s, b, in, list, min_seg, vis, count, lds_max, cu, st);
+    // Up to `wide` paths a wave each, more four lanes each: those take nocc / 4 tests
+    // one after the other, a wave one, but 16 paths go through a wave at once.  The
+    // lines were about 2,500 paths at 6 occluders, 16,000 at 41, 25,000 at 61, 36,000
+    // at 91, that is nocc / 20 paths to each of 8192 resident waves; above 96
+    // occluders every list gets waves (200, 100,000 paths: 267 us against 296).  The
+    // list's length is on the device: both kernels are launched where it decides, and
+    // one of them ends at once.
+    const int nocc = s.n_pl + (s.n_pl_ln_q - s.n_pl_ln);
+    const int64_t line = nocc <= 96 ? (int64_t)nocc * cu * 8 * 4 / 20 : INT32_MAX;
+    const int wide = (int)std::min<int64_t>(line, INT32_MAX);
+    launch_lanes<64>(s, b, in, list, min_seg, vis, count, lds_max, cu, wide, st);
+    if (b.n > wide) launch_lanes<4>(s, b, in, list, min_seg, vis, count, lds_max, cu, wide, st);
 }
 
 }  // namespace mpt

@@ -1,6 +1,6 @@
-"""Validation with four lanes or a whole wave to a path: numbers of occluders at
-the edges of both, lists at the edges of a wave's and a block's paths.  The flags
-are the oracle's decisions and must be equal."""
+"""Validation with four lanes or a whole wave to a path: numbers of occluders and
+of kept paths at the edges of both, lists at the edges of a wave's and a block's
+paths.  The flags are the oracle's decisions and must be equal."""
 import numpy as np
 import pytest
 
@@ -27,7 +27,10 @@ def test_lanes_of_a_path(ctx, n_planes, n_quads):
     rng = np.random.default_rng([n_planes, n_quads, 7])
     sc = scene(rng, n_planes, n_quads=n_quads)
     ctx.upload_scene(sc)
-    for n in (1, 15, 17, 63, 65, 257, 4099):
+    # kept paths up to which each gets a wave
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    line = (n_planes + n_quads) * cus * 32 // 20
+    for n in (1, 15, 17, 63, 65, 257, 4099, line + 50, line + 51):
         order = rng.integers(1, 6, n).astype(np.int32)
         prim = rng.integers(0, sc.n_prims, (5, n)).astype(np.int32)
         b = W.Batch(rng.uniform(0, 40, (9, 3)), rng.integers(0, 9, n), order, prim)
@@ -35,7 +38,9 @@ def test_lanes_of_a_path(ctx, n_planes, n_quads):
         start = b.rx[b.rx_index] + rng.normal(size=(n, 3)) * 3
         for j in range(5):
             x[3 * j:3 * j + 3] = np.where(order > j, (start + rng.normal(size=(n, 3)) * 2).T, 0.0)
-        acc = (rng.random(n) < 0.7).astype(np.uint8)
+        keep = n - 50 if n >= line + 50 and n > 4099 else int(0.7 * n) + 1
+        acc = np.zeros(n, np.uint8)
+        acc[rng.permutation(n)[:keep]] = 1
         out = mpt.DeviceOut(n)
         out.x.copy_(torch.from_numpy(mpt.to_rows(x)))
         vis, kept = ctx.visible(mpt.DeviceBatch(b), out, torch.from_numpy(acc).cuda())

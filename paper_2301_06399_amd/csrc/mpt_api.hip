@@ -447,13 +447,26 @@ static mpt_status batch_dev(mpt_ctx *c, const mpt_batch_desc *b, BatchDev &bd)
     return MPT_OK;
 }
 
-// The waves a launch of the FP32 implicit kernels gets on each CU: one while the
-// lanes of one hold the batch, two while the lanes of two do, else one per SIMD
-// (4).  Launches that run side by side share the batch.
-static int implicit_waves(const mpt_ctx *c, int sched, int64_t n)
+// Does an untuned FP32 implicit solve launch blocks of one wave, of which a launch
+// that finds few paths spreads one or two over each CU (used_waves in mpt_lm.hip)?
+// The mixed-order kernel's 88 KB of code are more than the instruction cache that
+// two CUs share, and a type is a branch of its own, so waves at different points of
+// an iteration evict each other's code: 16,384 paths among curved objects take 1886
+// us with four waves of 16 paths on a CU and 1226 with one of 64, 32,768 paths 1641
+// with four and 1332 with two (also among facets alone: 595 and 533 us on 16,384).
+// Of the launches side by side, orders 4 and 5 (279 and 340 registers) cannot share
+// a SIMD; with fewer waves they find CUs of their own: 2586 and 1859 us on 16,384,
+// 2622 and 1804 on 65,536.  There each block also stages the scene, so it pays only
+// where a path's iterations are long (curved objects; 16,384 paths among facets 800
+// us without and 900 with it) and many paths share a block (700 paths: 1440 us
+// without, 1560 with it).  The parametric kernels, whose planar sequences have code
+// of their own each, gain from fewer paths to a wave instead (4000 of the room: 222
+// us with four waves on a CU, 250 with one).
+static bool spreads(const mpt_ctx *c, int sched, int64_t n)
 {
-    const int64_t m = sched == MPT_SCHED_PERSISTENT ? n : n / 4, lanes = (int64_t)c->cu * 64;
-    return m <= lanes ? 1 : m <= 2 * lanes ? 2 : 4;
+    const int64_t lanes = (int64_t)c->cu * 64;
+    if (sched == MPT_SCHED_PERSISTENT) return n <= 2 * lanes;
+    return c->curved && n > lanes / 8 && n <= 8 * lanes;
 }
 
 // Blocks of a persistent launch: as many as can be resident at once, and no
@@ -557,19 +570,7 @@ static void choose(mpt_ctx *c, const mpt_solve_opts *o, int64_t n, int &sched, i
     // the rows of refracting facets are compiled into the mixed-order
     // kernel only
     if (c->refr) sched = MPT_SCHED_PERSISTENT, gdiv = 1;
-    // Small batches in the FP32 implicit kernels: blocks of one wave, one or two
-    // of them on a CU.  The mixed-order kernel's 88 KB of code are more than the
-    // instruction cache that two CUs share, and a type is a branch of its own, so
-    // waves at different points of an iteration evict each other's code; and
-    // orders 4 and 5 (279 and 340 registers) cannot run side by side on one SIMD.
-    // Among curved objects 16,384 paths take 1886 us with four waves of 16 paths
-    // on a CU and 1226 with one of 64, 32,768 paths 1641 with four and 1332 with
-    // two; one launch per order 2586 and 1859 (65,536 paths: 2622 and 1804).  The
-    // parametric kernels, whose planar sequences have code of their own each, gain
-    // from fewer paths to a wave instead (4000 of the room: 222 us with four waves
-    // on a CU, 250 with one).
-    if (!tuned && o->precision != MPT_FP64_PLAIN && form == MPT_FORM_IMPLICIT && implicit_waves(c, sched, n) < 4)
-        block = 64;
+    if (!tuned && o->precision != MPT_FP64_PLAIN && form == MPT_FORM_IMPLICIT && spreads(c, sched, n)) block = 64;
     if (o->block) block = o->block;
 }
 
@@ -763,12 +764,11 @@ static mpt_status enqueue_solve(mpt_ctx *c, const mpt_batch_desc *b, const mpt_s
                 g = resident_grid(c, k, blk, n, blk / 64, lds ? rec_bytes : 0);
                 // and one wave per SIMD while its lanes hold the whole batch: two
                 // would only take turns
-                const bool impl32 = md == MODE_FP32 && form == MPT_FORM_IMPLICIT;
-                const int waves = impl32 && blk == 64 ? implicit_waves(c, sch, n) : 4;
-                const int64_t most = (int64_t)c->cu * waves * 64 / blk;
-                if ((waves < 4 || n <= (int64_t)c->cu * 256) && g > most) g = (int)most;
+                const int64_t one = (int64_t)c->cu * 256 / blk;
+                if (n <= one * blk && g > one) g = (int)one;
                 if (first && gdiv > 1) g = (g + gdiv - 1) / gdiv;
             }
+            kp.spread = md == MODE_FP32 && form == MPT_FORM_IMPLICIT && blk == 64 && !opts->grid ? c->cu : 0;
             launch_lm(md, ord, lds, form, c->refr, rec_bytes, kp, g, blk, where);
         };
         if (sch == MPT_SCHED_PERSISTENT) {
@@ -933,7 +933,7 @@ mpt_status mpt_autotune(mpt_ctx *c, const mpt_batch_desc *b, const mpt_solve_opt
         // form gets
         auto blocks = [&](int sch) {
             const bool small = opts->precision != MPT_FP64_PLAIN && fm == MPT_FORM_IMPLICIT &&
-                               implicit_waves(c, sch, b->n) < 4;
+                               spreads(c, sch, b->n);
             return small ? std::vector<int>{64, 128, 256} : std::vector<int>{128, 256};
         };
         for (int sp : {0, 8, 16, 32})

@@ -76,6 +76,7 @@ struct KParams {
     int spill_t;               // park a drained bin's busy lanes when at most this many (0: never)
     int refill;                // a wave takes new paths once at least this many lanes are idle
     int resume;                // 1: this launch finishes the parked paths
+    int spread;                // CUs that a small launch's waves are spread over (blocks of one wave), or 0
     int *spill_cnt;            // [5] parked paths per order
     int *spill_head;           // [5] work counters of the straggler pass
     int *spill_list;           // [n] bin slots of the parked paths (bin-relative places)

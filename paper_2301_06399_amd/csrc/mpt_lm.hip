@@ -239,6 +239,16 @@ constexpr int kStaticChunk = 128, kMinChunk = 64, kMaxChunk = 4096;
 
 __device__ __forceinline__ int launch_waves() { return (int)(gridDim.x * (blockDim.x >> 6)); }
 
+// The waves of a launch that take part for `count` paths: all, or, where the host
+// asks for it (kp.spread CUs, blocks of one wave), one on each CU while its lanes
+// hold the launch's paths and two while two's do (see choose in mpt_api.hip).
+__device__ __forceinline__ int used_waves(const KParams &kp, int count)
+{
+    const int all = launch_waves(), cu = kp.spread;
+    if (cu == 0 || count > 2 * 64 * cu) return all;
+    return min(all, count > 64 * cu ? 2 * cu : cu);
+}
+
 struct BinShare {
     int rank, size;  // this wave among the waves that start with the bin; rank -1: none of them
 };
@@ -619,10 +629,9 @@ struct OrderShare {
     }
 };
 
-__device__ __forceinline__ OrderShare order_share(const int *cnt, int max_order)
+__device__ __forceinline__ OrderShare order_share(const int *cnt, int max_order, int all)
 {
     OrderShare s;
-    const int all = launch_waves();
     s.wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     float w[kMaxN + 1], tot = 0.0f, sum = 0.0f;
 #pragma unroll
@@ -661,12 +670,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OccAll
 k_lm(KParams kp)
 {
     const int *cnt = kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt;
-    if (cnt[0] + cnt[1] + cnt[2] + cnt[3] + cnt[4] == 0) return;  // nothing to solve: skip the staging
+    const int total = cnt[0] + cnt[1] + cnt[2] + cnt[3] + cnt[4], waves = used_waves(kp, total);
+    if (total == 0 || (int)blockIdx.x >= waves) return;  // nothing to solve: skip the staging
     const typename ModeT<MODE>::T *rec = stage_scene<MODE, LDS>(kp);
     // each wave starts with one order (all orders' longest descents begin at
     // once), then helps the others, long paths first so that the short ones
     // fill the tail
-    const OrderShare sh = order_share(cnt, 5);
+    const OrderShare sh = order_share(cnt, 5, waves);
 #pragma nounroll
     for (int pass = 0; pass < 2; pass++) {
         if (turn(sh.of(5), pass)) lm_bin<MODE, 5, FORM, true, REFR>(kp, rec, part(sh.of(5), pass));
@@ -687,7 +697,7 @@ __attribute__((amdgpu_waves_per_eu(Occ<MODE, 3, FORM>::W, Occ<MODE, 3, FORM>::W)
     const int *cnt = kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt;
     if (cnt[0] + cnt[1] + cnt[2] == 0) return;
     const typename ModeT<MODE>::T *rec = stage_scene<MODE, LDS>(kp);
-    const OrderShare sh = order_share(cnt, 3);
+    const OrderShare sh = order_share(cnt, 3, launch_waves());
 #pragma nounroll
     for (int pass = 0; pass < 2; pass++) {
         if (turn(sh.of(3), pass)) lm_bin<MODE, 3, FORM>(kp, rec, part(sh.of(3), pass));
@@ -701,12 +711,14 @@ template <int MODE, int N, bool LDS, int FORM>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(Occ<MODE, N, FORM>::W, Occ<MODE, N, FORM>::W))) k_lm_one(KParams kp)
 {
-    if ((kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt)[N - 1] == 0) return;
+    const int total = (kp.resume ? kp.spill_cnt : (MODE == MODE_FALLBACK64) ? kp.fb_cnt : kp.bin_cnt)[N - 1];
+    const int waves = N >= 4 ? used_waves(kp, total) : launch_waves();
+    if (total == 0 || (int)blockIdx.x >= waves) return;
     const typename ModeT<MODE>::T *rec = stage_scene<MODE, LDS>(kp);
     // fixed-type steps for the planar paths of orders 1-3 here as in the
     // mixed-order kernel (stress LM stage 22.0 -> 21.7 ms, bit-identical)
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-    lm_bin<MODE, N, FORM, (N <= 3)>(kp, rec, BinShare{wave, launch_waves()});
+    lm_bin<MODE, N, FORM, (N <= 3)>(kp, rec, BinShare{wave, waves});
 }
 
 // ------------------------------------------------------------------ kernel table

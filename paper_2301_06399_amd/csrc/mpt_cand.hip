@@ -196,8 +196,9 @@ __device__ __forceinline__ int flat_samples(const SceneDev &s, int k)
 // consecutive objects j of one type as their sample pairs fit its lanes (one
 // with several rounds where they do not), culls the occluders once for all of
 // them, and sets the bits of the pairs some sample pair of which is free.
-// Bound: FP64 vector issue.  One wave per pair with every facet tested by every
-// lane took 2.34 ms (and the BS row 0.10 ms) on the street canyon (651 objects,
+// Bound: the chain of box and FP64 tests at three waves per SIMD (waves wait in 35%
+// of their cycles, the VALU is busy about half of the time).  One wave per pair with
+// every facet tested by every lane took 2.34 ms (and the BS row 0.10 ms) on the street canyon (651 objects,
 // 4 samples per side); this takes 0.60 ms for both.
 __global__ void __launch_bounds__(256) k_vis_pairs(SceneDev s, int k, double min_seg, const double *__restrict__ samp,
                                                    const int *__restrict__ cnt, const float *__restrict__ obox,

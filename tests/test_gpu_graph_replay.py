@@ -87,3 +87,30 @@ def test_replay_after_facets_start_to_refract(prec, form):
             ctx.synchronize()
             assert same(out.numpy(), want[rep % 2]), (rep, again)
     ctx.close()
+
+
+@pytest.mark.parametrize("sched", ["SCHED_PER_ORDER", "SCHED_SPLIT", "SCHED_PERSISTENT"])
+def test_capture_behind_launches_side_by_side(sched):
+    """A solve is captured on one of the streams that direct solves launch on:
+    captured while such launches are still queued, in every schedule, it gives
+    the direct solve's results, and so do they."""
+    from paper_2301_06399_amd import mpt
+    sc, b = curved()
+    ctx = mpt.Context(0)
+    try:
+        ctx.upload_scene(sc)
+        db = mpt.DeviceBatch(b)
+        large = mpt.DeviceBatch(b.subset(np.tile(np.arange(b.n), 8)))
+        opts = dict(sched=getattr(mpt, sched), form=2)
+        want = ctx.solve(db, mpt.default_opts(**opts)).numpy()
+        many = ctx.solve(large, mpt.default_opts(**opts)).numpy()
+        queued = [mpt.DeviceOut(large.n) for _ in range(3)]
+        out = [mpt.DeviceOut(b.n) for _ in range(3)]
+        for q, o in zip(queued, out):
+            ctx.solve(large, mpt.default_opts(sched=mpt.SCHED_PER_ORDER, form=2), q)
+            ctx.solve(db, mpt.default_opts(graph=1, **opts), o)   # new outputs: a new capture
+            ctx.solve(db, mpt.default_opts(graph=1, **opts), o)
+        for q, o in zip(queued, out):
+            assert same(o.numpy(), want) and same(q.numpy(), many)
+    finally:
+        ctx.close()
